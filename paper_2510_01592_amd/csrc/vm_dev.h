@@ -81,11 +81,14 @@ __device__ __forceinline__ float4 hyp_plane(const float* __restrict__ X, const f
             nx = nx * inv;
             ny = ny * inv;
             nz = nz * inv;
-            if (nz < 0.0 || (nz == 0.0 && (ny < 0.0 || (ny == 0.0 && nx < 0.0)))) {
-                nx = -nx;
-                ny = -ny;
-                nz = -nz;
-            }
+            // one flag and a product with -1 or +1 (exact, and +0 becomes -0 as
+            // under negation): the nested short-circuit form was compiled so
+            // that for nz = 0 the inner tests were lost
+            const bool flip = (nz < 0.0) | ((nz == 0.0) & ((ny < 0.0) | ((ny == 0.0) & (nx < 0.0))));
+            const double sg = flip ? -1.0 : 1.0;
+            nx = nx * sg;
+            ny = ny * sg;
+            nz = nz * sg;
             const double d = -(nx * ax + ny * ay + nz * az);
             pl = make_float4((float)nx, (float)ny, (float)nz, (float)d);
         }
