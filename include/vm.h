@@ -331,13 +331,13 @@ vm_status vm_ransac_planes_noalloc(const vm_clusters* cl, const vm_ransac_params
 typedef struct {
     uint32_t count_grid;        /* workgroups of the tiled counting kernel: a multiple of 8
                                    (one per XCD), 8..65536; default 16384 */
-    uint32_t chunk_mult;        /* the hypotheses of a point tile (of a wave-counted cluster) are
-                                   split into chunks so that there are about chunk_mult work items
-                                   per workgroup (per wave), 1..16; default 2 */
+    uint32_t chunk_mult;        /* a point tile is cut into slices (the hypotheses of a wave-counted
+                                   cluster into chunks) so that there are about chunk_mult work items
+                                   per resident workgroup (per wave), 1..16; default 2 */
     uint32_t wave_max_points;   /* clusters of at most this many points are counted by one wave
                                    each, 0..1024 (0: all tiled); default 256 */
-    uint32_t plane_max_points;  /* of those, clusters of at most this many points put the lanes
-                                   over hypotheses instead of points, 0..min(256, wave_max_points);
+    uint32_t plane_max_points;  /* of those, clusters of at most this many points go through the
+                                   matrix cores, lanes over hypotheses instead of points, 0..min(256, wave_max_points);
                                    default 256 */
 } vm_count_config;
 
@@ -378,15 +378,14 @@ typedef struct {
 vm_status vm_hulls(const vm_clusters* cl, const vm_planes* planes, vm_hulls_out* out,
                    void* d_work, size_t work_bytes, void* stream);
 
-/* ---- planes and polygons in one persistent launch ---------------------- */
+/* ---- planes and polygons, counted in one persistent launch -------------- */
 /* Sec. III-C (a)-(c) and "Boundary polygon generation" for every cluster of
- * `cl`, run cluster-parallel as one persistent launch over a device work
- * queue (the batched form for thousands of clusters of very uneven size):
- * clusters sorted by size, largest first, are cut into (point tile,
- * hypothesis chunk) items; each item's integer counts go to their own slot;
- * the workgroup that completes a cluster's last item selects its best
- * hypothesis, lists its inliers and builds its polygon.  The outputs --
- * planes (including the optional d_counts / d_hyp), inlier CSR, polygons,
+ * `cl`, the inlier counting run cluster-parallel as one persistent launch
+ * over a device work queue (the batched form for thousands of clusters of
+ * very uneven size): clusters sorted by size, largest first, are cut into
+ * (point tile, hypothesis chunk) items whose integer counts go to their own
+ * slots; selection, inlier lists and polygons follow in tile-parallel
+ * passes.  The outputs -- planes (including the optional d_counts / d_hyp), inlier CSR, polygons,
  * areas, status flags -- are bit-identical to vm_ransac_planes followed by
  * vm_hulls, for every work split (vm_fused_config).  d_work: at least
  * vm_workspace_bytes(min(cl->k_cap, planes->k_cap, hulls->k_cap), cl->n_cap,
@@ -399,9 +398,9 @@ vm_status vm_planes_hulls(const vm_clusters* cl, const vm_ransac_params* params,
  * results; only the speed differs. */
 typedef struct {
     uint32_t hyp_chunk;      /* hypotheses per work item: a multiple of 64, 64..512; default 512 */
-    uint32_t small_max;      /* clusters of at most this many points are counted with the lanes over the
-                                hypotheses (one item per chunk), larger ones in 4096-point tiles; 0..256,
-                                default 0 (every cluster in tiles) */
+    uint32_t small_max;      /* clusters of at most this many points are one item for all their hypotheses,
+                                larger ones one per (4096-point tile, chunk); 0..256, default 0 (every
+                                cluster in tiles) */
     uint32_t groups_per_cu;  /* persistent workgroups per compute unit, 1..8; default 5 */
     uint32_t reserved;       /* must be 0 */
 } vm_fused_config;

@@ -345,9 +345,11 @@ hipError_t launch_clear_rays(const float* xyz, int64_t n, const Pose& pose, cons
 // ---- RANSAC and hulls (vm_ransac.hip, vm_hull.hip) --------------------------
 constexpr int kHullDirs = 8;   // support directions of the hull pre-filter
 
+constexpr uint32_t kPointTile = 4096;   // points per tile of the passes over a cluster's points
+
 struct WorkLayout {
     uint32_t k_cap;         // clusters the layout was made for
-    int32_t* counts;        // [k_cap * H]
+    int32_t* counts;        // [count rows * H]: a row per cluster, or (persistent pass) per point tile
     float4* hyp;            // [k_cap * H]
     uint32_t* tile_off;     // [k_cap + 1]
     uint32_t* tile_k;       // [n_cap / tile + k_cap + 1] cluster of each point tile
@@ -371,7 +373,8 @@ struct WorkLayout {
                             // hull tiles, chain-list length
     size_t bytes;
 };
-WorkLayout work_layout(void* base, uint32_t k_cap, uint32_t n_cap, uint32_t n_hyp);
+// count_rows: rows of counts (0: one per cluster)
+WorkLayout work_layout(void* base, uint32_t k_cap, uint32_t n_cap, uint32_t n_hyp, uint64_t count_rows = 0);
 uint64_t hull_tiles_bound(uint32_t k_cap, uint32_t n_cap);
 
 // d_cframe: optional per-cluster RNG frame word (merged cluster sets); when
@@ -385,11 +388,15 @@ vm_count_config count_config_get();
 void count_config_set(const vm_count_config& c);
 vm_status hulls(const vm_clusters& cl, const vm_planes& planes, const vm_hulls_out& out, const WorkLayout& w,
                 hipStream_t s);
-// the workgroup chain over listed clusters (count in small[7]) whose survivors
-// sit at gu/gv/gi[in_off[k] + s]; vertices to hull_tmp[in_off[k] + k + q]
-hipError_t launch_hull_chain_list(const uint32_t* small, const uint32_t* list, const uint32_t* in_off,
-                                  const uint32_t* in_idx, const uint32_t* surv_cnt, double* gu, double* gv, uint32_t* gi,
-                                  uint32_t* hull_cnt, uint32_t* hull_tmp, double* area_out, uint32_t grid, hipStream_t s);
+// steps of ransac_planes shared with the persistent form: every hypothesis'
+// plane and the cluster of each point tile (w.tile_off scanned; clusters of
+// more than wave_max points also get their counts cleared and their tiles
+// listed for the tiled counting), and (c) from the counts -- tile_rows: a row
+// per point tile instead of one per cluster
+hipError_t launch_hypotheses(const vm_clusters& cl, const vm_ransac_params& p, const WorkLayout& w, uint32_t kc,
+                             uint32_t wave_max, const uint32_t* d_cframe, hipStream_t s);
+vm_status select_and_list(const vm_clusters& cl, const vm_ransac_params& p, const vm_planes& out, const WorkLayout& w,
+                          uint32_t kc, bool tile_rows, hipStream_t s);
 
 // ---- RANSAC and polygons in one persistent launch (vm_fused.hip) ---------------
 bool fused_config_valid(const vm_fused_config& c);

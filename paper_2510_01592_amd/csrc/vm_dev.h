@@ -102,6 +102,175 @@ __device__ __forceinline__ bool inlier_test(const float4 pl, float x, float y, f
     return fabsf(fmaf(pl.z, z, fmaf(pl.y, y, fmaf(pl.x, x, pl.w)))) < eps;
 }
 
+// ---- inlier counting on the matrix cores ------------------------------------------
+// The test's distance is the chain fma(nz, z, fma(ny, y, fma(nx, x, d))).
+// v_mfma_f32_16x16x1 (four blocks, K = 1) adds one product to each of its
+// 1024 accumulators with a single rounding, so three of them from an
+// accumulator holding d give that chain bit for bit (on 2M random (point,
+// plane) pairs over magnitudes 1e-16..1e16, degenerate NaN planes and
+// subnormal values included, every result equalled the fmaf chain's).  The columns are a
+// wave's 64 planes (block b holds planes 16b .. 16b + 15), the rows 16 of its
+// 64 points, broadcast to all four blocks (cbsz 2, abid the group of 16): lane
+// l gets planes 16b + l % 16 against points 4 (l / 16) .. + 3.
+// Why: on this chip a VALU instruction with a scalar-register operand issues
+// at half rate (4.1 cycles per wave against 2.2-2.7), and a ballot form needs
+// two scalar instructions per 64 tests besides; here every operand is a
+// vector register, the three multiply-adds take 7.1 cycles per 64 tests and
+// counting two 2-cycle VALU instructions more.  A loop of these tests over
+// rows read from memory reaches 14.0 T tests/s with two plane groups per wave
+// and 13.2 T with one; the ballot form with the planes (or eps) in scalar
+// registers 8.6-9.1 T.
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+// |d| < eps as 1 or 0: (eps - |d|) * big in one fma, clamped to [0, 1], with
+// big = 2^(26 - e) for eps = m 2^e (0.5 <= m < 1).  eps * big is exact, the
+// fma's sign is exact, and the smallest positive eps - |d| is 2^(e - 25), so
+// a passing test gives at least 2 before the clamp; NaN clamps to 0.  For
+// eps below kMinFloatEps big would overflow: those calls compare instead.
+constexpr float kMinFloatEps = 0x1p-90f;
+
+struct EpsTest {
+    float eps, big, scaled;
+};
+
+inline __host__ __device__ EpsTest eps_test(float eps)
+{
+    EpsTest t;
+    t.eps = eps;
+    int e = 0;
+    if (eps >= kMinFloatEps) (void)frexpf(eps, &e);
+    t.big = ldexpf(1.0f, 26 - e);
+    t.scaled = eps * t.big;
+    return t;
+}
+
+__device__ __forceinline__ float vector_reg(float v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// G groups of 64 planes on one wave and their running counts (whole numbers
+// in fp32: a lane adds at most a tile's points).
+template <int G>
+struct PlaneGroups {
+    float nx[G], ny[G], nz[G];
+    f32x16 d[G];
+    float cnt[G][4];
+
+    // planes h0 .. h1 - 1 (at most 64 G of them) of the cluster's list; the
+    // rest are NaN and pass no test
+    __device__ __forceinline__ void load(const float4* __restrict__ hk, uint32_t h0, uint32_t h1, int lane)
+    {
+        const float qnan = __builtin_nanf("");
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const uint32_t h = h0 + (uint32_t)(g * kWave + lane);
+            const float4 p = h < h1 ? hk[h] : make_float4(qnan, qnan, qnan, qnan);
+            nx[g] = p.x;
+            ny[g] = p.y;
+            nz[g] = p.z;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const float w = __shfl(p.w, 16 * b + (lane & 15), kWave);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) d[g][4 * b + i] = w;
+                cnt[g][b] = 0.0f;
+            }
+        }
+    }
+
+    // points 16 A .. 16 A + 15 of the wave's row of 64
+    template <int A, bool kFloat>
+    __device__ __forceinline__ void step(float x, float y, float z, const EpsTest& t)
+    {
+        f32x16 r[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) r[g] = __builtin_amdgcn_mfma_f32_16x16x1f32(x, nx[g], d[g], 2, A, 0);
+#pragma unroll
+        for (int g = 0; g < G; ++g) r[g] = __builtin_amdgcn_mfma_f32_16x16x1f32(y, ny[g], r[g], 2, A, 0);
+#pragma unroll
+        for (int g = 0; g < G; ++g) r[g] = __builtin_amdgcn_mfma_f32_16x16x1f32(z, nz[g], r[g], 2, A, 0);
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float v = r[g][4 * b + i];
+                    if (kFloat) cnt[g][b] += fminf(fmaxf(fmaf(-fabsf(v), t.big, t.scaled), 0.0f), 1.0f);
+                    else cnt[g][b] += fabsf(v) < t.eps ? 1.0f : 0.0f;
+                }
+    }
+
+    template <bool kFloat>
+    __device__ __forceinline__ void row(float x, float y, float z, const EpsTest& t)
+    {
+        step<0, kFloat>(x, y, z, t);
+        step<1, kFloat>(x, y, z, t);
+        step<2, kFloat>(x, y, z, t);
+        step<3, kFloat>(x, y, z, t);
+    }
+
+    // n points (n > 0) at X/Y/Z, a row of 64 at a time with the next kAhead
+    // rows' loads in flight (a row's 8 G matrix steps take about a
+    // microsecond beside the other waves', a read from HBM two; the loads are
+    // unconditional, from the last point past the end: a branch around them
+    // would make the row before wait for them); points past the end are NaN
+    template <bool kFloat>
+    __device__ __forceinline__ void sweep(const float* __restrict__ X, const float* __restrict__ Y,
+                                          const float* __restrict__ Z, uint32_t n, EpsTest t, int lane)
+    {
+        constexpr uint32_t kAhead = 4;
+        t.eps = vector_reg(t.eps);
+        t.big = vector_reg(t.big);
+        t.scaled = vector_reg(t.scaled);
+        float x[kAhead], y[kAhead], z[kAhead];
+        auto fetch = [&](uint32_t j, uint32_t r) {
+            const uint32_t q = min(r + (uint32_t)lane, n - 1u);
+            x[j] = X[q];
+            y[j] = Y[q];
+            z[j] = Z[q];
+        };
+#pragma unroll
+        for (uint32_t j = 0; j < kAhead; ++j) fetch(j, j * kWave);
+        uint32_t r = 0;
+        for (; r + kAhead * kWave <= n; r += kAhead * kWave) {
+#pragma unroll
+            for (uint32_t j = 0; j < kAhead; ++j) {
+                row<kFloat>(x[j], y[j], z[j], t);
+                fetch(j, r + (j + kAhead) * kWave);
+            }
+        }
+        // the last rows: only the groups of 16 that hold points
+#pragma unroll
+        for (uint32_t j = 0; j < kAhead; ++j, r += kWave) {
+            if (r >= n) break;
+            const uint32_t m = n - r;
+            if ((uint32_t)lane >= m) x[j] = __builtin_nanf("");
+            step<0, kFloat>(x[j], y[j], z[j], t);
+            if (m > 16) step<1, kFloat>(x[j], y[j], z[j], t);
+            if (m > 32) step<2, kFloat>(x[j], y[j], z[j], t);
+            if (m > 48) step<3, kFloat>(x[j], y[j], z[j], t);
+        }
+    }
+
+    // lane l's count of plane 64 g + l: a plane's tests lie on the four lanes
+    // that share l % 16
+    __device__ __forceinline__ uint32_t count(int g, int lane) const
+    {
+        float v = 0.0f;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            float s = cnt[g][b];
+            s += __shfl_xor(s, 16, kWave);
+            s += __shfl_xor(s, 32, kWave);
+            v = (lane >> 4) == b ? s : v;
+        }
+        return (uint32_t)v;
+    }
+};
+
 __device__ __forceinline__ bool p2_less(double au, double av, uint32_t ai, double bu, double bv, uint32_t bi)
 {
     if (au != bu) return au < bu;

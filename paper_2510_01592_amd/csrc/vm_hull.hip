@@ -597,8 +597,7 @@ __global__ void __launch_bounds__(kChainBlock) k_hull_chain(
 {
     __shared__ ChainLds<kLdsCap> L;
     __shared__ RefineLds R;
-    // the listed clusters: more than kMidMax survivors (k_hull_list), or the
-    // persistent pass's clusters with more than one wave of survivors
+    // the listed clusters: more than kMidMax survivors (k_hull_list)
     const uint32_t nc = small[7];
     for (uint32_t c = blockIdx.x; c < nc; c += gridDim.x) {
         const uint32_t k = chain_list[c];
@@ -723,15 +722,6 @@ __global__ void __launch_bounds__(kBlock) k_hull_pack(const uint32_t* __restrict
 }
 
 }  // namespace
-
-hipError_t launch_hull_chain_list(const uint32_t* small, const uint32_t* list, const uint32_t* in_off,
-                                  const uint32_t* in_idx, const uint32_t* surv_cnt, double* gu, double* gv, uint32_t* gi,
-                                  uint32_t* hull_cnt, uint32_t* hull_tmp, double* area_out, uint32_t grid, hipStream_t s)
-{
-    k_hull_chain<<<grid ? grid : 1, kChainBlock, 0, s>>>(small, list, in_off, in_idx, surv_cnt, gu, gv, gi, hull_cnt,
-                                                         hull_tmp, area_out);
-    return hipGetLastError();
-}
 
 uint64_t hull_tiles_bound(uint32_t k_cap, uint32_t n_cap)
 {

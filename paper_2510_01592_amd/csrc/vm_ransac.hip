@@ -8,11 +8,13 @@
 // load-balance across the 256 CUs without the host knowing any size.
 //
 // Inlier counting is the arithmetic hot spot (sum over clusters of n_k x H
-// point-plane tests).  Each lane keeps P points of its tile in registers; the
-// plane of the current hypothesis is wave-uniform (scalar loads), so one test
-// is three v_fma_f32 and one v_cmp with the |.| modifier, and the count of a
-// whole wave is a ballot and one scalar popcount.  Counts are integers added
-// with atomics, hence independent of the order of tiles.
+// point-plane tests).  It runs on the matrix cores: a wave keeps 64 or 128
+// planes in registers and sweeps points (PlaneGroups in vm_dev.h); three K = 1
+// fp32 matrix steps give the specified fma chain bit for bit.  Counts are
+// integers added with atomics, hence independent of the order of tiles.
+// (6.7M clustered points x 1024 hypotheses: 0.65 ms, 10.6 T tests/s, from 0.95
+// ms with ballots over points in registers and planes in scalar registers;
+// clusters of at most 256 points, 11k of them x 512: 14 us, from 24.)
 #include "vm_common.h"
 #include "vm_dev.h"
 
@@ -27,9 +29,7 @@ using namespace dev;
 
 constexpr int kCountBlock = 256;
 constexpr int kPtsPerLane = 16;
-constexpr int kTile = kCountBlock * kPtsPerLane;   // points per tile (4096)
-constexpr int kMaxHypChunk = 4096;                 // hypotheses per work item (LDS counters)
-constexpr int kHypBatch = 4;                       // planes loaded together
+constexpr int kTile = (int)kPointTile;             // points per tile
 constexpr uint32_t kXcds = 8;                      // accelerator complex dies (separate L2s)
 
 // (a) hypothesis (k, h): three distinct points -> unit normal (+z first) and
@@ -140,13 +140,9 @@ __global__ void __launch_bounds__(kBlock) k_tiles(const uint32_t* __restrict__ s
     }
 }
 
-// (b) inlier counting over (tile, hypothesis-chunk) items.  The number of
-// hypothesis chunks is chosen on the device from the tile count so that small
-// frames still cover every CU; each item keeps its points in registers and
-// sweeps its chunk of planes, kHypBatch planes per scalar-load batch.  A wave
-// evaluates only the rows of 64 points that hold points of the tile's
-// cluster: the last tile of a cluster is usually short, and most clusters
-// are smaller than one tile.
+// (b) inlier counting.  The rows form, for clusters that vm_count_config gives
+// to one wave with its lanes over points: a wave evaluates only the rows of 64
+// points that hold points of its cluster.
 template <int R>
 __device__ __forceinline__ uint32_t count_rows(const float4 pl, const float* px, const float* py, const float* pz,
                                                float eps)
@@ -158,49 +154,6 @@ __device__ __forceinline__ uint32_t count_rows(const float4 pl, const float* px,
         acc += (uint32_t)__popcll(__ballot(fabsf(dd) < eps));
     }
     return acc;
-}
-
-// Planes hb..he (at most 64) against the wave's points.  A wave's count for
-// a plane is uniform; the counts are gathered in one register, lane q
-// keeping plane hb + q.
-template <int R>
-__device__ __forceinline__ int count_batch(const float4* __restrict__ hk, uint32_t hb, uint32_t he, const float* px,
-                                           const float* py, const float* pz, float eps, int lane)
-{
-    int cv = 0;
-    uint32_t h = hb;
-    for (; h + kHypBatch <= he; h += kHypBatch) {
-        float4 pl[kHypBatch];
-#pragma unroll
-        for (int b = 0; b < kHypBatch; ++b) pl[b] = hk[h + b];
-#pragma unroll
-        for (int b = 0; b < kHypBatch; ++b) {
-            if (pl[b].x != pl[b].x) continue;   // degenerate hypothesis
-            const uint32_t acc = count_rows<R>(pl[b], px, py, pz, eps);
-            cv = (lane == (int)(h + b - hb)) ? (int)acc : cv;
-        }
-    }
-    for (; h < he; ++h) {
-        const float4 pl = hk[h];
-        if (pl.x != pl.x) continue;
-        const uint32_t acc = count_rows<R>(pl, px, py, pz, eps);
-        cv = (lane == (int)(h - hb)) ? (int)acc : cv;
-    }
-    return cv;
-}
-
-// Planes h0..h1 of a tile: one vector LDS add per 64 planes into the block's
-// counters.
-template <int R>
-__device__ __forceinline__ void count_planes(const float4* __restrict__ hk, uint32_t h0, uint32_t h1,
-                                             const float* px, const float* py, const float* pz, float eps,
-                                             uint32_t* lcnt, int lane)
-{
-    for (uint32_t hb = h0; hb < h1; hb += kWave) {
-        const uint32_t he = min(h1, hb + (uint32_t)kWave);
-        const int cv = count_batch<R>(hk, hb, he, px, py, pz, eps, lane);
-        if ((uint32_t)lane < he - hb && cv) atomicAdd(&lcnt[hb - h0 + (uint32_t)lane], (uint32_t)cv);
-    }
 }
 
 // All planes of a cluster that one wave holds: the counts are final, stored.
@@ -231,59 +184,24 @@ __device__ __forceinline__ void count_all(const float4* __restrict__ hk, uint32_
     }
 }
 
-// Clusters of at most a few rows of points: the lanes take the planes
-// instead (lane q counts plane hb + q) and loop over the points, whose
-// coordinates are wave-uniform loads (scalar loads, 16 points per step),
-// so no lane idles and no per-plane reduction is needed.  The count is the
-// same sum of the same tests.
+// Clusters of at most a few rows of points: the wave's lanes hold 64 G planes
+// at a time against all the points (PlaneGroups).
+template <int G, bool kFloat>
 __device__ __forceinline__ void count_by_planes(const float4* __restrict__ hk, uint32_t h0, uint32_t h1, uint32_t n,
                                                 const float* __restrict__ X, const float* __restrict__ Y,
-                                                const float* __restrict__ Z, float eps, int32_t* __restrict__ ck,
-                                                int lane)
+                                                const float* __restrict__ Z, const EpsTest& eps,
+                                                int32_t* __restrict__ ck, int lane)
 {
-    // four 64-plane batches at a time: their plane loads are issued
-    // together and each point is loaded once for all four
-    constexpr int kB = 4;
-    for (uint32_t hb = h0; hb < h1; hb += kB * kWave) {
-        float4 pl[kB];
-        bool has[kB];
-        uint32_t c[kB];
+    for (uint32_t hb = h0; hb < h1; hb += G * kWave) {
+        PlaneGroups<G> pg;
+        pg.load(hk, hb, h1, lane);
+        pg.template sweep<kFloat>(X, Y, Z, n, eps, lane);
 #pragma unroll
-        for (int b = 0; b < kB; ++b) {
-            const uint32_t h = hb + (uint32_t)(b * kWave + lane);
-            has[b] = h < h1;
-            pl[b] = has[b] ? hk[h] : make_float4(0.f, 0.f, 0.f, 0.f);
-            c[b] = 0;
+        for (int g = 0; g < G; ++g) {
+            const uint32_t h = hb + (uint32_t)(g * kWave + lane);
+            const uint32_t c = pg.count(g, lane);
+            if (h < h1) ck[h] = (int32_t)c;
         }
-        uint32_t j = 0;
-        for (; j + 16 <= n; j += 16) {
-            float x[16], y[16], z[16];
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                x[q] = X[j + q];
-                y[q] = Y[j + q];
-                z[q] = Z[j + q];
-            }
-#pragma unroll
-            for (int b = 0; b < kB; ++b) {
-#pragma unroll
-                for (int q = 0; q < 16; ++q) {
-                    const float dd = fmaf(pl[b].z, z[q], fmaf(pl[b].y, y[q], fmaf(pl[b].x, x[q], pl[b].w)));
-                    c[b] += fabsf(dd) < eps ? 1u : 0u;   // a degenerate (NaN) plane never passes
-                }
-            }
-        }
-        for (; j < n; ++j) {
-            const float x = X[j], y = Y[j], z = Z[j];
-#pragma unroll
-            for (int b = 0; b < kB; ++b) {
-                const float dd = fmaf(pl[b].z, z, fmaf(pl[b].y, y, fmaf(pl[b].x, x, pl[b].w)));
-                c[b] += fabsf(dd) < eps ? 1u : 0u;
-            }
-        }
-#pragma unroll
-        for (int b = 0; b < kB; ++b)
-            if (has[b]) ck[hb + (uint32_t)(b * kWave + lane)] = (int32_t)c[b];
     }
 }
 
@@ -297,10 +215,11 @@ __device__ __forceinline__ void count_by_planes(const float4* __restrict__ hk, u
 constexpr uint32_t kWaveMaxPts = kWave * kPtsPerLane;   // 1024
 constexpr uint32_t kPlaneMaxPts = 4 * kWave;            // 256
 
-__global__ void __launch_bounds__(kCountBlock) k_count_small(const uint32_t* __restrict__ small,
+template <bool kFloat>
+__global__ void __launch_bounds__(kCountBlock, 4) k_count_small(const uint32_t* __restrict__ small,
                                                              const uint32_t* __restrict__ off,
                                                              const float* __restrict__ X, const float* __restrict__ Y,
-                                                             const float* __restrict__ Z, uint32_t H, float eps,
+                                                             const float* __restrict__ Z, uint32_t H, EpsTest eps,
                                                              const float4* __restrict__ hyp,
                                                              int32_t* __restrict__ counts, uint32_t wave_max,
                                                              uint32_t plane_max, uint32_t chunk_mult)
@@ -325,6 +244,12 @@ __global__ void __launch_bounds__(kCountBlock) k_count_small(const uint32_t* __r
         const uint32_t h0 = hc * cb * kWave, h1 = min(H, h0 + cb * kWave);
         const uint32_t base = off[k], n = off[k + 1] - base;
         if (n < 3 || n > wave_max) continue;   // fewer than 3: no planes; more: the tiled kernel
+        const float4* hk = hyp + (size_t)k * H;
+        int32_t* ck = counts + (size_t)k * H;
+        if (n <= plane_max) {
+            count_by_planes<2, kFloat>(hk, h0, h1, n, X + base, Y + base, Z + base, eps, ck, lane);
+            continue;
+        }
         const int rows = (int)((n + kWave - 1) / kWave);
         float px[kPtsPerLane], py[kPtsPerLane], pz[kPtsPerLane];
 #pragma unroll
@@ -335,77 +260,65 @@ __global__ void __launch_bounds__(kCountBlock) k_count_small(const uint32_t* __r
             py[j] = v ? Y[base + i] : qnan;
             pz[j] = v ? Z[base + i] : qnan;
         }
-        const float4* hk = hyp + (size_t)k * H;
-        int32_t* ck = counts + (size_t)k * H;
-        if (n <= plane_max) count_by_planes(hk, h0, h1, n, X + base, Y + base, Z + base, eps, ck, lane);
-        else if (rows > 8) count_all<16>(hk, h0, h1, px, py, pz, eps, ck, lane);
-        else if (rows > 4) count_all<8>(hk, h0, h1, px, py, pz, eps, ck, lane);
-        else if (rows > 2) count_all<4>(hk, h0, h1, px, py, pz, eps, ck, lane);
-        else if (rows > 1) count_all<2>(hk, h0, h1, px, py, pz, eps, ck, lane);
-        else count_all<1>(hk, h0, h1, px, py, pz, eps, ck, lane);
+        if (rows > 8) count_all<16>(hk, h0, h1, px, py, pz, eps.eps, ck, lane);
+        else if (rows > 4) count_all<8>(hk, h0, h1, px, py, pz, eps.eps, ck, lane);
+        else if (rows > 2) count_all<4>(hk, h0, h1, px, py, pz, eps.eps, ck, lane);
+        else if (rows > 1) count_all<2>(hk, h0, h1, px, py, pz, eps.eps, ck, lane);
+        else count_all<1>(hk, h0, h1, px, py, pz, eps.eps, ck, lane);
     }
 }
 
-__global__ void __launch_bounds__(kCountBlock) k_count(const uint32_t* __restrict__ small,
+// Larger clusters: an item is a slice of a 4096-point tile against a chunk of
+// hypotheses, 64 G per wave, so each wave holds its planes in registers and
+// sweeps the slice's points (PlaneGroups).  A tile is cut into slices (down to
+// 256 points) until there are about chunk_mult items per resident workgroup:
+// the frame's few hundred tiles alone would leave most of the chip idle.
+constexpr uint32_t kMaxSlices = 16;          // slices of a tile (256 points each)
+constexpr uint32_t kCountResident = 1280;    // workgroups of this kernel on the chip at once
+
+// (the bound of four workgroups per compute unit also keeps the matrix results
+// out of the accumulation registers, each of which would cost a move to read)
+template <int G, bool kFloat>
+__global__ void __launch_bounds__(kCountBlock, 4) k_count(const uint32_t* __restrict__ small,
                                                        const uint32_t* __restrict__ tile_off, const uint32_t* __restrict__ tile_k,
                                                        const uint32_t* __restrict__ off, const float* __restrict__ X,
                                                        const float* __restrict__ Y, const float* __restrict__ Z,
-                                                       uint32_t H, float eps, const float4* __restrict__ hyp,
+                                                       uint32_t H, EpsTest eps, const float4* __restrict__ hyp,
                                                        int32_t* __restrict__ counts, uint32_t chunk_mult)
 {
-    __shared__ uint32_t lcnt[kMaxHypChunk];
     const uint32_t T = small[3];   // tiles of the clusters beyond one wave
     if (T == 0) return;
-    // chunks per tile: enough items for two per block of the grid, chunks of
-    // at least 32 hypotheses, at most kMaxHypChunk
-    uint32_t HC = (chunk_mult * gridDim.x + T - 1) / T;
-    const uint32_t hc_max = (H + 31) / 32;
-    if (HC > hc_max) HC = hc_max;
-    if (HC < (H + kMaxHypChunk - 1) / kMaxHypChunk) HC = (H + kMaxHypChunk - 1) / kMaxHypChunk;
-    if (HC < 1) HC = 1;
-    const uint32_t chunk = (H + HC - 1) / HC;
+    constexpr uint32_t kChunk = (uint32_t)(G * kCountBlock);
+    const uint32_t HC = (H + kChunk - 1) / kChunk;
+    uint32_t S = 1;
+    while (S < kMaxSlices && (uint64_t)T * HC * S < (uint64_t)chunk_mult * kCountResident) S <<= 1;
+    const uint32_t slice = kTile / S;
     // Workgroups are dispatched round-robin over the XCDs, each with its own
-    // L2: tile t is handled on XCD t mod kXcds only, so the hypothesis chunks
-    // of a tile (run at about the same time) fetch its points from memory once.
+    // L2: tile t is handled on XCD t mod kXcds only, so the items of a tile
+    // (run at about the same time) fetch its points from memory once.
     const uint32_t xcd = blockIdx.x % kXcds, sub = blockIdx.x / kXcds, nsub = gridDim.x / kXcds;
     const uint32_t tiles_x = T > xcd ? (T - xcd + kXcds - 1) / kXcds : 0u;
-    const uint64_t items = (uint64_t)tiles_x * HC;
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const uint64_t items = (uint64_t)tiles_x * HC * S;
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     for (uint64_t item = sub; item < items; item += nsub) {
-        const uint32_t t = (uint32_t)(item / HC) * kXcds + xcd, hc = (uint32_t)(item % HC);
+        const uint32_t t = (uint32_t)(item / (HC * S)) * kXcds + xcd, q = (uint32_t)(item % (HC * S));
+        const uint32_t hc = q / S, sl = q % S;
         const uint32_t k = tile_k[t];
-        const uint32_t p0 = off[k] + (t - tile_off[k]) * kTile;
+        const uint32_t p0 = off[k] + (t - tile_off[k]) * kTile + sl * slice;
         const uint32_t pend = off[k + 1];
-        const uint32_t h0 = hc * chunk, h1 = min(H, h0 + chunk);
-        const uint32_t wbase = p0 + (uint32_t)(wave * kWave * kPtsPerLane);
-        const int rows = pend > wbase ? (int)min((uint32_t)kPtsPerLane, (pend - wbase + kWave - 1) / kWave) : 0;
-        float px[kPtsPerLane], py[kPtsPerLane], pz[kPtsPerLane];
-        const float qnan = __builtin_nanf("");
-#pragma unroll
-        for (int j = 0; j < kPtsPerLane; ++j) {
-            const uint32_t i = wbase + (uint32_t)(j * kWave + lane);
-            const bool v = i < pend;
-            px[j] = v ? X[i] : qnan;   // NaN never passes |d| < eps
-            py[j] = v ? Y[i] : qnan;
-            pz[j] = v ? Z[i] : qnan;
-        }
-        for (uint32_t h = h0 + threadIdx.x; h < h1; h += kCountBlock) lcnt[h - h0] = 0;
-        __syncthreads();
-        const float4* hk = hyp + (size_t)k * H;
-        // rows is wave-uniform; rows past the cluster's end hold NaN points
-        static_assert(kPtsPerLane == 16, "the row dispatch below assumes 16 rows per lane");
-        if (rows > 8) count_planes<16>(hk, h0, h1, px, py, pz, eps, lcnt, lane);
-        else if (rows > 4) count_planes<8>(hk, h0, h1, px, py, pz, eps, lcnt, lane);
-        else if (rows > 2) count_planes<4>(hk, h0, h1, px, py, pz, eps, lcnt, lane);
-        else if (rows > 1) count_planes<2>(hk, h0, h1, px, py, pz, eps, lcnt, lane);
-        else if (rows == 1) count_planes<1>(hk, h0, h1, px, py, pz, eps, lcnt, lane);
-        __syncthreads();
+        const uint32_t h0 = hc * kChunk + wave * (uint32_t)(G * kWave);
+        if (p0 >= pend || h0 >= H) continue;   // wave-uniform; no barriers below
+        PlaneGroups<G> pg;
+        pg.load(hyp + (size_t)k * H, h0, H, lane);
+        pg.template sweep<kFloat>(X + p0, Y + p0, Z + p0, min(slice, pend - p0), eps, lane);
         int32_t* ck = counts + (size_t)k * H;
-        for (uint32_t hh = h0 + threadIdx.x; hh < h1; hh += kCountBlock) {
-            const uint32_t c = lcnt[hh - h0];
-            if (c) atomicAdd(&ck[hh], (int32_t)c);
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const uint32_t h = h0 + (uint32_t)(g * kWave + lane);
+            const uint32_t c = pg.count(g, lane);
+            if (h < H && c) atomicAdd(&ck[h], (int32_t)c);
         }
-        __syncthreads();
     }
 }
 
@@ -447,6 +360,58 @@ __global__ void __launch_bounds__(kBlock) k_select(const uint32_t* __restrict__ 
                 plane_out[k] = hyp[(size_t)k * H + bh];
             }
         }
+    }
+}
+
+// the same from a row of counts per point tile, a workgroup per cluster: a
+// cluster's count is the sum of its tiles' rows
+__global__ void __launch_bounds__(kBlock) k_select_rows(const uint32_t* __restrict__ small,
+                                                        const uint32_t* __restrict__ off,
+                                                        const uint32_t* __restrict__ tile_off, uint32_t H,
+                                                        const int32_t* __restrict__ rows, const float4* __restrict__ hyp,
+                                                        float4* __restrict__ plane_out, int32_t* __restrict__ best_out,
+                                                        int32_t* __restrict__ nin_out, int32_t* __restrict__ counts_out,
+                                                        float4* __restrict__ hyp_out)
+{
+    __shared__ int32_t sc[kBlock / kWave];
+    __shared__ uint32_t sh[kBlock / kWave];
+    const uint32_t K = small[0];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    for (uint32_t k = blockIdx.x; k < K; k += gridDim.x) {
+        const uint32_t nt = (off[k + 1] - off[k] + kTile - 1) / kTile;
+        const int32_t* row = rows + (size_t)tile_off[k] * H;
+        int32_t bc = -1;
+        uint32_t bh = 0xFFFFFFFFu;
+        for (uint32_t h = threadIdx.x; h < H; h += kBlock) {
+            const float4 pl = hyp[(size_t)k * H + h];
+            const bool degen = pl.x != pl.x;
+            int32_t c = 0;
+#pragma unroll 8
+            for (uint32_t t = 0; t < nt; ++t) c += row[(size_t)t * H + h];
+            if (degen) c = -1;
+            if (c > bc) { bc = c; bh = h; }
+            if (counts_out) counts_out[(size_t)k * H + h] = c;
+            if (hyp_out) hyp_out[(size_t)k * H + h] = degen ? make_float4(0.f, 0.f, 0.f, 0.f) : pl;
+        }
+#pragma unroll
+        for (int d = kWave / 2; d >= 1; d >>= 1) {
+            const int32_t oc = __shfl_xor(bc, d, kWave);
+            const uint32_t oh = __shfl_xor(bh, d, kWave);
+            if (oc > bc || (oc == bc && oh < bh)) { bc = oc; bh = oh; }
+        }
+        if (lane == 0) {
+            sc[wave] = bc;
+            sh[wave] = bh;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int w = 1; w < kBlock / kWave; ++w)
+                if (sc[w] > bc || (sc[w] == bc && sh[w] < bh)) { bc = sc[w]; bh = sh[w]; }
+            best_out[k] = bc < 0 ? -1 : (int32_t)bh;
+            nin_out[k] = bc < 0 ? 0 : bc;
+            plane_out[k] = bc < 0 ? make_float4(0.f, 0.f, 0.f, 0.f) : hyp[(size_t)k * H + bh];
+        }
+        __syncthreads();   // sc and sh are reused by the next cluster
     }
 }
 
@@ -576,7 +541,7 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 }  // namespace
 
-WorkLayout work_layout(void* base, uint32_t k_cap, uint32_t n_cap, uint32_t n_hyp)
+WorkLayout work_layout(void* base, uint32_t k_cap, uint32_t n_cap, uint32_t n_hyp, uint64_t count_rows)
 {
     WorkLayout w{};
     w.k_cap = k_cap;
@@ -588,7 +553,7 @@ WorkLayout work_layout(void* base, uint32_t k_cap, uint32_t n_cap, uint32_t n_hy
         return r;
     };
     const size_t kh = (size_t)k_cap * (size_t)n_hyp;
-    w.counts = (int32_t*)take(kh * sizeof(int32_t));
+    w.counts = (int32_t*)take((count_rows ? (size_t)count_rows * n_hyp : kh) * sizeof(int32_t));
     w.hyp = (float4*)take(kh * sizeof(float4));
     w.tile_off = (uint32_t*)take(((size_t)k_cap + 2) * sizeof(uint32_t));
     w.tile_k = (uint32_t*)take(((size_t)n_cap / kTile + k_cap + 2) * sizeof(uint32_t));
@@ -650,6 +615,42 @@ void count_config_set(const vm_count_config& c)
     g_count_cfg = c;
 }
 
+hipError_t launch_hypotheses(const vm_clusters& cl, const vm_ransac_params& p, const WorkLayout& w, uint32_t kc,
+                             uint32_t wave_max, const uint32_t* d_cframe, hipStream_t s)
+{
+    const uint64_t kh = (uint64_t)kc * p.n_hyp;
+    k_hypotheses<<<grid_for(kh, kBlock, 16384), kBlock, 0, s>>>(w.small, cl.d_off, cl.d_tag, cl.d_x, cl.d_y, cl.d_z,
+                                                                p.n_hyp, p.seed, p.frame, p.d_frame, d_cframe,
+                                                                w.tile_off, w.tile_k, w.tile_off_big, w.tile_k_big,
+                                                                wave_max, w.counts, w.hyp);
+    return hipGetLastError();
+}
+
+vm_status select_and_list(const vm_clusters& cl, const vm_ransac_params& p, const vm_planes& out, const WorkLayout& w,
+                          uint32_t kc, bool tile_rows, hipStream_t s)
+{
+    const uint32_t H = p.n_hyp;
+    StageScope t(VM_STAGE_SELECT, s);
+    if (tile_rows)
+        k_select_rows<<<grid_for(kc, 1, 8192), kBlock, 0, s>>>(w.small, cl.d_off, w.tile_off, H, w.counts, w.hyp,
+                                                               (float4*)out.d_plane, out.d_best_h, out.d_n_inliers,
+                                                               out.d_counts, (float4*)out.d_hyp);
+    else
+        k_select<<<grid_for((uint64_t)kc * kWave), kBlock, 0, s>>>(w.small, H, w.counts, w.hyp, (float4*)out.d_plane,
+                                                                   out.d_best_h, out.d_n_inliers, out.d_counts,
+                                                                   (float4*)out.d_hyp);
+    const int tgrid = grid_for((uint64_t)cl.n_cap / kTile + kc + 1, 1, 8192);   // most tiles are small: many workgroups
+    // w.flags holds the per-tile counts, then their prefixes (tiles <= points)
+    k_inlier_count<<<tgrid, kCountBlock, 0, s>>>(w.small, w.tile_off, w.tile_k, cl.d_off, cl.d_x, cl.d_y, cl.d_z,
+                                                 p.eps, out.d_best_h, (const float4*)out.d_plane, w.flags);
+    k_inlier_scan<<<1, kOneBlockThreads, 0, s>>>(w.small, w.tile_off, w.flags, out.d_in_off);
+    k_inlier_write<<<tgrid, kCountBlock, 0, s>>>(w.small, w.tile_off, w.tile_k, cl.d_off, cl.d_x, cl.d_y, cl.d_z, p.eps,
+                                                 out.d_best_h, (const float4*)out.d_plane, w.flags, out.in_cap,
+                                                 out.d_in_idx, out.d_status);
+    VM_HIP(hipGetLastError());
+    return VM_OK;
+}
+
 vm_status ransac_planes(const vm_clusters& cl, const vm_ransac_params& p, const vm_planes& out,
                         const WorkLayout& w, hipStream_t s, const uint32_t* d_cframe)
 {
@@ -671,40 +672,33 @@ vm_status ransac_planes(const vm_clusters& cl, const vm_ransac_params& p, const 
             VM_HIP(scan_exclusive_dev(w.tile_off, w.tile_off, w.small, kc, w.small + 1, w.blk, s));
             VM_HIP(scan_exclusive_dev(w.tile_off_big, w.tile_off_big, w.small, kc, w.small + 3, w.blk, s));
         }
-        const uint64_t kh = (uint64_t)kc * H;
-        k_hypotheses<<<grid_for(kh, kBlock, 16384), kBlock, 0, s>>>(w.small, cl.d_off, cl.d_tag, cl.d_x, cl.d_y,
-                                                                    cl.d_z, H, p.seed, p.frame, p.d_frame, d_cframe,
-                                                                    w.tile_off, w.tile_k, w.tile_off_big, w.tile_k_big,
-                                                                    cc.wave_max_points, w.counts, w.hyp);
-        VM_HIP(hipGetLastError());
+        VM_HIP(launch_hypotheses(cl, p, w, kc, cc.wave_max_points, d_cframe, s));
     }
     {
         StageScope t(VM_STAGE_COUNT, s);
-        if (cc.wave_max_points >= 3)
-            k_count_small<<<grid_for((uint64_t)kc * ((H + kWave - 1) / kWave) * kWave, kCountBlock, 1024), kCountBlock,
-                            0, s>>>(
-                w.small, cl.d_off, cl.d_x, cl.d_y, cl.d_z, H, p.eps, w.hyp, w.counts, cc.wave_max_points,
-                cc.plane_max_points, cc.chunk_mult);
-        k_count<<<cc.count_grid, kCountBlock, 0, s>>>(w.small, w.tile_off_big, w.tile_k_big, cl.d_off, cl.d_x, cl.d_y,
-                                                      cl.d_z, H, p.eps, w.hyp, w.counts, cc.chunk_mult);
+        const EpsTest et = eps_test(p.eps);
+        const bool flt = p.eps >= kMinFloatEps;
+        if (cc.wave_max_points >= 3) {
+            const int grid = grid_for((uint64_t)kc * ((H + kWave - 1) / kWave) * kWave, kCountBlock, 1024);
+            auto count_small = [&](auto kernel) {
+                kernel<<<grid, kCountBlock, 0, s>>>(w.small, cl.d_off, cl.d_x, cl.d_y, cl.d_z, H, et, w.hyp, w.counts,
+                                                    cc.wave_max_points, cc.plane_max_points, cc.chunk_mult);
+            };
+            if (flt) count_small(k_count_small<true>);
+            else count_small(k_count_small<false>);
+        }
+        auto count = [&](auto kernel) {
+            kernel<<<cc.count_grid, kCountBlock, 0, s>>>(w.small, w.tile_off_big, w.tile_k_big, cl.d_off, cl.d_x,
+                                                         cl.d_y, cl.d_z, H, et, w.hyp, w.counts, cc.chunk_mult);
+        };
+        // two plane groups per wave need fewer point reads per test, one
+        // fills four waves with up to 256 hypotheses
+        if (!flt) count(k_count<1, false>);
+        else if (H > (uint32_t)kCountBlock) count(k_count<2, true>);
+        else count(k_count<1, true>);
         VM_HIP(hipGetLastError());
     }
-    {
-        StageScope t(VM_STAGE_SELECT, s);
-        k_select<<<grid_for((uint64_t)kc * kWave), kBlock, 0, s>>>(w.small, H, w.counts, w.hyp, (float4*)out.d_plane,
-                                                                   out.d_best_h, out.d_n_inliers, out.d_counts,
-                                                                   (float4*)out.d_hyp);
-        const int tgrid = grid_for((uint64_t)cl.n_cap / kTile + kc + 1, 1, 8192);   // most tiles are small: many workgroups
-        // w.flags holds the per-tile counts, then their prefixes (tiles <= points)
-        k_inlier_count<<<tgrid, kCountBlock, 0, s>>>(w.small, w.tile_off, w.tile_k, cl.d_off, cl.d_x, cl.d_y, cl.d_z,
-                                                     p.eps, out.d_best_h, (const float4*)out.d_plane, w.flags);
-        k_inlier_scan<<<1, kOneBlockThreads, 0, s>>>(w.small, w.tile_off, w.flags, out.d_in_off);
-        k_inlier_write<<<tgrid, kCountBlock, 0, s>>>(w.small, w.tile_off, w.tile_k, cl.d_off, cl.d_x, cl.d_y, cl.d_z, p.eps,
-                                                     out.d_best_h, (const float4*)out.d_plane, w.flags, out.in_cap,
-                                                     out.d_in_idx, out.d_status);
-        VM_HIP(hipGetLastError());
-    }
-    return VM_OK;
+    return select_and_list(cl, p, out, w, kc, false, s);
 }
 
 }  // namespace vm
