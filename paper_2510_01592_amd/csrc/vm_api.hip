@@ -34,7 +34,7 @@ struct vm_map_s {
     // classification buffers (allocated on the first steppable call)
     StepBuffers sb{};
     void* step_mem = nullptr;
-    // ray and keep bitmaps of the clearing pass (allocated on the first call)
+    // the clearing pass's copy of the occupancy with the marks of rays, then its bitmap of end cells (first call)
     uint32_t* clr_mem = nullptr;
     // per-sweep change flags of label propagation (device) and their host copy
     uint32_t* lp_flags = nullptr;
@@ -435,7 +435,7 @@ vm_status vm_clear_rays(vm_map m, const float* d_xyz, int64_t n, const vm_pose* 
     hipStream_t s = (hipStream_t)stream;
     if (!m->clr_mem) {
         if (capturing(s)) return VM_E_STATE;   // no allocation inside a capture
-        const size_t bytes = (size_t)m->g.nwords * 4 * 2;
+        const size_t bytes = (size_t)clear_words(m->g) * 4 * 3;
         if (hipMalloc((void**)&m->clr_mem, bytes) != hipSuccess) {
             (void)hipGetLastError();
             m->clr_mem = nullptr;
@@ -448,7 +448,8 @@ vm_status vm_clear_rays(vm_map m, const float* d_xyz, int64_t n, const vm_pose* 
         }
     }
     StageScope t(VM_STAGE_CLEAR, s);
-    VM_HIP(launch_clear_rays(d_xyz, n, q, m->g, sv, m->h, m->bits, m->clr_mem, m->clr_mem + m->g.nwords, m->ctr, s));
+    VM_HIP(launch_clear_rays(d_xyz, n, q, m->g, sv, m->h, m->bits, m->clr_mem + 2 * clear_words(m->g), m->clr_mem,
+                             m->ins.key, m->ins.cap, m->ctr, s));
     return VM_OK;
 }
 

@@ -33,7 +33,8 @@ struct DevCounters {
     uint32_t group_sel;               // buffer (0/1) holding the voxels sorted by cluster
     unsigned long long cleared;       // voxels cleared by ray casting since create/clear
     unsigned long long shifted_out;   // voxels dropped by grid shifts since create/clear
-    uint32_t pad[5];
+    uint32_t rays[2];                 // lines listed by the clearing pass (batches in turn)
+    uint32_t pad[3];
 };
 
 struct Geom {
@@ -337,10 +338,12 @@ hipError_t launch_lp_finish(const uint32_t* bits, SegBuffers& b, uint32_t cap, c
 // ---- ray casting and clearing (vm_clear.hip) ---------------------------------
 // Eq. (2) for one frame: cast every point's ray from the sensor's voxel,
 // then free the occupied cells on a ray that hold none of the frame's points.
-// ray and keep are zero on entry (nwords words each) and zero again on exit.
+// ends (clear_words words) is zero on entry and zero again on exit; work: two
+// times as many words of scratch, 8-byte aligned; list: list_cap words.
+uint64_t clear_words(const Geom& g);
 hipError_t launch_clear_rays(const float* xyz, int64_t n, const Pose& pose, const Geom& g, const int32_t sensor[3],
-                             const Hash& h, uint32_t* bits, uint32_t* ray, uint32_t* keep, DevCounters* ctr,
-                             hipStream_t s);
+                             const Hash& h, uint32_t* bits, uint32_t* ends, uint32_t* work, uint32_t* list,
+                             uint32_t list_cap, DevCounters* ctr, hipStream_t s);
 
 // ---- RANSAC and hulls (vm_ransac.hip, vm_hull.hip) --------------------------
 constexpr int kHullDirs = 8;   // support directions of the hull pre-filter
