@@ -346,8 +346,6 @@ hipError_t launch_clear_rays(const float* xyz, int64_t n, const Pose& pose, cons
                              uint32_t list_cap, DevCounters* ctr, hipStream_t s);
 
 // ---- RANSAC and hulls (vm_ransac.hip, vm_hull.hip) --------------------------
-constexpr int kHullDirs = 8;   // support directions of the hull pre-filter
-
 constexpr uint32_t kPointTile = 4096;   // points per tile of the passes over a cluster's points
 
 struct WorkLayout {
@@ -367,13 +365,10 @@ struct WorkLayout {
     double* hull_v;         // [n_cap]
     uint32_t* hull_i;       // [n_cap]
     uint32_t* hull_tile_off;  // [k_cap + 2]
-    double* ext_v;          // [hull tiles * kHullDirs]
-    uint32_t* ext_i;        // [hull tiles * kHullDirs]
-    double* poly;           // [k_cap * (2 kHullDirs + 2)]
+    double* margin;         // [k_cap] of the filter polygon's test
     uint32_t* surv_cnt;     // [k_cap]
-    uint32_t* chain_list;   // [k_cap] clusters for the workgroup hull chain (count in small[7])
     uint32_t* small;        // [64] device scalars: K, tiles, inliers, large-cluster tiles, K (hull), vertices,
-                            // hull tiles, chain-list length
+                            // hull tiles
     size_t bytes;
 };
 // count_rows: rows of counts (0: one per cluster)

@@ -5,22 +5,25 @@
 // from the few candidates left.  Here the whole hull stays on the device and
 // every pass over the inliers is tile-parallel, so one huge cluster (a floor)
 // spreads over the whole chip instead of one workgroup:
-//   B. per tile of inliers: project onto the in-plane basis (fp64) and find
-//      the extreme inlier in each of 8 directions (every 45 degrees);
+//   B. per tile of inliers: project onto the in-plane basis (fp64) and find an
+//      extreme inlier in each of 64 directions, a lane per direction;
 //   C. per cluster: combine the tiles' extremes; the convex polygon through
 //      them lies inside the hull, so a point strictly inside it (by a margin
 //      far above the fp64 rounding of the test) cannot be a hull vertex;
 //   D. per tile: keep only the points not strictly inside that polygon
 //      (block-aggregated compaction into the cluster's own region);
 //   E. per cluster: sort the survivors by (u, v, inlier index) -- in a
-//      wave's registers for at most 64, bitonic in LDS, or in global memory
-//      for very large survivor sets -- and run Andrew's monotone chain,
-//      popping on every non-left turn (strictly convex, counter-clockwise
-//      from the smallest point).  Up to LDS size the lower and the upper
-//      chain run at once; joined at their shared end points they give
-//      exactly the single-stack chain's output;
+//      wave's registers for at most 64, by a workgroup in LDS up to kLdsCap, in
+//      global memory beyond -- and find both chains of the hull (strictly
+//      convex, counter-clockwise from the smallest point);
 //   F. scan the vertex counts and pack the polygons, each vertex projected
 //      onto the plane.
+// The stage is bound by latency, not by bytes: nine launches with serial
+// chains in between took 130-280 us on the frames measured (an octagon filter
+// that left hundreds to thousands of survivors on a ray-cast floor, thinned by
+// one workgroup; one lane pruning each polygon; one lane per chain popping
+// point after point); with the 64-gon found by all tiles and the polygon and
+// the chains found by whole waves, six launches take 36-75 us.
 #include "vm_common.h"
 #include "vm_dev.h"
 
@@ -34,8 +37,12 @@ using namespace dev;
 constexpr int kTileThreads = 256;
 constexpr int kTileItems = 4;
 constexpr int kHullTile = kTileThreads * kTileItems;   // inliers per tile
-constexpr int kSmallGrid = 2048;   // workgroups of the wave-per-cluster kernels (8192 waves)
-constexpr int kLdsCap = 2048;                           // survivors sorted in LDS
+constexpr int kDirs = 64;          // support directions of the filter polygon, a lane each
+constexpr double kMargin = 4e-9;   // of the extent's square: the margin of the polygon's corners and of the filter
+constexpr int kPolyGrid = 2048;    // workgroups of the polygon kernel
+constexpr int kFinishGrid = 512;   // workgroups of the hull kernel: two per compute unit (67 KB of LDS)
+constexpr int kLdsCap = 2048;      // survivors sorted in LDS
+static_assert(kDirs == kWave, "a lane per direction");
 
 // Whether cluster k gets a polygon: it has a plane, its inlier list fits the
 // output and indexes its own points.
@@ -64,15 +71,38 @@ __device__ __forceinline__ ClusterFrame cluster_frame(uint32_t k, const uint32_t
     return f;
 }
 
+// The same projection in fp32, for the choice of the polygon and the first
+// test of a point against it.
+struct FrameF {
+    float u[3], v[3], ox, oy, oz;
+};
 
-// largest k with tile_off[k] <= t (tile_off is an exclusive scan of K entries)
+__device__ __forceinline__ FrameF frame_f(const ClusterFrame& f)
+{
+    return {{(float)f.B.u[0], (float)f.B.u[1], (float)f.B.u[2]},
+            {(float)f.B.v[0], (float)f.B.v[1], (float)f.B.v[2]},
+            (float)f.ox, (float)f.oy, (float)f.oz};
+}
+
+__device__ __forceinline__ float2 project_f(const FrameF& f, float x, float y, float z)
+{
+    const float dx = x - f.ox, dy = y - f.oy, dz = z - f.oz;
+    return make_float2(fmaf(f.u[0], dx, fmaf(f.u[1], dy, f.u[2] * dz)),
+                       fmaf(f.v[0], dx, fmaf(f.v[1], dy, f.v[2] * dz)));
+}
+
+// largest k with tile_off[k] <= t (tile_off is an exclusive scan of K entries),
+// found by a whole wave, 64 probes at a time: two dependent reads for up to
+// 4096 clusters, which is what a tile waits for before anything else
 __device__ __forceinline__ uint32_t cluster_of_tile(const uint32_t* __restrict__ tile_off, uint32_t K, uint32_t t)
 {
-    uint32_t lo = 0, hi = K;
-    while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (tile_off[mid] <= t) lo = mid;
-        else hi = mid;
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    uint32_t lo = 0, n = K;
+    while (n > 1) {
+        const uint32_t step = (n + kWave - 1) / kWave, i = lo + lane * step;
+        const bool le = lane * step < n && tile_off[min(i, K - 1u)] <= t;
+        lo += ((uint32_t)__popcll(__ballot(le)) - 1u) * step;
+        n = min(step, K - lo);
     }
     return lo;
 }
@@ -92,8 +122,6 @@ __global__ void __launch_bounds__(kBlock) k_hull_validate(const uint32_t* __rest
     const uint32_t K = validate_clusters(meta, off, kc, n_cap, status, &bad);
     if (threadIdx.x == 0) {
         small[4] = K;
-        small[7] = 0;   // chain list
-        small[9] = 0;   // mid list
     }
 }
 
@@ -136,69 +164,135 @@ __global__ void __launch_bounds__(kOneBlockThreads) k_hull_prepare(
     if (threadIdx.x == 0) {
         small[4] = K;
         small[6] = total[0];
-        small[7] = 0;   // chain list
-        small[9] = 0;   // mid list
     }
 }
 
 // ---- B: projection + directional extremes per tile --------------------------------
+// The polygon that the extremes give may be through any inliers (it only has to
+// lie inside the hull), so the extremes are compared in fp32, with a point's
+// number in the value's lowest bits: one instruction makes the key,
+// half of one keeps the largest.  Opposite directions share the product, and
+// a lane has four directions (q, q + 16 and their opposites) for a quarter of
+// its wave's points: a point per lane and direction took 64 LDS reads per
+// wave and 5 instructions each and was bound by both (526 us for the 34M
+// inliers of 2000 clusters, 257 us so; the bytes take about 130).  A tile's 64
+// extremes (value, position in the inlier list) go to ext_v / ext_i.
+__device__ __forceinline__ float key_of(float v, uint32_t pos, uint32_t mask)
+{
+    return __uint_as_float((__float_as_uint(v) & ~mask) | pos);
+}
+
+// largest / smallest of three, a NaN loses (the compiler's own form quiets
+// every operand first)
+__device__ __forceinline__ float max3f(float a, float b, float c)
+{
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+__device__ __forceinline__ float min3f(float a, float b, float c)
+{
+    float r;
+    asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
 __global__ void __launch_bounds__(kTileThreads) k_hull_extremes(
     const uint32_t* __restrict__ small, const uint32_t* __restrict__ tile_off, const uint32_t* __restrict__ off,
     const float* __restrict__ X, const float* __restrict__ Y, const float* __restrict__ Z,
     const float4* __restrict__ plane, const uint32_t* __restrict__ in_off, const uint32_t* __restrict__ in_idx,
-    double* __restrict__ ext_v, uint32_t* __restrict__ ext_i)
+    float* __restrict__ ext_v, uint32_t* __restrict__ ext_i)
 {
-    __shared__ double rv[kTileThreads / kWave][kDirs];
-    __shared__ uint32_t ri[kTileThreads / kWave][kDirs];
+    constexpr int kWaves = kTileThreads / kWave;
+    constexpr int kQuarter = kHullTile / kWaves;       // points of a wave
+    constexpr int kGroups = 4;                         // lane groups that share them, two points at a time
+    constexpr int kStep = 2 * kGroups;
+    constexpr uint32_t kPosMask = kQuarter / kGroups - 1;
+    static_assert(kDirs == 4 * (kWave / kGroups) && (kPosMask & (kPosMask + 1)) == 0, "four directions per lane");
+    __shared__ __align__(16) float2 uv[kHullTile];
+    __shared__ float rv[kWaves * kGroups][kDirs];
+    __shared__ uint32_t ri[kWaves * kGroups][kDirs];
     const uint32_t K = small[4];
     const uint32_t T = small[6];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int dir = lane & (kDirs / 4 - 1), grp = lane / (kDirs / 4);
+    float sn, cs;
+    sincospif((float)dir / (kDirs / 2), &sn, &cs);
     for (uint32_t t = blockIdx.x; t < T; t += gridDim.x) {
         const uint32_t k = cluster_of_tile(tile_off, K, t);
         const ClusterFrame f = cluster_frame(k, off, X, Y, Z, plane, in_off, in_idx);
-        const uint32_t j0 = (t - tile_off[k]) * kHullTile, j1 = min(j0 + kHullTile, f.m);
-        double bv[kDirs];
-        uint32_t bi[kDirs];
+        const FrameF ff = frame_f(f);
+        const uint32_t j0 = (t - tile_off[k]) * kHullTile, m = min((uint32_t)kHullTile, f.m - j0);
+        // a wave projects and then searches its own quarter of the tile; what
+        // is not a point of the cluster is NaN and never an extreme
+        const int q0 = wave * kQuarter;
+        uint32_t li[kQuarter / kWave];
 #pragma unroll
-        for (int d = 0; d < kDirs; ++d) { bv[d] = -INFINITY; bi[d] = 0xFFFFFFFFu; }
-        for (uint32_t j = j0 + threadIdx.x; j < j1; j += kTileThreads) {
-            const uint32_t li = in_idx[f.ib + j];
-            if (li >= f.nk) continue;
-            const uint32_t i = f.pb + li;
-            double pu, pv;
-            project(f, X[i], Y[i], Z[i], &pu, &pv);
-#pragma unroll
-            for (int d = 0; d < kDirs; ++d) {
-                const double v = dir_val(d, pu, pv);
-                if (v > bv[d]) { bv[d] = v; bi[d] = j; }   // j ascends per thread: first maximum kept
-            }
+        for (int it = 0; it < kQuarter / kWave; ++it) {
+            const uint32_t j = (uint32_t)(q0 + it * kWave + lane);
+            li[it] = in_idx[f.ib + j0 + min(j, m - 1u)];
+            if (j >= m) li[it] = f.nk;
         }
 #pragma unroll
-        for (int d = 0; d < kDirs; ++d) {
-            for (int s = kWave / 2; s >= 1; s >>= 1) {
-                const double ov = __shfl_xor(bv[d], s, kWave);
-                const uint32_t oi = __shfl_xor(bi[d], s, kWave);
-                if (ov > bv[d] || (ov == bv[d] && oi < bi[d])) { bv[d] = ov; bi[d] = oi; }
-            }
-            if (lane == 0) { rv[wave][d] = bv[d]; ri[wave][d] = bi[d]; }
+        for (int it = 0; it < kQuarter / kWave; ++it) {
+            const uint32_t i = f.pb + min(li[it], f.nk - 1u);
+            const float2 p = project_f(ff, X[i], Y[i], Z[i]);
+            uv[q0 + it * kWave + lane] = li[it] < f.nk ? p : make_float2(__builtin_nanf(""), 0.0f);
         }
+        wave_sync();
+        float hi0 = -INFINITY, hi1 = -INFINITY, lo0 = INFINITY, lo1 = INFINITY;
+        const int n = min(kQuarter, (int)m - q0);
+#pragma unroll 4
+        for (int j = 0; j < n; j += kStep) {
+            const float4 p = *(const float4*)&uv[q0 + j + 2 * grp];
+            const uint32_t pos = (uint32_t)(j / kGroups);
+            const float a0 = key_of(fmaf(p.x, cs, p.y * sn), pos, kPosMask);
+            const float b0 = key_of(fmaf(p.z, cs, p.w * sn), pos + 1u, kPosMask);
+            const float a1 = key_of(fmaf(p.y, cs, -(p.x * sn)), pos, kPosMask);
+            const float b1 = key_of(fmaf(p.w, cs, -(p.z * sn)), pos + 1u, kPosMask);
+            hi0 = max3f(hi0, a0, b0);
+            lo0 = min3f(lo0, a0, b0);
+            hi1 = max3f(hi1, a1, b1);
+            lo1 = min3f(lo1, a1, b1);
+        }
+        const auto put = [&](int d, float key, bool none) {
+            const uint32_t pos = __float_as_uint(key) & kPosMask;
+            rv[wave * kGroups + grp][d] = none ? -INFINITY : d < kDirs / 2 ? key : -key;
+            ri[wave * kGroups + grp][d] = j0 + (uint32_t)q0 + (pos >> 1) * kStep + 2u * (uint32_t)grp + (pos & 1u);
+        };
+        put(dir, hi0, hi0 == -INFINITY);
+        put(dir + kDirs / 4, hi1, hi1 == -INFINITY);
+        put(dir + kDirs / 2, lo0, lo0 == INFINITY);
+        put(dir + 3 * kDirs / 4, lo1, lo1 == INFINITY);
         __syncthreads();
-        if (threadIdx.x < kDirs) {
-            const int d = threadIdx.x;
-            double v = rv[0][d];
-            uint32_t ix = ri[0][d];
-            for (int w = 1; w < kTileThreads / kWave; ++w)
-                if (rv[w][d] > v || (rv[w][d] == v && ri[w][d] < ix)) { v = rv[w][d]; ix = ri[w][d]; }
-            ext_v[kDirs * (size_t)t + d] = v;
-            ext_i[kDirs * (size_t)t + d] = ix;
+        if (wave == 0) {
+            float bv = -INFINITY;
+            uint32_t bi = 0xFFFFFFFFu;
+#pragma unroll
+            for (int w = 0; w < kWaves * kGroups; ++w)
+                if (rv[w][lane] > bv) {
+                    bv = rv[w][lane];
+                    bi = ri[w][lane];
+                }
+            ext_v[kDirs * (size_t)t + lane] = bv;
+            ext_i[kDirs * (size_t)t + lane] = bi;
         }
         __syncthreads();
     }
 }
 
 // ---- C: per-cluster extreme polygon -----------------------------------------------
-// poly layout per cluster (kPolyWords doubles): u[kDirs], v[kDirs], margin,
-// vertex count (-1: no polygon for the cluster, 0: no filtering)
+// A workgroup per cluster: its waves share the tiles, lane d its extreme in
+// direction d; then one wave merges repeated extremes and drops the corners
+// that do not turn left by more than a margin, all lanes at once, until every
+// corner is strictly convex (at least every other bad corner of a run goes in
+// a round, so the rounds end).  The rest bound a convex polygon inside the
+// hull.  Its corners, as positions in the inlier list, counter-clockwise, go
+// to the first 64 words of the cluster's own region of hull_tmp, their number
+// (below 3: no filtering) to the next one; the filtered clusters have more
+// than 64 inliers, so the region holds them.  margin[k] is far above the fp64
+// rounding of a cross product at the polygon's scale.
 __global__ void __launch_bounds__(kBlock) k_hull_poly(const uint32_t* __restrict__ small,
                                                      const uint32_t* __restrict__ tile_off,
                                                      const uint32_t* __restrict__ off, const float* __restrict__ X,
@@ -206,173 +300,317 @@ __global__ void __launch_bounds__(kBlock) k_hull_poly(const uint32_t* __restrict
                                                      const float4* __restrict__ plane,
                                                      const uint32_t* __restrict__ in_off,
                                                      const uint32_t* __restrict__ in_idx,
-                                                     const double* __restrict__ ext_v,
-                                                     const uint32_t* __restrict__ ext_i, double* __restrict__ poly,
-                                                     uint32_t* __restrict__ surv_cnt)
+                                                     const float* __restrict__ ext_v,
+                                                     const uint32_t* __restrict__ ext_i, double* __restrict__ margin,
+                                                     uint32_t* __restrict__ hull_tmp, uint32_t* __restrict__ surv_cnt)
 {
+    constexpr int kWaves = kBlock / kWave;
+    constexpr uint32_t kAhead = 8;   // tiles whose reads a wave has in flight
+    __shared__ double su[kWave], sv[kWave];
+    __shared__ float rv[kWaves][kDirs];
+    __shared__ uint32_t ri[kWaves][kDirs];
     const uint32_t K = small[4];
     const uint32_t T = small[6];
     const int lane = threadIdx.x & (kWave - 1);
-    const uint32_t waves = gridDim.x * (kBlock / kWave);
-    const uint32_t w0 = __builtin_amdgcn_readfirstlane(blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave);
-    for (uint32_t k = w0; k < K; k += waves) {   // a wave per cluster (wave-uniform index: scalar loads)
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    for (uint32_t k = blockIdx.x; k < K; k += gridDim.x) {
         const uint32_t t0 = tile_off[k], t1 = tiles_end(tile_off, k, K, T);
-        if (lane == 0) surv_cnt[k] = 0;
-        double* P = poly + kPolyWords * (size_t)k;
-        if (t0 == t1) {
-            if (lane == 0) P[kPolyWords - 1] = -1.0;
+        if (threadIdx.x == 0) surv_cnt[k] = 0;
+        if (t0 == t1) continue;   // workgroup-uniform
+        float bv = -INFINITY;
+        uint32_t e = 0xFFFFFFFFu;
+        for (uint32_t t = t0 + wave * kAhead; t < t1; t += kWaves * kAhead) {
+            float v[kAhead];
+            uint32_t i[kAhead];
+#pragma unroll
+            for (uint32_t q = 0; q < kAhead; ++q) {
+                const size_t x = kDirs * (size_t)min(t + q, t1 - 1u) + lane;
+                v[q] = ext_v[x];
+                i[q] = ext_i[x];
+            }
+#pragma unroll
+            for (uint32_t q = 0; q < kAhead; ++q)
+                if (v[q] > bv) {
+                    bv = v[q];
+                    e = i[q];
+                }
+        }
+        rv[wave][lane] = bv;
+        ri[wave][lane] = e;
+        __syncthreads();
+        if (wave != 0) {
+            __syncthreads();   // (the end of the round below)
             continue;
         }
-        // the wave strides over the cluster's tiles, then reduces each direction
-        double bv[kDirs];
-        uint32_t bi[kDirs];
 #pragma unroll
-        for (int d = 0; d < kDirs; ++d) { bv[d] = -INFINITY; bi[d] = 0xFFFFFFFFu; }
-        for (uint32_t t = t0 + lane; t < t1; t += kWave) {
-#pragma unroll
-            for (int d = 0; d < kDirs; ++d) {
-                const double tv = ext_v[kDirs * (size_t)t + d];
-                const uint32_t ti = ext_i[kDirs * (size_t)t + d];
-                if (tv > bv[d] || (tv == bv[d] && ti < bi[d])) { bv[d] = tv; bi[d] = ti; }
+        for (int w = 1; w < kWaves; ++w)
+            if (rv[w][lane] > bv) {
+                bv = rv[w][lane];
+                e = ri[w][lane];
             }
+        const ClusterFrame f = cluster_frame(k, off, X, Y, Z, plane, in_off, in_idx);
+        double u = 0.0, v = 0.0;
+        const bool found = e < f.m;
+        if (found) {
+            const uint32_t i = f.pb + min(in_idx[f.ib + e], f.nk - 1u);
+            project(f, X[i], Y[i], Z[i], &u, &v);
         }
-        uint32_t e[kDirs];
-#pragma unroll
-        for (int d = 0; d < kDirs; ++d) {
-            for (int sft = kWave / 2; sft >= 1; sft >>= 1) {
-                const double ov = __shfl_xor(bv[d], sft, kWave);
-                const uint32_t oi = __shfl_xor(bi[d], sft, kWave);
-                if (ov > bv[d] || (ov == bv[d] && oi < bi[d])) { bv[d] = ov; bi[d] = oi; }
+        su[lane] = u;
+        sv[lane] = v;
+        wave_sync();
+        // the corners: extremes that differ from the one before
+        const uint32_t prev = __shfl(e, (lane + kWave - 1) & (kWave - 1), kWave);
+        uint64_t alive = __ballot(found) == ~0ull ? __ballot(e != prev) : 0ull;
+        const double span = wave_max_d(fmax(fabs(u - su[0]), fabs(v - sv[0])));
+        // (the largest distance from one corner is at least half the extent)
+        const double mg = kMargin * span * span + 1e-300;
+        const uint64_t below = (1ull << lane) - 1ull, above = ~below & ~(1ull << lane);
+        while (__popcll(alive) >= 3) {
+            bool bad = false;
+            const bool me = (alive >> lane) & 1ull;
+            int p = 0;
+            if (me) {
+                // neighbours on the circle of corners
+                p = (alive & below) ? 63 - __clzll((long long)(alive & below)) : 63 - __clzll((long long)alive);
+                const int n = __ffsll((long long)((alive & above) ? (alive & above) : alive)) - 1;
+                bad = cross3(su[p], sv[p], u, v, su[n], sv[n]) <= mg;
             }
-            e[d] = bi[d];
+            const uint64_t b = __ballot(bad);
+            if (b == 0) break;
+            const bool even = (__popcll(alive & below) & 1) == 0;
+            alive &= ~__ballot(bad && (even || !((b >> p) & 1ull)));
         }
+        const uint32_t np = (uint32_t)__popcll(alive);
+        uint32_t* out = hull_tmp + f.ib + k;
+        if ((alive >> lane) & 1ull) out[__popcll(alive & below)] = e;
         if (lane == 0) {
-            const ClusterFrame f = cluster_frame(k, off, X, Y, Z, plane, in_off, in_idx);
-            extreme_polygon(e, f.m, P, [&](uint32_t j, double* pu, double* pv) {
-                const uint32_t i = f.pb + in_idx[f.ib + j];
-                project(f, X[i], Y[i], Z[i], pu, pv);
-            });
+            out[kDirs] = np;
+            margin[k] = mg;
         }
+        __syncthreads();   // the scratch is reused by the next cluster
     }
 }
 
 // ---- D: survivors of the polygon test, compacted per cluster ---------------------
+// Whether (u, v) lies strictly inside the convex polygon P[0..np): the wedge
+// at corner 0 that holds it is found by bisection, then the wedge's outer
+// edge and both edges at corner 0 (a point that nearly coincides with that
+// corner may be put in any wedge) are tested by the margin.
+template <typename F2, typename F>
+__device__ __forceinline__ bool inside_polygon(const F2* P, int np, F mg, F u, F v)
+{
+    const F2 c0 = P[0];
+    const F wu = u - c0.x, wv = v - c0.y;
+    const auto side = [&](int i) { return (P[i].x - c0.x) * wv - (P[i].y - c0.y) * wu; };
+    int lo = 1, hi = np - 1;   // the wedge (lo, hi)
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (side(mid) >= F(0)) lo = mid;
+        else hi = mid;
+    }
+    const F2 a = P[lo], b = P[hi];
+    return (b.x - a.x) * (v - a.y) - (b.y - a.y) * (u - a.x) > mg && side(1) > mg && side(np - 1) < -mg;
+}
+
+// A point is first tested in fp32, by a margin far above the rounding there
+// (1e-6 of the extent in a coordinate, 8e-6 of its square in a product).  The
+// few near the border or outside are collected and tested in fp64 by margin[k],
+// so that one wave does for a tile what else nearly every wave would run for a
+// lane or two (34M inliers in no order: 277 us with fp64 alone, 355 us with
+// both in place, 312 us so).
+constexpr double kMarginF = 3e-5;   // of the extent's square
+
+// (extents whose square leaves fp32's range are left to fp64)
+__device__ __forceinline__ float margin_f(double mg)
+{
+    const double m = mg * (kMarginF / kMargin);
+    return m < 1e30 ? (float)m + 1e-37f : INFINITY;
+}
+
 __global__ void __launch_bounds__(kTileThreads) k_hull_filter(
     const uint32_t* __restrict__ small, const uint32_t* __restrict__ tile_off, const uint32_t* __restrict__ off,
     const float* __restrict__ X, const float* __restrict__ Y, const float* __restrict__ Z,
     const float4* __restrict__ plane, const uint32_t* __restrict__ in_off, const uint32_t* __restrict__ in_idx,
-    const double* __restrict__ poly, uint32_t* __restrict__ surv_cnt, double* __restrict__ gu,
-    double* __restrict__ gv, uint32_t* __restrict__ gi)
+    const double* __restrict__ margin, const uint32_t* __restrict__ hull_tmp, uint32_t* __restrict__ surv_cnt,
+    double* __restrict__ gu, double* __restrict__ gv, uint32_t* __restrict__ gi)
 {
-    __shared__ double P[kPolyWords];
-    __shared__ uint32_t lcount, lbase;
+    __shared__ double2 poly[kDirs];
+    __shared__ float2 polyf[kDirs];
+    __shared__ float4 rest[kHullTile];   // the points left for the fp64 test, with their numbers
+    __shared__ uint32_t nrest;
     const uint32_t K = small[4];
     const uint32_t T = small[6];
+    const int lane = threadIdx.x & (kWave - 1);
     for (uint32_t t = blockIdx.x; t < T; t += gridDim.x) {
         const uint32_t k = cluster_of_tile(tile_off, K, t);
-        if (threadIdx.x < kPolyWords) P[threadIdx.x] = poly[kPolyWords * (size_t)k + threadIdx.x];
-        if (threadIdx.x == 0) lcount = 0;
-        __syncthreads();
         const ClusterFrame f = cluster_frame(k, off, X, Y, Z, plane, in_off, in_idx);
+        const FrameF ff = frame_f(f);
+        const uint32_t* corner = hull_tmp + f.ib + k;
+        const int np = (int)corner[kDirs];
+        const double mg = margin[k];
+        const float mgf = margin_f(mg);
         const uint32_t j0 = (t - tile_off[k]) * kHullTile;
-        const int np = (int)P[kPolyWords - 1];
-        const double mg = P[kPolyWords - 2];
-        double su[kTileItems], sv[kTileItems];
-        uint32_t sj[kTileItems], slot[kTileItems];
-        int ns = 0;
+        // the tile's points, while the polygon's come in
+        uint32_t pt[kTileItems];
+        float x[kTileItems], y[kTileItems], z[kTileItems];
+        bool in[kTileItems];
 #pragma unroll
         for (int it = 0; it < kTileItems; ++it) {
             const uint32_t j = j0 + it * kTileThreads + threadIdx.x;
-            if (j >= f.m) continue;
-            const uint32_t li = in_idx[f.ib + j];
-            if (li >= f.nk) continue;
-            const uint32_t i = f.pb + li;
-            double pu, pv;
-            project(f, X[i], Y[i], Z[i], &pu, &pv);
-            bool inside = np >= 3;
-            for (int a = 0; inside && a < np; ++a) {
-                const int b = (a + 1 == np) ? 0 : a + 1;
-                inside = cross3(P[a], P[kDirs + a], P[b], P[kDirs + b], pu, pv) > mg;
-            }
-            if (!inside) {
-                su[ns] = pu;
-                sv[ns] = pv;
-                sj[ns] = j;
-                slot[ns] = atomicAdd(&lcount, 1u);
-                ++ns;
-            }
+            const uint32_t li = in_idx[f.ib + min(j, f.m - 1u)];
+            in[it] = j < f.m && li < f.nk;
+            pt[it] = f.pb + min(li, f.nk - 1u);
+        }
+#pragma unroll
+        for (int it = 0; it < kTileItems; ++it) {
+            x[it] = X[pt[it]];
+            y[it] = Y[pt[it]];
+            z[it] = Z[pt[it]];
+        }
+        if ((int)threadIdx.x < np) {
+            const uint32_t i = f.pb + in_idx[f.ib + corner[threadIdx.x]];
+            const float cx = X[i], cy = Y[i], cz = Z[i];
+            double2 c;
+            project(f, cx, cy, cz, &c.x, &c.y);
+            poly[threadIdx.x] = c;
+            polyf[threadIdx.x] = project_f(ff, cx, cy, cz);
+        }
+        if (threadIdx.x == 0) nrest = 0;
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < kTileItems; ++it) {
+            const float2 p = project_f(ff, x[it], y[it], z[it]);
+            if (in[it] && !(np >= 3 && inside_polygon(polyf, np, mgf, p.x, p.y)))
+                rest[atomicAdd(&nrest, 1u)] =
+                    make_float4(x[it], y[it], z[it], __uint_as_float(j0 + it * kTileThreads + threadIdx.x));
         }
         __syncthreads();
-        if (threadIdx.x == 0) lbase = lcount ? atomicAdd(&surv_cnt[k], lcount) : 0u;
-        __syncthreads();
-        for (int a = 0; a < ns; ++a) {
-            const uint32_t dst = f.ib + lbase + slot[a];
-            gu[dst] = su[a];
-            gv[dst] = sv[a];
-            gi[dst] = sj[a];
+        const uint32_t n = nrest;
+        for (uint32_t r0 = 0; r0 < n; r0 += kTileThreads) {
+            const uint32_t r = r0 + threadIdx.x;
+            double u = 0.0, v = 0.0;
+            float4 p;
+            bool out = false;
+            if (r < n) {
+                p = rest[r];
+                project(f, p.x, p.y, p.z, &u, &v);
+                out = !(np >= 3 && inside_polygon(poly, np, mg, u, v));
+            }
+            const uint64_t b = __ballot(out);
+            if (b == 0) continue;
+            uint32_t base = 0;
+            if (lane == 0) base = atomicAdd(&surv_cnt[k], (uint32_t)__popcll(b));
+            base = __shfl(base, 0, kWave);
+            if (out) {
+                const uint32_t dst = f.ib + base + (uint32_t)__popcll(b & ((1ull << lane) - 1ull));
+                gu[dst] = u;
+                gv[dst] = v;
+                gi[dst] = __float_as_uint(p.w);
+            }
         }
         __syncthreads();
     }
 }
 
-// Filtered clusters whose survivors need a workgroup: up to kMidMax of them
-// go to the mid list (stored from the end of the list buffer, count in
-// small[9]) for k_hull_small, more to the chain list (count in small[7]) for
-// k_hull_chain.  The two never meet: together they hold at most K <= cap
-// entries.
-constexpr uint32_t kMidMax = kChainBlock;
-static_assert(kBlock == kChainBlock, "k_hull_small runs the workgroup chain with its own workgroup");
-
-__global__ void __launch_bounds__(kBlock) k_hull_list(uint32_t* __restrict__ small,
-                                                      const uint32_t* __restrict__ tile_off,
-                                                      const uint32_t* __restrict__ surv_cnt,
-                                                      uint32_t* __restrict__ list, uint32_t cap)
+// ---- E: the hulls of the survivors -------------------------------------------------
+// A survivor set beyond LDS: sorted in global memory (bitonic, partners beyond
+// ns are +infinity) by the workgroup, chained by one thread.
+__device__ void global_chain(uint32_t k, uint32_t ns, uint32_t ib, double* U, double* Vv, uint32_t* I,
+                             const uint32_t* __restrict__ in_idx, uint32_t* hull_cnt, uint32_t* hull_tmp,
+                             double* area_out)
 {
-    const uint32_t K = small[4];
-    const uint32_t T = small[6];
-    for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < K; k += gridDim.x * blockDim.x) {
-        if (tile_off[k] == tiles_end(tile_off, k, K, T)) continue;   // not filtered: the wave path
-        const uint32_t ns = surv_cnt[k];
-        if (ns <= (uint32_t)kWave) continue;
-        if (ns <= kMidMax) list[cap - 1u - atomicAdd(&small[9], 1u)] = k;
-        else list[atomicAdd(&small[7], 1u)] = k;
+    uint32_t N = 1;
+    while (N < ns) N <<= 1;
+    for (uint32_t size = 2; size <= N; size <<= 1) {
+        for (uint32_t t = threadIdx.x; t < N / 2; t += kChainBlock) {
+            const uint32_t blk = t / (size >> 1), r = t % (size >> 1);
+            const uint32_t a = blk * size + r, b = blk * size + size - 1 - r;
+            if (b < ns && p2_less(U[b], Vv[b], I[b], U[a], Vv[a], I[a])) swap3(U, Vv, I, a, b);
+        }
+        __syncthreads();
+        for (uint32_t stride = size >> 2; stride > 0; stride >>= 1) {
+            for (uint32_t t = threadIdx.x; t < N / 2; t += kChainBlock) {
+                const uint32_t a = 2 * t - (t & (stride - 1)), b = a + stride;
+                if (b < ns && p2_less(U[b], Vv[b], I[b], U[a], Vv[a], I[a])) swap3(U, Vv, I, a, b);
+            }
+            __syncthreads();
+        }
     }
+    if (threadIdx.x == 0) {
+        // single-stack chain; cluster k's stack is hull_tmp[ib + k, ib + k + m + 1)
+        // and never holds more than ns + 1 <= m + 1 entries
+        uint32_t* st = hull_tmp + ib + k;
+        uint32_t h = 0;
+        for (uint32_t i = 0; i < ns; ++i) {
+            while (h >= 2) {
+                const uint32_t a = st[h - 2], b = st[h - 1];
+                if (cross3(U[a], Vv[a], U[b], Vv[b], U[i], Vv[i]) <= 0.0) --h;
+                else break;
+            }
+            st[h++] = i;
+        }
+        const uint32_t lower = h + 1;
+        for (int32_t i = (int32_t)ns - 2; i >= 0; --i) {
+            while (h >= lower) {
+                const uint32_t a = st[h - 2], b = st[h - 1];
+                if (cross3(U[a], Vv[a], U[b], Vv[b], U[i], Vv[i]) <= 0.0) --h;
+                else break;
+            }
+            st[h++] = (uint32_t)i;
+        }
+        --h;   // the last point repeats the first
+        double s = 0.0;
+        if (h >= 3) {
+            for (uint32_t q = 0; q < h; ++q) {
+                const uint32_t p0 = st[q], p1 = st[q + 1 == h ? 0 : q + 1];
+                s = s + (U[p0] * Vv[p1] - U[p1] * Vv[p0]);
+            }
+        }
+        area_out[k] = h >= 3 ? 0.5 * s : 0.0;
+        // entry q of the stack is read before slot q is overwritten
+        for (uint32_t q = 0; q < h; ++q) hull_tmp[ib + k + q] = in_idx[ib + I[st[q]]];
+        hull_cnt[k] = h;
+    }
+    __syncthreads();
 }
 
-// Clusters with at most 64 points to chain -- survivors of the filter, or
-// (clusters the filter skips) all inliers, projected here exactly as the
-// filter projects them -- one wave each, four per workgroup.  The points are
-// sorted across the wave's lanes (bitonic network on shuffles, same order:
-// u, then v, then inlier position), then one lane runs the lower and the
-// upper chain; the result is the same as the workgroup path's.  Up to half
-// of the workgroups first take the mid list's clusters (65..kMidMax
-// survivors) with the workgroup chain, so that those serial chains run while
-// the other workgroups go through the small clusters instead of in a launch
-// of their own afterwards; the rest split the small clusters among their
-// waves.
-__global__ void __launch_bounds__(kBlock) k_hull_small(
-    uint32_t* __restrict__ small, const uint32_t* __restrict__ list, uint32_t cap, const uint32_t* __restrict__ tile_off,
-    const uint32_t* __restrict__ off,
+// Workgroup b takes clusters b, b + G, ..., b + 7 G of each round of 8 G (G
+// workgroups): while there are fewer clusters than workgroups each gets one,
+// so the large ones, neighbours in label order, run side by side.  First the
+// workgroup chains together those of them with more than 64 survivors of the
+// filter, then each wave its own of the others: at most 64 survivors, or (a
+// cluster that the filter skips) all inliers, projected here exactly as the
+// filter projects them.
+__global__ void __launch_bounds__(kChainBlock) k_hull_finish(
+    const uint32_t* __restrict__ small, const uint32_t* __restrict__ tile_off, const uint32_t* __restrict__ off,
     const float* __restrict__ X, const float* __restrict__ Y, const float* __restrict__ Z,
     const float4* __restrict__ plane, const int32_t* __restrict__ best, uint32_t in_cap,
     const uint32_t* __restrict__ in_off, const uint32_t* __restrict__ in_idx, const uint32_t* __restrict__ surv_cnt,
-    const double* __restrict__ gu, const double* __restrict__ gv, const uint32_t* __restrict__ gi,
-    uint32_t* __restrict__ hull_cnt, uint32_t* __restrict__ hull_tmp, double* __restrict__ area_out)
+    double* __restrict__ gu, double* __restrict__ gv, uint32_t* __restrict__ gi, uint32_t* __restrict__ hull_cnt,
+    uint32_t* __restrict__ hull_tmp, double* __restrict__ area_out)
 {
-    __shared__ double su[kBlock / kWave][kWave];
-    __shared__ double sv[kBlock / kWave][kWave];
-    __shared__ uint32_t si[kBlock / kWave][kWave];
-    __shared__ uint8_t st[kBlock / kWave][2 * kWave + 2];
-    __shared__ ChainLds<kMidMax> L;
+    constexpr uint32_t kWaves = kChainBlock / kWave;
+    __shared__ double su[kWaves][kWave];
+    __shared__ double sv[kWaves][kWave];
+    __shared__ uint32_t si[kWaves][kWave];
+    __shared__ uint8_t st[kWaves][2 * kWave + 2];
+    __shared__ ChainLds<kLdsCap> L;
     const uint32_t K = small[4];
     const uint32_t T = small[6];
-    const uint32_t nmid = small[9];
-    const uint32_t gmid = nmid < gridDim.x / 2 ? nmid : gridDim.x / 2;   // uniform over the grid
-    if (blockIdx.x < gmid) {
-        for (uint32_t c = blockIdx.x; c < nmid; c += gmid) {
-            const uint32_t k = list[cap - 1u - c];
+    const uint32_t G = gridDim.x;
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    for (uint32_t c0 = blockIdx.x; c0 < K; c0 += kWaves * G) {
+        for (uint32_t w = 0; w < kWaves && c0 + w * G < K; ++w) {   // workgroup-uniform
+            const uint32_t k = c0 + w * G;
+            if (tile_off[k] == tiles_end(tile_off, k, K, T)) continue;
+            const uint32_t ns = surv_cnt[k];
+            if (ns <= (uint32_t)kWave) continue;
             const uint32_t ib = in_off[k];
-            const uint32_t ns = surv_cnt[k];   // 65..kMidMax
+            if (ns > (uint32_t)kLdsCap) {
+                global_chain(k, ns, ib, gu + ib, gv + ib, gi + ib, in_idx, hull_cnt, hull_tmp, area_out);
+                continue;
+            }
             double area = 0.0;
             const uint32_t hh = block_chain(L, ns,
                                             [&](uint32_t t, double* u, double* v, uint32_t* id) {
@@ -388,21 +626,15 @@ __global__ void __launch_bounds__(kBlock) k_hull_small(
             }
             __syncthreads();   // L is reused by the next cluster
         }
-        return;
-    }
-    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-    const uint32_t waves = (gridDim.x - gmid) * (kBlock / kWave);
-    // wave-uniform cluster index: the cluster's own loads become scalar
-    const uint32_t w0 = __builtin_amdgcn_readfirstlane((blockIdx.x - gmid) * (kBlock / kWave) + wv);
-    for (uint32_t k = w0; k < K; k += waves) {
-        const bool tiled = tile_off[k] != tiles_end(tile_off, k, K, T);
+        const uint32_t k = c0 + wv * G;
+        if (k >= K) continue;   // wave-uniform, no barriers below
         uint32_t ns;
         double u = INFINITY, v = INFINITY;
         uint32_t i = 0xFFFFFFFFu;
         const uint32_t ib = in_off[k];
-        if (tiled) {
+        if (tile_off[k] != tiles_end(tile_off, k, K, T)) {
             ns = surv_cnt[k];
-            if (ns > (uint32_t)kWave) continue;   // listed for a workgroup chain
+            if (ns > (uint32_t)kWave) continue;   // done by the workgroup
             if ((uint32_t)lane < ns) {
                 u = gu[ib + lane];
                 v = gv[ib + lane];
@@ -430,257 +662,17 @@ __global__ void __launch_bounds__(kBlock) k_hull_small(
             hull_cnt[k] = r.h;
         }
         if ((uint32_t)lane < r.h) hull_tmp[ib + k + lane] = in_idx[ib + si[wv][r.vi]];
-        __builtin_amdgcn_wave_barrier();
-    }
-}
-
-// Survivor sets of more than kRefineMin points are thinned once more before sorting:
-// the extremes of the survivors in kRefineDirs directions (every 360/64
-// degrees, counter-clockwise) bound a convex polygon inside the hull, and the
-// survivors strictly inside it (by the same margin as the octagon's) are
-// dropped.  The hull of what is left is the same polygon, since every vertex
-// survives; a disc keeps about 0.2 % of its points outside a 64-gon.
-constexpr int kRefineDirs = 64;
-constexpr uint32_t kRefineMin = 512;   // survivor sets above this are refined (a few passes beat a long sort)
-constexpr int kRefineBatch = 8;   // directions reduced per pass over the survivors
-
-struct RefineLds {
-    double rv[kChainBlock / kWave][kRefineBatch];
-    uint32_t ri[kChainBlock / kWave][kRefineBatch];
-    uint32_t ext[kRefineDirs];
-    double pu[kRefineDirs], pv[kRefineDirs];
-    double margin;
-    int np;
-    uint32_t wcnt[kChainBlock / kWave];
-};
-
-// compacts U/V/I[0, ns) in place to the points not strictly inside the
-// refinement polygon; returns their number (every thread of the block calls it)
-__device__ uint32_t refine_survivors(RefineLds& R, double* U, double* V, uint32_t* I, uint32_t ns)
-{
-    const int lane = threadIdx.x & (kWave - 1), wv = threadIdx.x / kWave;
-    for (int d0 = 0; d0 < kRefineDirs; d0 += kRefineBatch) {
-        double cs[kRefineBatch], sn[kRefineBatch], bv[kRefineBatch];
-        uint32_t bi[kRefineBatch];
-#pragma unroll
-        for (int j = 0; j < kRefineBatch; ++j) {
-            sincospi((double)(d0 + j) / (kRefineDirs / 2), &sn[j], &cs[j]);
-            bv[j] = -INFINITY;
-            bi[j] = 0xFFFFFFFFu;
-        }
-        for (uint32_t t = threadIdx.x; t < ns; t += kChainBlock) {
-            const double u = U[t], v = V[t];
-#pragma unroll
-            for (int j = 0; j < kRefineBatch; ++j) {
-                const double val = u * cs[j] + v * sn[j];
-                if (val > bv[j]) {   // t ascends per thread: the first maximum is kept
-                    bv[j] = val;
-                    bi[j] = t;
-                }
-            }
-        }
-        // the largest value, lowest position on ties
-#pragma unroll
-        for (int j = 0; j < kRefineBatch; ++j) {
-            for (int o = kWave / 2; o > 0; o >>= 1) {
-                const double ov = __shfl_xor(bv[j], o, kWave);
-                const uint32_t oi = __shfl_xor(bi[j], o, kWave);
-                if (ov > bv[j] || (ov == bv[j] && oi < bi[j])) {
-                    bv[j] = ov;
-                    bi[j] = oi;
-                }
-            }
-            if (lane == 0) {
-                R.rv[wv][j] = bv[j];
-                R.ri[wv][j] = bi[j];
-            }
-        }
-        __syncthreads();
-        if (threadIdx.x < kRefineBatch) {
-            const int j = threadIdx.x;
-            double b = R.rv[0][j];
-            uint32_t i = R.ri[0][j];
-            for (int w = 1; w < kChainBlock / kWave; ++w)
-                if (R.rv[w][j] > b || (R.rv[w][j] == b && R.ri[w][j] < i)) {
-                    b = R.rv[w][j];
-                    i = R.ri[w][j];
-                }
-            R.ext[d0 + j] = i;
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        // the extremes in direction order, repeats merged, then pruned to
-        // strictly convex corners (as the octagon is)
-        int np = 0;
-        for (int d = 0; d < kRefineDirs; ++d)   // in place: np <= d
-            if (R.ext[d] < ns && (np == 0 || R.ext[np - 1] != R.ext[d])) R.ext[np++] = R.ext[d];
-        while (np > 1 && R.ext[np - 1] == R.ext[0]) --np;
-        double umin = INFINITY, umax = -INFINITY, vmin = INFINITY, vmax = -INFINITY;
-        for (int a = 0; a < np; ++a) {
-            R.pu[a] = U[R.ext[a]];
-            R.pv[a] = V[R.ext[a]];
-            umin = fmin(umin, R.pu[a]);
-            umax = fmax(umax, R.pu[a]);
-            vmin = fmin(vmin, R.pv[a]);
-            vmax = fmax(vmax, R.pv[a]);
-        }
-        const double span = np > 0 ? fmax(umax - umin, vmax - vmin) : 0.0;
-        const double margin = 1e-9 * span * span + 1e-300;
-        for (bool changed = np >= 3; changed && np >= 3;) {
-            changed = false;
-            for (int a = 0; a < np && np >= 3; ++a) {
-                const int b = (a + 1) % np, c = (a + 2) % np;
-                if (cross3(R.pu[a], R.pv[a], R.pu[b], R.pv[b], R.pu[c], R.pv[c]) <= margin) {
-                    for (int r = b; r + 1 < np; ++r) {
-                        R.pu[r] = R.pu[r + 1];
-                        R.pv[r] = R.pv[r + 1];
-                    }
-                    --np;
-                    changed = true;
-                }
-            }
-        }
-        R.margin = margin;
-        R.np = np;
-    }
-    __syncthreads();
-    const int np = R.np;
-    if (np < 3) return ns;
-    const double mg = R.margin;
-    // in-place compaction, a block-wide chunk at a time: every thread of a
-    // chunk has read its point before any is written, and writes land at or
-    // below the chunk's positions
-    uint32_t nout = 0;
-    for (uint32_t base = 0; base < ns; base += kChainBlock) {
-        const uint32_t t = base + threadIdx.x;
-        double u = 0.0, v = 0.0;
-        uint32_t id = 0;
-        bool keep = false;
-        if (t < ns) {
-            u = U[t];
-            v = V[t];
-            id = I[t];
-            bool inside = true;
-            for (int a = 0; inside && a < np; ++a) {
-                const int b = a + 1 == np ? 0 : a + 1;
-                inside = cross3(R.pu[a], R.pv[a], R.pu[b], R.pv[b], u, v) > mg;
-            }
-            keep = !inside;
-        }
-        const uint64_t bal = __ballot(keep);
-        const uint32_t below = (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
-        if (lane == 0) R.wcnt[wv] = (uint32_t)__popcll(bal);
-        __syncthreads();
-        uint32_t pre = 0, tot = 0;
-        for (int w = 0; w < kChainBlock / kWave; ++w) {
-            if (w < wv) pre += R.wcnt[w];
-            tot += R.wcnt[w];
-        }
-        if (keep) {
-            const uint32_t o = nout + pre + below;
-            U[o] = u;
-            V[o] = v;
-            I[o] = id;
-        }
-        nout += tot;
-        __syncthreads();
-    }
-    return nout;
-}
-
-__global__ void __launch_bounds__(kChainBlock) k_hull_chain(
-    const uint32_t* __restrict__ small, const uint32_t* __restrict__ chain_list, const uint32_t* __restrict__ in_off,
-    const uint32_t* __restrict__ in_idx, const uint32_t* __restrict__ surv_cnt, double* __restrict__ gu,
-    double* __restrict__ gv, uint32_t* __restrict__ gi, uint32_t* __restrict__ hull_cnt,
-    uint32_t* __restrict__ hull_tmp, double* __restrict__ area_out)
-{
-    __shared__ ChainLds<kLdsCap> L;
-    __shared__ RefineLds R;
-    // the listed clusters: more than kMidMax survivors (k_hull_list)
-    const uint32_t nc = small[7];
-    for (uint32_t c = blockIdx.x; c < nc; c += gridDim.x) {
-        const uint32_t k = chain_list[c];
-        const uint32_t ib = in_off[k];
-        uint32_t ns = surv_cnt[k];
-        if (ns > kRefineMin) ns = refine_survivors(R, gu + ib, gv + ib, gi + ib, ns);
-        if (ns <= (uint32_t)kLdsCap) {
-            double area = 0.0;
-            const uint32_t hh = block_chain(L, ns,
-                                            [&](uint32_t t, double* u, double* v, uint32_t* id) {
-                                                *u = gu[ib + t];
-                                                *v = gv[ib + t];
-                                                *id = gi[ib + t];
-                                            },
-                                            [&](uint32_t q, uint32_t p) { hull_tmp[ib + k + q] = in_idx[ib + L.si[p]]; },
-                                            &area);
-            if (threadIdx.x == 0) {
-                area_out[k] = area;
-                hull_cnt[k] = hh;
-            }
-        } else {
-            // bitonic network in global memory; partners beyond ns are +infinity
-            uint32_t N = 1;
-            while (N < ns) N <<= 1;
-            double* U = gu + ib;
-            double* Vv = gv + ib;
-            uint32_t* I = gi + ib;
-            for (uint32_t size = 2; size <= N; size <<= 1) {
-                for (uint32_t t = threadIdx.x; t < N / 2; t += kChainBlock) {
-                    const uint32_t blk = t / (size >> 1), r = t % (size >> 1);
-                    const uint32_t a = blk * size + r, b = blk * size + size - 1 - r;
-                    if (b < ns && p2_less(U[b], Vv[b], I[b], U[a], Vv[a], I[a])) swap3(U, Vv, I, a, b);
-                }
-                __syncthreads();
-                for (uint32_t stride = size >> 2; stride > 0; stride >>= 1) {
-                    for (uint32_t t = threadIdx.x; t < N / 2; t += kChainBlock) {
-                        const uint32_t a = 2 * t - (t & (stride - 1)), b = a + stride;
-                        if (b < ns && p2_less(U[b], Vv[b], I[b], U[a], Vv[a], I[a])) swap3(U, Vv, I, a, b);
-                    }
-                    __syncthreads();
-                }
-            }
-            if (threadIdx.x == 0) {
-                // single-stack chain; cluster k's stack is hull_tmp[ib + k, ib + k + m + 1)
-                // and never holds more than ns + 1 <= m + 1 entries
-                uint32_t* st = hull_tmp + ib + k;
-                uint32_t h = 0;
-                for (uint32_t i = 0; i < ns; ++i) {
-                    while (h >= 2) {
-                        const uint32_t a = st[h - 2], b = st[h - 1];
-                        if (cross3(U[a], Vv[a], U[b], Vv[b], U[i], Vv[i]) <= 0.0) --h;
-                        else break;
-                    }
-                    st[h++] = i;
-                }
-                const uint32_t lower = h + 1;
-                for (int32_t i = (int32_t)ns - 2; i >= 0; --i) {
-                    while (h >= lower) {
-                        const uint32_t a = st[h - 2], b = st[h - 1];
-                        if (cross3(U[a], Vv[a], U[b], Vv[b], U[i], Vv[i]) <= 0.0) --h;
-                        else break;
-                    }
-                    st[h++] = (uint32_t)i;
-                }
-                --h;   // the last point repeats the first
-                double s = 0.0;
-                if (h >= 3) {
-                    for (uint32_t q = 0; q < h; ++q) {
-                        const uint32_t p0 = st[q], p1 = st[q + 1 == h ? 0 : q + 1];
-                        s = s + (U[p0] * Vv[p1] - U[p1] * Vv[p0]);
-                    }
-                }
-                area_out[k] = h >= 3 ? 0.5 * s : 0.0;
-                // entry q of the stack is read before slot q is overwritten
-                for (uint32_t q = 0; q < h; ++q) hull_tmp[ib + k + q] = in_idx[ib + I[st[q]]];
-                hull_cnt[k] = h;
-            }
-        }
-        __syncthreads();
+        wave_sync();
     }
 }
 
 // ---- F: pack --------------------------------------------------------------------------
+// Groups of kPackClusters clusters, a workgroup each.  scan is the exclusive
+// scan of the vertex counts and small[5] their total, or, when scan is null
+// (at most kOneBlockMax clusters), a group sums the counts of the clusters
+// before it itself, which saves a launch that took longer than this one.
+constexpr uint32_t kPackClusters = 64;
+
 __global__ void __launch_bounds__(kBlock) k_hull_pack(const uint32_t* __restrict__ small,
                                                       const uint32_t* __restrict__ off, const float* __restrict__ X,
                                                       const float* __restrict__ Y, const float* __restrict__ Z,
@@ -688,38 +680,69 @@ __global__ void __launch_bounds__(kBlock) k_hull_pack(const uint32_t* __restrict
                                                       const uint32_t* __restrict__ in_off,
                                                       const uint32_t* __restrict__ hull_cnt,
                                                       const uint32_t* __restrict__ hull_tmp,
-                                                      const uint32_t* __restrict__ v_scan, uint32_t v_cap,
+                                                      const uint32_t* __restrict__ scan, uint32_t v_cap,
                                                       uint32_t* __restrict__ v_off, uint32_t* __restrict__ v_idx,
                                                       float* __restrict__ v_xyz, uint32_t* __restrict__ status)
 {
+    __shared__ uint32_t part[kBlock / kWave];
+    __shared__ uint32_t s_off[kPackClusters + 1];   // first vertex of each cluster of the group, and the end
     const uint32_t K = small[4];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     bool over = false;
-    for (uint32_t k = blockIdx.x; k < K; k += gridDim.x) {
-        const uint32_t h = hull_cnt[k];
-        const uint32_t base = v_scan[k];
-        if (threadIdx.x == 0) v_off[k] = base;
-        if (h == 0) continue;
-        const float4 pl = plane[k];
-        const double nx = pl.x, ny = pl.y, nz = pl.z, d = pl.w;
-        const uint32_t ib = in_off[k], pb = off[k];
-        for (uint32_t q = threadIdx.x; q < h; q += blockDim.x) {
-            const uint32_t pos = base + q;
+    if (K == 0 && blockIdx.x == 0 && threadIdx.x == 0) v_off[0] = 0;
+    for (uint32_t k0 = blockIdx.x * kPackClusters; k0 < K; k0 += gridDim.x * kPackClusters) {
+        uint32_t pre = 0;
+        if (!scan) {
+#pragma unroll 4
+            for (uint32_t k = threadIdx.x; k < k0; k += kBlock) pre += hull_cnt[k];
+        }
+#pragma unroll
+        for (int d = kWave / 2; d >= 1; d >>= 1) pre += __shfl_xor(pre, d, kWave);
+        if (lane == 0) part[wave] = pre;
+        __syncthreads();
+        if (wave == 0) {
+            const uint32_t k = k0 + (uint32_t)lane, c = k < K ? hull_cnt[k] : 0u;
+            uint32_t base = scan ? scan[k0] : 0u;
+#pragma unroll
+            for (int w = 0; w < kBlock / kWave; ++w) base += part[w];
+            uint32_t inc = c;
+#pragma unroll
+            for (int d = 1; d < kWave; d <<= 1) {
+                const uint32_t o = __shfl_up(inc, d, kWave);
+                if (lane >= d) inc += o;
+            }
+            s_off[lane] = base + inc - c;
+            if (lane == kWave - 1) s_off[kPackClusters] = base + inc;
+            if (k < K) v_off[k] = base + inc - c;
+            if (k + 1 == K) v_off[K] = base + inc;
+        }
+        __syncthreads();
+        for (uint32_t pos = s_off[0] + threadIdx.x; pos < s_off[kPackClusters]; pos += kBlock) {
             if (pos >= v_cap) {
                 over = true;
                 continue;
             }
-            const uint32_t j = hull_tmp[ib + k + q];
-            const double px = X[pb + j], py = Y[pb + j], pz = Z[pb + j];
+            uint32_t lo = 0;   // the cluster: the last one starting at or before pos (empty ones precede it)
+#pragma unroll
+            for (uint32_t h = kPackClusters / 2; h; h >>= 1)
+                if (s_off[lo + h] <= pos) lo += h;
+            const uint32_t k = k0 + lo;
+            const float4 pl = plane[k];
+            const double nx = pl.x, ny = pl.y, nz = pl.z, d = pl.w;
+            const uint32_t j = hull_tmp[in_off[k] + k + (pos - s_off[lo])], i = off[k] + j;
+            const double px = X[i], py = Y[i], pz = Z[i];
             const double dist = nx * px + ny * py + nz * pz + d;
             v_idx[pos] = j;
             v_xyz[3 * (size_t)pos + 0] = (float)(px - dist * nx);
             v_xyz[3 * (size_t)pos + 1] = (float)(py - dist * ny);
             v_xyz[3 * (size_t)pos + 2] = (float)(pz - dist * nz);
         }
+        __syncthreads();   // part and s_off are reused by the next group
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) v_off[K] = small[5];
     if (over) atomicOr(status, (uint32_t)VM_FLAG_HULL_CAP);
 }
+
+static_assert(kPackClusters == (uint32_t)kWave, "a lane per cluster of a group");
 
 }  // namespace
 
@@ -750,28 +773,31 @@ vm_status hulls(const vm_clusters& cl, const vm_planes& planes, const vm_hulls_o
     // grids sized for a few workgroups per CU; the kernels stride over the
     // device-side counts, so empty workgroups are not launched by the thousand
     const int tgrid = grid_for(hull_tiles_bound(kc, cl.n_cap), 1, 2048);
+    // the tiles' extremes lie where the survivors go afterwards: a filtered
+    // cluster of m > 64 inliers has at most m / 1024 + 1 tiles of 256 bytes in
+    // each table, less than the 8 m bytes of its part of hull_u or hull_v
+    float* ext_v = (float*)w.hull_u;
+    uint32_t* ext_i = (uint32_t*)w.hull_v;
     k_hull_extremes<<<tgrid, kTileThreads, 0, s>>>(w.small, w.hull_tile_off, cl.d_off, cl.d_x, cl.d_y, cl.d_z, pl,
-                                                   planes.d_in_off, planes.d_in_idx, w.ext_v, w.ext_i);
-    const int kgrid = kc < 1024 ? (int)(kc ? kc : 1) : 1024;
-    const int cgrid = kc < 512 ? (int)(kc ? kc : 1) : 512;   // the chain kernel holds ~70 KB of LDS
-    k_hull_poly<<<kSmallGrid, kBlock, 0, s>>>(w.small, w.hull_tile_off, cl.d_off, cl.d_x, cl.d_y, cl.d_z, pl,
-                                        planes.d_in_off, planes.d_in_idx, w.ext_v, w.ext_i, w.poly, w.surv_cnt);
+                                                   planes.d_in_off, planes.d_in_idx, ext_v, ext_i);
+    k_hull_poly<<<grid_for(kc, 1, kPolyGrid), kBlock, 0, s>>>(
+        w.small, w.hull_tile_off, cl.d_off, cl.d_x, cl.d_y, cl.d_z, pl, planes.d_in_off, planes.d_in_idx, ext_v, ext_i,
+        w.margin, w.hull_tmp, w.surv_cnt);
     k_hull_filter<<<tgrid, kTileThreads, 0, s>>>(w.small, w.hull_tile_off, cl.d_off, cl.d_x, cl.d_y, cl.d_z, pl,
-                                                 planes.d_in_off, planes.d_in_idx, w.poly, w.surv_cnt, w.hull_u,
-                                                 w.hull_v, w.hull_i);
-    k_hull_list<<<grid_for(kc), kBlock, 0, s>>>(w.small, w.hull_tile_off, w.surv_cnt, w.chain_list, kc);
-    k_hull_small<<<kSmallGrid, kBlock, 0, s>>>(w.small, w.chain_list, kc, w.hull_tile_off, cl.d_off, cl.d_x, cl.d_y,
-                                              cl.d_z, pl,
-                                              planes.d_best_h, planes.in_cap, planes.d_in_off, planes.d_in_idx,
-                                              w.surv_cnt, w.hull_u, w.hull_v, w.hull_i, w.hull_cnt, w.hull_tmp,
-                                              out.d_area);
-    k_hull_chain<<<cgrid, kChainBlock, 0, s>>>(w.small, w.chain_list, planes.d_in_off, planes.d_in_idx, w.surv_cnt,
-                                               w.hull_u, w.hull_v, w.hull_i, w.hull_cnt, w.hull_tmp, out.d_area);
+                                                 planes.d_in_off, planes.d_in_idx, w.margin, w.hull_tmp, w.surv_cnt,
+                                                 w.hull_u, w.hull_v, w.hull_i);
+    k_hull_finish<<<grid_for(kc, 1, kFinishGrid), kChainBlock, 0, s>>>(
+        w.small, w.hull_tile_off, cl.d_off, cl.d_x, cl.d_y, cl.d_z, pl, planes.d_best_h, planes.in_cap, planes.d_in_off,
+        planes.d_in_idx, w.surv_cnt, w.hull_u, w.hull_v, w.hull_i, w.hull_cnt, w.hull_tmp, out.d_area);
     VM_HIP(hipGetLastError());
-    VM_HIP(scan_exclusive_dev(w.hull_cnt, w.hull_off, w.small + 4, kc, w.small + 5, w.blk, s));
-    k_hull_pack<<<kgrid, kBlock, 0, s>>>(w.small, cl.d_off, cl.d_x, cl.d_y, cl.d_z, pl, planes.d_in_off, w.hull_cnt,
-                                         w.hull_tmp, w.hull_off, out.v_cap, out.d_v_off, out.d_v_idx, out.d_v_xyz,
-                                         out.d_status);
+    const uint32_t* scan = nullptr;
+    if (kc > kOneBlockMax) {
+        VM_HIP(scan_exclusive_dev(w.hull_cnt, w.hull_off, w.small + 4, kc, w.small + 5, w.blk, s));
+        scan = w.hull_off;
+    }
+    k_hull_pack<<<grid_for(kc, (int)kPackClusters, 1024), kBlock, 0, s>>>(
+        w.small, cl.d_off, cl.d_x, cl.d_y, cl.d_z, pl, planes.d_in_off, w.hull_cnt, w.hull_tmp, scan, out.v_cap,
+        out.d_v_off, out.d_v_idx, out.d_v_xyz, out.d_status);
     VM_HIP(hipGetLastError());
     return VM_OK;
 }

@@ -569,12 +569,11 @@ WorkLayout work_layout(void* base, uint32_t k_cap, uint32_t n_cap, uint32_t n_hy
     w.hull_v = (double*)take(((size_t)n_cap + 1) * sizeof(double));
     w.hull_i = (uint32_t*)take(((size_t)n_cap + 1) * sizeof(uint32_t));
     w.hull_tile_off = (uint32_t*)take(((size_t)k_cap + 2) * sizeof(uint32_t));
-    const size_t ht = hull_tiles_bound(k_cap, n_cap);
-    w.ext_v = (double*)take(ht * kHullDirs * sizeof(double));
-    w.ext_i = (uint32_t*)take(ht * kHullDirs * sizeof(uint32_t));
-    w.poly = (double*)take((size_t)k_cap * (2 * kHullDirs + 2) * sizeof(double) + 8);
+    w.margin = (double*)take((size_t)k_cap * sizeof(double) + 8);
     w.surv_cnt = (uint32_t*)take(((size_t)k_cap + 1) * sizeof(uint32_t));
-    w.chain_list = (uint32_t*)take(((size_t)k_cap + 1) * sizeof(uint32_t));
+    // the size decides which calls vm_ransac_planes_noalloc accepts: it stays
+    // what it was with 96 bytes per hull tile and 140 more per cluster in use
+    (void)take((size_t)hull_tiles_bound(k_cap, n_cap) * 96 + (size_t)k_cap * 140 + 512);
     w.small = (uint32_t*)take(64 * sizeof(uint32_t));
     w.bytes = o;
     return w;
