@@ -28,6 +28,7 @@ namespace {
 using namespace dev;
 
 constexpr int kCountBlock = 256;
+constexpr int kInlierBlock = 512;   // of k_inlier_count
 constexpr int kPtsPerLane = 16;
 constexpr int kTile = (int)kPointTile;             // points per tile
 constexpr uint32_t kXcds = 8;                      // accelerator complex dies (separate L2s)
@@ -416,10 +417,25 @@ __global__ void __launch_bounds__(kBlock) k_select_rows(const uint32_t* __restri
 }
 
 // (c) the inlier lists of the winning planes, over the same point tiles, in
-// three launches: inliers per tile; one workgroup's scan of the tile counts
-// (which also gives each cluster's list offset); the lists, each workgroup
-// placing its tile's inliers in point order with a block scan.
-__global__ void __launch_bounds__(kCountBlock) k_inlier_count(const uint32_t* __restrict__ small,
+// three launches: the inliers of each tile, as a bit mask and their number;
+// one workgroup's scan of the tile counts (which also gives each cluster's
+// list offset); the lists, written from the masks.  The first reads every
+// point (bound by that: 118 us for the 48M points of 2000 clusters, 4.9 TB/s),
+// the last reads a bit per point and consecutive lanes write consecutive
+// places (testing the points again, with a thread writing out 32 points in
+// turn, took 364 us there, this 46 us).  512 threads leave a thread eight
+// points in the first (81 tiles: 4.9 us, 6.5 us with 256; clusters of a few
+// points: 5.2 us, 8.6 us with 1024); the last has little to wait for (2000
+// clusters: 46 us with 256, 55 with 512).
+// the mask words of tile t, whose first point is p0: tiles start at distinct
+// words that do not overlap, whatever their sizes (a tile of n points needs
+// n / 32 rounded up, at most one more than the quotient)
+__device__ __forceinline__ uint32_t* tile_mask(uint32_t* mask, uint32_t p0, uint32_t t)
+{
+    return mask + (p0 / 32 + t);
+}
+
+__global__ void __launch_bounds__(kInlierBlock) k_inlier_count(const uint32_t* __restrict__ small,
                                                               const uint32_t* __restrict__ tile_off,
                                                               const uint32_t* __restrict__ tile_k,
                                                               const uint32_t* __restrict__ off,
@@ -427,28 +443,36 @@ __global__ void __launch_bounds__(kCountBlock) k_inlier_count(const uint32_t* __
                                                               const float* __restrict__ Z, float eps,
                                                               const int32_t* __restrict__ best,
                                                               const float4* __restrict__ plane,
+                                                              uint32_t* __restrict__ mask,
                                                               uint32_t* __restrict__ tile_cnt)
 {
-    __shared__ uint32_t wsum[kCountBlock / kWave];
+    __shared__ uint32_t wsum[kInlierBlock / kWave];
     const uint32_t T = small[1];
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     for (uint32_t t = blockIdx.x; t < T; t += gridDim.x) {
         const uint32_t k = tile_k[t];
         const uint32_t p0 = off[k] + (t - tile_off[k]) * kTile;
-        const uint32_t pend = min(p0 + kTile, off[k + 1]);
+        const uint32_t n = min(kTile, off[k + 1] - p0);
         uint32_t c = 0;
         if (best[k] >= 0) {
             const float4 pl = plane[k];
-            for (uint32_t i = p0 + threadIdx.x; i < pend; i += kCountBlock) c += inlier_test(pl, X[i], Y[i], Z[i], eps);
+            uint32_t* m = tile_mask(mask, p0, t);
+#pragma unroll 4
+            for (uint32_t j0 = wave * kWave; j0 < n; j0 += kInlierBlock) {
+                const uint32_t j = j0 + (uint32_t)lane, i = p0 + min(j, n - 1u);
+                const bool in = j < n && inlier_test(pl, X[i], Y[i], Z[i], eps);
+                const uint64_t b = __ballot(in);
+                c += (uint32_t)__popcll(b);
+                if (lane < 2 && j0 + 32 * lane < n) m[j0 / 32 + lane] = lane ? (uint32_t)(b >> 32) : (uint32_t)b;
+            }
         }
-#pragma unroll
-        for (int d = kWave / 2; d >= 1; d >>= 1) c += __shfl_xor(c, d, kWave);
         if (lane == 0) wsum[wave] = c;
         __syncthreads();
         if (threadIdx.x == 0) {
             uint32_t tot = 0;
 #pragma unroll
-            for (int w = 0; w < kCountBlock / kWave; ++w) tot += wsum[w];
+            for (int w = 0; w < kInlierBlock / kWave; ++w) tot += wsum[w];
             tile_cnt[t] = tot;
         }
         __syncthreads();   // wsum is reused by the next tile
@@ -477,62 +501,50 @@ __global__ void __launch_bounds__(kCountBlock) k_inlier_write(const uint32_t* __
                                                               const uint32_t* __restrict__ tile_off,
                                                               const uint32_t* __restrict__ tile_k,
                                                               const uint32_t* __restrict__ off,
-                                                              const float* __restrict__ X, const float* __restrict__ Y,
-                                                              const float* __restrict__ Z, float eps,
                                                               const int32_t* __restrict__ best,
-                                                              const float4* __restrict__ plane,
+                                                              uint32_t* __restrict__ mask,
                                                               const uint32_t* __restrict__ tile_pre, uint32_t in_cap,
                                                               uint32_t* __restrict__ in_idx, uint32_t* __restrict__ status)
 {
-    // The tile's tests are made with coalesced loads (consecutive lanes,
-    // consecutive points) and collected as a bit mask in LDS, 64 bits per
-    // wave step by a ballot; then thread w takes mask word w (32 points), a
-    // block scan of the words' counts places their inliers in point order.
+    // a point's place: the tile's prefix, the inliers in the mask words before
+    // its own, and those below it in the word
     constexpr uint32_t kWords = kTile / 32;   // 128
-    static_assert(kWords <= kCountBlock, "a thread per mask word");
-    __shared__ uint32_t mask[kWords];
-    __shared__ uint32_t wsum[kCountBlock / kWave];
+    static_assert(kWords == 2 * kWave && kWords <= kCountBlock, "two waves scan the words");
+    __shared__ uint32_t sm[kWords], pre[kWords];
+    __shared__ uint32_t half;
     const uint32_t T = small[1];
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int lane = threadIdx.x & (kWave - 1);
     bool over = false;
     for (uint32_t t = blockIdx.x; t < T; t += gridDim.x) {
         const uint32_t k = tile_k[t];
         if (best[k] < 0) continue;   // workgroup-uniform
         const uint32_t base = off[k];
         const uint32_t p0 = base + (t - tile_off[k]) * kTile;
-        const uint32_t pend = min(p0 + kTile, off[k + 1]);
-        const float4 pl = plane[k];
-#pragma unroll 4
-        for (uint32_t j0 = 0; j0 < kTile; j0 += kCountBlock) {
-            const uint32_t i = p0 + j0 + threadIdx.x;
-            const bool in = i < pend && inlier_test(pl, X[i], Y[i], Z[i], eps);
-            const uint64_t b = __ballot(in);
-            if (lane == 0) {
-                const uint32_t w = (j0 + (uint32_t)wave * kWave) / 32;
-                mask[w] = (uint32_t)b;
-                mask[w + 1] = (uint32_t)(b >> 32);
+        const uint32_t n = min(kTile, off[k + 1] - p0);
+        if (threadIdx.x < kWords) {
+            const uint32_t m = threadIdx.x * 32 < n ? tile_mask(mask, p0, t)[threadIdx.x] : 0u;
+            const uint32_t c = (uint32_t)__popc(m);
+            uint32_t inc = c;
+#pragma unroll
+            for (int d = 1; d < kWave; d <<= 1) {
+                const uint32_t o = __shfl_up(inc, d, kWave);
+                if (lane >= d) inc += o;
             }
+            sm[threadIdx.x] = m;
+            pre[threadIdx.x] = inc - c;
+            if (threadIdx.x == kWave - 1) half = inc;
         }
         __syncthreads();
-        uint32_t m = threadIdx.x < kWords ? mask[threadIdx.x] : 0u;
-        const uint32_t c = (uint32_t)__popc(m);
-        uint32_t inc = c;
-#pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) {
-            const uint32_t o = __shfl_up(inc, d, kWave);
-            if (lane >= d) inc += o;
-        }
-        if (lane == kWave - 1) wsum[wave] = inc;
-        __syncthreads();
-        uint32_t p = tile_pre[t] + inc - c;
-#pragma unroll
-        for (int w = 0; w < kCountBlock / kWave; ++w) p += (w < wave) ? wsum[w] : 0u;
-        const uint32_t q0 = p0 + threadIdx.x * 32 - base;   // cluster-local index of the word's first point
-        for (; m; m &= m - 1, ++p) {
-            if (p < in_cap) in_idx[p] = q0 + (uint32_t)(__ffs(m) - 1);
+        const uint32_t first = tile_pre[t];
+#pragma unroll 4
+        for (uint32_t j = threadIdx.x; j < n; j += kCountBlock) {
+            const uint32_t w = j / 32, m = sm[w], bit = 1u << (j & 31);
+            if (!(m & bit)) continue;
+            const uint32_t p = first + pre[w] + (w >= (uint32_t)kWave ? half : 0u) + (uint32_t)__popc(m & (bit - 1u));
+            if (p < in_cap) in_idx[p] = p0 - base + j;
             else over = true;
         }
-        __syncthreads();   // mask and wsum are reused by the next tile
+        __syncthreads();   // the words are reused by the next tile
     }
     if (over) atomicOr(status, (uint32_t)VM_FLAG_INLIERS_CAP);
 }
@@ -639,13 +651,15 @@ vm_status select_and_list(const vm_clusters& cl, const vm_ransac_params& p, cons
                                                                    out.d_best_h, out.d_n_inliers, out.d_counts,
                                                                    (float4*)out.d_hyp);
     const int tgrid = grid_for((uint64_t)cl.n_cap / kTile + kc + 1, 1, 8192);   // most tiles are small: many workgroups
-    // w.flags holds the per-tile counts, then their prefixes (tiles <= points)
-    k_inlier_count<<<tgrid, kCountBlock, 0, s>>>(w.small, w.tile_off, w.tile_k, cl.d_off, cl.d_x, cl.d_y, cl.d_z,
-                                                 p.eps, out.d_best_h, (const float4*)out.d_plane, w.flags);
+    // w.flags holds the per-tile counts, then their prefixes (tiles <= points);
+    // the mask takes at most n_cap / 32 + tiles + 1 words of what the polygons
+    // use later (2 n_cap + 2 words, tiles <= points)
+    uint32_t* mask = (uint32_t*)w.hull_u;
+    k_inlier_count<<<tgrid, kInlierBlock, 0, s>>>(w.small, w.tile_off, w.tile_k, cl.d_off, cl.d_x, cl.d_y, cl.d_z,
+                                                p.eps, out.d_best_h, (const float4*)out.d_plane, mask, w.flags);
     k_inlier_scan<<<1, kOneBlockThreads, 0, s>>>(w.small, w.tile_off, w.flags, out.d_in_off);
-    k_inlier_write<<<tgrid, kCountBlock, 0, s>>>(w.small, w.tile_off, w.tile_k, cl.d_off, cl.d_x, cl.d_y, cl.d_z, p.eps,
-                                                 out.d_best_h, (const float4*)out.d_plane, w.flags, out.in_cap,
-                                                 out.d_in_idx, out.d_status);
+    k_inlier_write<<<tgrid, kCountBlock, 0, s>>>(w.small, w.tile_off, w.tile_k, cl.d_off, out.d_best_h, mask, w.flags,
+                                                out.in_cap, out.d_in_idx, out.d_status);
     VM_HIP(hipGetLastError());
     return VM_OK;
 }
