@@ -306,8 +306,6 @@ vm_status vm_map_create(const vm_map_desc* d, vm_map* out)
     // scan partials; also the fused scans' per-tile totals (3 words per 1024 items)
     A((void**)&b.blk, std::max<size_t>(scan_blk_words(scan_n), 3 * (size_t)ts_tiles(scan_n)) * 4);
     A((void**)&b.hist, radix_hist_words(cap) * 4);
-    A((void**)&b.pairs, ccl_tiles(m->g) * kCclTilePairs * 8);
-    A((void**)&b.npair, ccl_tiles(m->g) * 4);
     InsertScratch& ins = m->ins;
     ins.cap = batch;
     A((void**)&ins.key, (size_t)batch * 4);

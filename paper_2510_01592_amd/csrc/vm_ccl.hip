@@ -9,10 +9,9 @@
 //   * init:    every voxel points at the start of its run along x (runs of
 //              consecutive occupied cells share a component trivially);
 //   * merge:   runs in the four neighbouring rows with smaller keys
-//              (dz = -1, any dy; dz = 0, dy = -1) are hooked together; a
-//              voxel only hooks where an overlap between its run and a run of
-//              the other row begins, plus the diagonal end cells, so each
-//              pair of touching runs is hooked about once;
+//              (dz = -1, any dy; dz = 0, dy = -1) are united, each pair of
+//              touching runs once: inside tiles in LDS, then across their
+//              faces;
 //   * flatten: every voxel takes its root.
 // Hooks always put the larger root under the smaller one with a CAS on the
 // root, so every root ends as the minimum of its tree and the labels are
@@ -44,43 +43,33 @@ __device__ __forceinline__ void st_parent(uint32_t* p, uint32_t v)
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ __forceinline__ bool occ(const uint32_t* __restrict__ bits, uint32_t key)
+// a moves to the root of its set and b to the root of its own, with path
+// halving (each visited node is re-pointed at its grandparent; concurrent
+// writes only ever store an ancestor); a step of one and a step of the other
+// wait for memory together
+__device__ __forceinline__ void uf_roots(uint32_t* parent, uint32_t& a, uint32_t& b)
 {
-    return (bits[key >> 5] >> (key & 31)) & 1u;
-}
-
-__device__ __forceinline__ uint32_t rank_of(const uint32_t* __restrict__ bits, const uint32_t* __restrict__ wrank,
-                                            uint32_t key)
-{
-    const uint32_t b = key & 31;
-    return wrank[key >> 5] + __popc(bits[key >> 5] & ((1u << b) - 1u));
-}
-
-// Root of x with path halving (each visited node is re-pointed at its
-// grandparent; concurrent writes only ever store an ancestor).
-__device__ __forceinline__ uint32_t uf_find(uint32_t* parent, uint32_t x)
-{
-    uint32_t p = ld_parent(&parent[x]);
-    while (p != x) {
-        const uint32_t g = ld_parent(&parent[p]);
-        if (g == p) return p;
-        st_parent(&parent[x], g);
-        x = g;
-        p = ld_parent(&parent[x]);
+    while (a != b) {
+        const uint32_t pa = ld_parent(&parent[a]), pb = ld_parent(&parent[b]);
+        const uint32_t ga = ld_parent(&parent[pa]), gb = ld_parent(&parent[pb]);
+        const bool ra = ga == pa, rb = gb == pb;   // pa (pb) is a root
+        if (!ra) st_parent(&parent[a], ga);
+        if (!rb) st_parent(&parent[b], gb);
+        a = ga;
+        b = gb;
+        if (ra && rb) return;
     }
-    return x;
 }
 
 __device__ __forceinline__ void uf_unite(uint32_t* parent, uint32_t a, uint32_t b)
 {
-    a = uf_find(parent, a);
-    b = uf_find(parent, b);
+    uf_roots(parent, a, b);
     while (a != b) {
         if (a < b) { const uint32_t t = a; a = b; b = t; }
         const uint32_t old = atomicCAS(&parent[a], a, b);   // hook root a under b
         if (old == a) return;
-        a = uf_find(parent, old);
-        b = uf_find(parent, b);
+        a = old;
+        uf_roots(parent, a, b);
     }
 }
 
@@ -105,6 +94,7 @@ constexpr int kTileRows = kTY * kTZ;          // 256 = threads per workgroup
 constexpr int kRowRuns = kTX / 2;             // runs per row at most
 constexpr int kTileRuns = kTileRows * kRowRuns;   // 4096
 static_assert(kTileRows == kBlock, "one thread per tile row");
+constexpr int kJumps = 16;   // steps towards the root before the unions, a walk's first ones
 
 struct TileGrid {
     uint32_t ntx, nty, ntz;
@@ -150,8 +140,6 @@ __device__ __forceinline__ uint32_t row_bits(const uint32_t* __restrict__ bits, 
     return v;
 }
 
-__device__ __forceinline__ bool bit_at(uint32_t w, int x) { return x >= 0 && x < 32 && ((w >> x) & 1u); }
-
 // first cells of the runs of w, and last cells
 __device__ __forceinline__ uint32_t run_starts(uint32_t w) { return w & ~(w << 1); }
 __device__ __forceinline__ uint32_t run_ends(uint32_t w) { return w & ~(w >> 1); }
@@ -164,29 +152,12 @@ __device__ __forceinline__ uint32_t seg_rank0(const uint32_t* __restrict__ bits,
 }
 
 // Hooks between the runs of row segment v and those of an adjacent row
-// segment w (same x range): f(xa, xb) is called for a cell xa of v and an
-// adjacent occupied cell xb of w so that every pair of 26-adjacent runs gets
-// at least one call.  Two runs touch iff their x ranges, one widened by a
-// cell on each side, overlap: an overlap begins where the run of v or the
-// run of w starts (first test); a purely diagonal touch is the start of one
-// run against the end of the other (second and third tests).  Only run
-// starts and ends of v and run starts of w can fire.
-template <class F>
-__device__ __forceinline__ void hook_segments(uint32_t v, uint32_t w, F&& f)
-{
-    const uint32_t sv = run_starts(v), ev = run_ends(v);
-    for (uint32_t m = v & (sv | ev | run_starts(w)); m; m &= m - 1) {
-        const int xl = __ffs(m) - 1;
-        const bool st = (sv >> xl) & 1u, en = (ev >> xl) & 1u;
-        if (bit_at(w, xl) && (st || !bit_at(w, xl - 1))) f(xl, xl);
-        if (st && bit_at(w, xl - 1)) f(xl, xl - 1);
-        if (en && bit_at(w, xl + 1)) f(xl, xl + 1);
-    }
-}
-
-// The calls hook_segments(v, w, f) makes, as masks of the cells xl of v:
-// f(xl, xl) for the bits of a, f(xl, xl - 1) for those of b and
-// f(xl, xl + 1) for those of c.
+// segment w (same x range), as masks of the cells xl of v: with cell xl of w
+// for the bits of a, with xl - 1 for those of b and with xl + 1 for those of
+// c.  Two runs touch iff their x ranges, one widened by a cell on each side,
+// overlap: an overlap begins where the run of v or the run of w starts (a);
+// a purely diagonal touch is the start of one run against the end of the
+// other (b and c).
 struct HookMasks {
     uint32_t a, b, c;
 };
@@ -215,17 +186,20 @@ __device__ __forceinline__ void lds_st(uint32_t* p, uint32_t v)
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-__device__ __forceinline__ uint32_t lds_find(uint32_t* par, uint32_t x)
+// a moves to the root of its set and b to the root of its own, a step of each
+// at a time, so that the two walks wait for LDS together
+__device__ __forceinline__ void lds_roots(uint32_t* par, uint32_t& a, uint32_t& b)
 {
-    uint32_t p = lds_ld(&par[x]);
-    while (p != x) {
-        const uint32_t g = lds_ld(&par[p]);
-        if (g == p) return p;
-        lds_st(&par[x], g);
-        x = g;
-        p = lds_ld(&par[x]);
+    while (a != b) {
+        const uint32_t pa = lds_ld(&par[a]), pb = lds_ld(&par[b]);
+        const uint32_t ga = lds_ld(&par[pa]), gb = lds_ld(&par[pb]);
+        const bool ra = ga == pa, rb = gb == pb;   // pa (pb) is a root
+        if (!ra) lds_st(&par[a], ga);
+        if (!rb) lds_st(&par[b], gb);
+        a = ga;
+        b = gb;
+        if (ra && rb) return;
     }
-    return x;
 }
 
 // Root of x without writing anything on the way, for when the unions are
@@ -242,23 +216,18 @@ __device__ __forceinline__ uint32_t lds_root(const uint32_t* par, uint32_t x)
     return x;
 }
 
-__device__ __forceinline__ void lds_unite(uint32_t* par, uint32_t a, uint32_t b)
+// unites the sets of a and b; returns a node above both
+__device__ __forceinline__ uint32_t lds_unite(uint32_t* par, uint32_t a, uint32_t b)
 {
-    a = lds_find(par, a);
-    b = lds_find(par, b);
+    lds_roots(par, a, b);
     while (a != b) {
         if (a < b) { const uint32_t t = a; a = b; b = t; }
         const uint32_t old = atomicCAS(&par[a], a, b);
-        if (old == a) return;
-        a = lds_find(par, old);
-        b = lds_find(par, b);
+        if (old == a) return b;
+        a = old;
+        lds_roots(par, a, b);
     }
-}
-
-// first cell of the run of w that contains cell x (x must be occupied)
-__device__ __forceinline__ uint32_t run_start_of(uint32_t starts, int x)
-{
-    return 31u - __clz(starts & ((2u << x) - 1u));   // x = 31: (2u << 31) - 1 wraps to all ones
+    return a;
 }
 
 // ordinal of that run in its row (runs counted from x = 0)
@@ -267,40 +236,28 @@ __device__ __forceinline__ uint32_t run_ordinal(uint32_t starts, int x)
     return (uint32_t)__popc(starts & ((2u << x) - 1u)) - 1u;
 }
 
-// cell of the n-th (0-based) set bit of w (w has more than n set bits):
-// a branch-free binary search over popcounts of halves
-__device__ __forceinline__ uint32_t nth_set_bit(uint32_t w, uint32_t n)
-{
-    uint32_t pos = 0;
-#pragma unroll
-    for (uint32_t h = 16; h; h >>= 1) {
-        const uint32_t c = (uint32_t)__popc(w & ((1u << h) - 1u));
-        const bool up = n >= c;
-        n -= up ? c : 0u;
-        w >>= up ? h : 0u;
-        pos += up ? h : 0u;
-    }
-    return pos;
-}
-
-// Hook pairs buffered per tile (more are united in further rounds).  With
-// the run table the workgroup holds about 22 KB of LDS, so that seven
-// workgroups share a compute unit.
-constexpr uint32_t kPairCap = 768;
-
+// The workgroup's runs are numbered through (a row's first number is its
+// prefix), so that each step below gives every thread as many runs as any
+// other, however the runs lie.  A run first takes one run it touches as its
+// parent, with a plain store (only its own entry, a smaller number); pointers
+// are then jumped, after which most of the other touching pairs already have
+// one root and take two reads and no CAS.  (With rows as the unit, their pairs
+// listed and each united from scratch, the longest row and the longest chain
+// of a wave set the pace: a map of 916k voxels took 38 us and takes 26,
+// one of 29k, with a tile per compute unit, 30 and 13.)
 __global__ void __launch_bounds__(kBlock) k_ccl_tile(const uint32_t* __restrict__ bits, uint32_t nwords,
                                                      const uint32_t* __restrict__ wrank, Dims d, TileGrid tg,
                                                      uint32_t* __restrict__ parent, uint32_t* __restrict__ csize)
 {
     __shared__ uint32_t rowv[kTileRows];
     __shared__ uint32_t rowrank[kTileRows];
+    __shared__ uint16_t rowbase[kTileRows];
+    __shared__ uint16_t info[kTileRuns];   // a run's row and first cell: 32 row + x
     __shared__ uint32_t par[kTileRuns];
-    __shared__ uint32_t pairs[kPairCap];
     __shared__ uint32_t wtot[kBlock / kWave];
     const uint32_t j = threadIdx.x;
     const int lane = (int)(j & (kWave - 1)), wave = (int)(j / kWave);
     const int yl = (int)(j % kTY), zl = (int)(j / kTY);
-    const uint32_t ntiles = tg.ntx * tg.nty * tg.ntz;
     // tiles in the XCD-ordered walk of the face kernel: a row of tiles along
     // x shares its bitmap and rank lines in one L2 (7 % faster than the
     // launch order once the per-run count atomics were gone; with them, the
@@ -313,37 +270,10 @@ __global__ void __launch_bounds__(kBlock) k_ccl_tile(const uint32_t* __restrict_
         const uint32_t x0 = tx * kTX, y = ty * kTY + yl, z = tz * kTZ + zl;
         uint32_t key0;
         const uint32_t v = row_bits(bits, nwords, d, x0, y, z, &key0);
-        const uint32_t sv = run_starts(v), ev = run_ends(v);
-        rowv[j] = v;
         // (unconditional, so that its loads overlap those of the row; rows
         // outside the grid read key 0, and empty rows' ranks are never used)
-        rowrank[j] = seg_rank0(bits, wrank, key0);
-        // one union-find node per run
-        {
-            uint32_t c = j * kRowRuns;
-            for (uint32_t m = sv; m; m &= m - 1, ++c) par[c] = c;
-        }
-        // barrier + vote: a tile without occupied cells is skipped by all threads
-        if (!__syncthreads_or(v != 0u)) continue;
-        // hooks between the runs of the (up to) four neighbouring rows with
-        // smaller keys.  Each thread counts its row's hooks from bit masks,
-        // a block scan places them in the pair list (plain LDS stores), and
-        // all threads then unite the list, so that rows with many hooks do
-        // not hold up their wave.  More hooks than the list holds are taken
-        // in rounds of kPairCap.
-        HookMasks hm[4];
-        uint32_t nrow[4];
-        uint32_t cnt = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int dy = (q == 0) ? -1 : (q - 2);
-            const int dz = (q == 0) ? 0 : -1;
-            const int ny2 = yl + dy, nz2 = zl + dz;
-            const bool in = v && ny2 >= 0 && ny2 < kTY && nz2 >= 0;
-            nrow[q] = in ? (uint32_t)(ny2 + kTY * nz2) : 0u;
-            hm[q] = hook_masks(in ? v : 0u, in ? rowv[nrow[q]] : 0u);
-            cnt += (uint32_t)(__popc(hm[q].a) + __popc(hm[q].b) + __popc(hm[q].c));
-        }
+        const uint32_t rank0 = seg_rank0(bits, wrank, key0);
+        const uint32_t sv = run_starts(v), cnt = (uint32_t)__popc(sv);
         uint32_t inc = cnt;
 #pragma unroll
         for (int dd = 1; dd < kWave; dd <<= 1) {
@@ -351,76 +281,94 @@ __global__ void __launch_bounds__(kBlock) k_ccl_tile(const uint32_t* __restrict_
             if (lane >= dd) inc += o;
         }
         if (lane == kWave - 1) wtot[wave] = inc;
+        rowv[j] = v;
+        rowrank[j] = rank0;
         __syncthreads();
-        uint32_t slot = inc - cnt, npairs = 0;
+        uint32_t c0 = inc - cnt, nruns = 0;
 #pragma unroll
         for (int w2 = 0; w2 < kBlock / kWave; ++w2) {
             const uint32_t t2 = wtot[w2];
-            slot += (w2 < wave) ? t2 : 0u;
-            npairs += t2;
+            c0 += (w2 < wave) ? t2 : 0u;
+            nruns += t2;
         }
-        for (uint32_t r0 = 0; r0 < npairs; r0 += kPairCap) {   // npairs is block-uniform
-            if (cnt && slot < r0 + kPairCap && slot + cnt > r0) {
-                uint32_t sl = slot;
+        rowbase[j] = (uint16_t)c0;
+        for (uint32_t m = sv; m; m &= m - 1, ++c0) info[c0] = (uint16_t)(32u * j + (uint32_t)__ffs(m) - 1u);
+        __syncthreads();
+        if (nruns == 0) continue;   // (block-uniform; the next write to LDS follows no read here)
+
+        // f(number) for the runs that run c touches in the neighbouring rows
+        // with smaller keys, until it returns false
+        const auto touching = [&](uint32_t c, auto f) {
+            const uint32_t in = info[c], row = in / 32u, s0 = in & 31u;
+            const uint32_t e0 = (uint32_t)__ffs(run_ends(rowv[row]) >> s0) - 1u + s0;
+            const uint32_t win = (~0u >> (31u - min(e0 + 1u, 31u))) & (~0u << (s0 ? s0 - 1u : 0u));
+            const int ry = (int)(row % kTY), rz = (int)(row / kTY);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const uint32_t nr = nrow[q], sw = run_starts(rowv[nr]);
-                    auto put = [&](int xa, int xb) {
-                        if (sl >= r0 && sl < r0 + kPairCap) {
-                            const uint32_t a = j * kRowRuns + run_ordinal(sv, xa);
-                            const uint32_t b = nr * kRowRuns + run_ordinal(sw, xb);
-                            pairs[sl - r0] = (a << 16) | b;
-                        }
-                        ++sl;
-                    };
-                    for (uint32_t m = hm[q].a; m; m &= m - 1) put(__ffs(m) - 1, __ffs(m) - 1);
-                    for (uint32_t m = hm[q].b; m; m &= m - 1) put(__ffs(m) - 1, __ffs(m) - 2);
-                    for (uint32_t m = hm[q].c; m; m &= m - 1) put(__ffs(m) - 1, __ffs(m));
-                }
+            for (int q = 0; q < 4; ++q) {
+                const int dy = (q < 2) ? q - 1 : (q == 2 ? -1 : 1), dz = (q == 0) ? 0 : -1;
+                if (ry + dy < 0 || ry + dy >= kTY || rz + dz < 0) continue;
+                const uint32_t nr = (uint32_t)(ry + dy + kTY * (rz + dz)), w = rowv[nr], sw = run_starts(w);
+                const uint32_t m0 = w & win;
+                for (uint32_t m = run_starts(m0); m; m &= m - 1)
+                    if (!f(rowbase[nr] + run_ordinal(sw, __ffs(m) - 1))) return;
             }
-            __syncthreads();
-            const uint32_t np = min(npairs - r0, kPairCap);
-            for (uint32_t i = j; i < np; i += kBlock) {
-                const uint32_t pr = pairs[i];
-                lds_unite(par, pr >> 16, pr & 0xFFFFu);
-            }
-            __syncthreads();
-        }
-        // roots of the runs (a run's entry then holds its root; every value
-        // a walk reads is an ancestor or the root) ...
-        {
-            uint32_t c = j * kRowRuns;
-            for (uint32_t m = sv; m; m &= m - 1, ++c) lds_st(&par[c], lds_root(par, c));
+        };
+        for (uint32_t c = j; c < nruns; c += kBlock) {
+            uint32_t p = c;
+            touching(c, [&](uint32_t o) {
+                p = o;
+                return false;
+            });
+            par[c] = p;
         }
         __syncthreads();
-        // ... then each run adds its length to its root's count, kept in the
-        // upper 16 bits of the root's entry (run indices take 12 bits, a tile
-        // holds at most 8192 cells)
-        {
-            uint32_t c = j * kRowRuns;
-            for (uint32_t m = sv; m; m &= m - 1, ++c) {
-                const int s0 = __ffs(m) - 1;
-                const int e0 = __ffs(ev & ~((1u << s0) - 1u)) - 1;
-                atomicAdd(&par[par[c] & 0xFFFFu], (uint32_t)(e0 - s0 + 1) << 16);
+        // (a parent's entry may be jumped meanwhile: any value read is an ancestor)
+        for (uint32_t c = j; c < nruns; c += kBlock) {
+            uint32_t p = lds_ld(&par[c]);
+#pragma unroll 1
+            for (int i = 0; i < kJumps; ++i) {
+                const uint32_t g = lds_ld(&par[p]);
+                if (g == p) break;
+                p = g;
+                lds_st(&par[c], p);
             }
+        }
+        __syncthreads();
+        for (uint32_t c = j; c < nruns; c += kBlock) {
+            uint32_t a = c;
+            bool first = true;
+            touching(c, [&](uint32_t o) {
+                if (!first) a = lds_unite(par, a, o);   // (the first is its parent)
+                first = false;
+                return true;
+            });
+        }
+        __syncthreads();
+        // roots of the runs (a run's entry then holds its root; every value
+        // a walk reads is an ancestor or the root) ...
+        for (uint32_t c = j; c < nruns; c += kBlock) lds_st(&par[c], lds_root(par, c));
+        __syncthreads();
+        // ... then each run adds its length to its root's count, kept in the
+        // upper 16 bits of the root's entry (run numbers take 12 bits, a tile
+        // holds at most 8192 cells)
+        const auto run_len = [&](uint32_t row, uint32_t s0) { return (uint32_t)__ffs(run_ends(rowv[row]) >> s0); };
+        for (uint32_t c = j; c < nruns; c += kBlock) {
+            const uint32_t in = info[c];
+            atomicAdd(&par[par[c] & 0xFFFFu], run_len(in / 32u, in & 31u) << 16);
         }
         __syncthreads();
         // global parents: the rank of the local root, for a whole run at once
         // (consecutive cells of a run have consecutive ranks); the local
         // root's entry of csize receives its component's voxel count in the
         // tile
-        uint32_t c = j * kRowRuns;
-        for (uint32_t m = sv; m; m &= m - 1, ++c) {
-            const int s0 = __ffs(m) - 1;
-            const int e0 = __ffs(ev & ~((1u << s0) - 1u)) - 1;
-            const uint32_t pc = par[c], rt = pc & 0xFFFFu;
-            const uint32_t rrow = rt / kRowRuns, rx = nth_set_bit(run_starts(rowv[rrow]), rt % kRowRuns);
-            const uint32_t rr = rowrank[rrow] + __popc(rowv[rrow] & ((1u << rx) - 1u));
-            const uint32_t r = rowrank[j] + __popc(v & ((1u << s0) - 1u));
+        const auto rank_at = [&](uint32_t row, uint32_t x) { return rowrank[row] + __popc(rowv[row] & ((1u << x) - 1u)); };
+        for (uint32_t c = j; c < nruns; c += kBlock) {
+            const uint32_t in = info[c], pc = par[c], rt = pc & 0xFFFFu, ri = info[rt];
+            const uint32_t rr = rank_at(ri / 32u, ri & 31u), r = rank_at(in / 32u, in & 31u);
             // the run's entries: single stores up to a 16-byte boundary, then
             // 16-byte stores, then the rest
             uint32_t p0 = r;
-            const uint32_t pe = r + (uint32_t)(e0 - s0 + 1);
+            const uint32_t pe = r + run_len(in / 32u, in & 31u);
             for (; p0 < pe && (p0 & 3u); ++p0) parent[p0] = rr;
             for (; p0 + 4 <= pe; p0 += 4) *reinterpret_cast<uint4*>(parent + p0) = make_uint4(rr, rr, rr, rr);
             for (; p0 < pe; ++p0) parent[p0] = rr;
@@ -434,10 +382,32 @@ __global__ void __launch_bounds__(kBlock) k_ccl_tile(const uint32_t* __restrict_
     }
 }
 
-__device__ __forceinline__ bool occ_cell(const uint32_t* __restrict__ bits, const Dims& d, int x, int y, int z)
+// A row segment of 32 cells from x0 with the cells beside it, and the rank of
+// its first cell (occupied cells with smaller keys): `prev` and `next` have
+// the ranks rank0 - 1 and rank0 + popc(v).  Four reads without a branch, so
+// that those of several rows are in flight together.
+struct Segment {
+    uint32_t v, rank0;
+    bool prev, next;
+};
+
+__device__ __forceinline__ Segment segment_at(const uint32_t* __restrict__ bits, uint32_t nwords,
+                                              const uint32_t* __restrict__ wrank, const Dims& d, uint32_t x0,
+                                              uint32_t y, uint32_t z)
 {
-    if (x < 0 || y < 0 || z < 0 || x >= (int)d.nx || y >= (int)d.ny || z >= (int)d.nz) return false;
-    return occ(bits, (uint32_t)x + d.nx * ((uint32_t)y + d.ny * (uint32_t)z));
+    const bool ok = y < d.ny && z < d.nz;
+    const uint32_t key0 = ok ? x0 + d.nx * (y + d.ny * z) : 0u, w = key0 >> 5, sh = key0 & 31u;
+    const uint32_t a = bits[w ? w - 1u : 0u], b = bits[w], c = bits[min(w + 1u, nwords - 1u)], wr = wrank[w];
+    Segment s;
+    s.v = b >> sh;
+    if (sh && w + 1u < nwords) s.v |= c << (32u - sh);
+    const uint32_t n = min(d.nx - x0, 32u);
+    if (n < 32u) s.v &= (1u << n) - 1u;
+    if (!ok) s.v = 0u;
+    s.prev = ok && x0 > 0u && ((sh ? b >> (sh - 1u) : a >> 31) & 1u);
+    s.next = ok && x0 + 32u < d.nx && ((c >> sh) & 1u);
+    s.rank0 = wr + (uint32_t)__popc(b & ((1u << sh) - 1u));
+    return s;
 }
 
 // Cross-tile adjacencies, from the cell with the larger key.
@@ -448,23 +418,27 @@ __device__ __forceinline__ bool occ_cell(const uint32_t* __restrict__ bits, cons
 //  * x faces: the first cell of a segment links each occupied neighbour with
 //    a smaller key at x - 1 (five of them), the last cell each one at x + 1
 //    (four); these pairs lie in tiles of another x range.
-// Each pair is replaced by the local roots of its two voxels (the labelling
-// pass left every voxel pointing at its tile-local root), and a tile keeps
-// one copy of each distinct root pair (an
-// LDS hash set): along a dense surface many cells link the same two local
-// components.  The distinct pairs go to the tile's slice of a pair buffer; a
-// second kernel unites all pairs of the grid at once.  A tile with more
-// distinct pairs than its slice unites the excess itself.
+// Each pair is replaced by the parents of its two voxels (the labelling pass
+// left every voxel pointing at its tile-local root, and another tile's unions
+// may have moved that on to another ancestor), and a tile keeps one copy of
+// each distinct pair (an LDS hash set): along a dense surface many cells link
+// the same two local components.  The distinct pairs are listed in LDS and
+// united a thread each; pairs beyond the list are united where they are found.
+// A row's reads (its own words, then those of its four neighbours with
+// smaller keys, which also hold the cells beyond the x faces) are in flight
+// together; cell by cell they were up to 18 waits in turn.  Unions by another
+// kernel cost a launch and the list's way through memory: boundary and pairs
+// 28 + 12 us for 916k voxels, 18 + 9 for 29k; in one 28 and 18.
 constexpr uint32_t kPairHash = 1024;   // LDS hash set of root pairs per tile
+constexpr uint32_t kTilePairs = 256;   // distinct pairs listed per tile
 constexpr uint32_t kRawPairs = 1024;   // voxel pairs gathered per tile before the root lookups
 
 __global__ void __launch_bounds__(kBlock) k_ccl_boundary(const uint32_t* __restrict__ bits, uint32_t nwords,
                                                          const uint32_t* __restrict__ wrank, Dims d, TileGrid tg,
-                                                         uint32_t* parent, uint64_t* __restrict__ pairs,
-                                                         uint32_t* __restrict__ npair)
+                                                         uint32_t* parent)
 {
     __shared__ uint64_t raw[kRawPairs];
-    __shared__ uint64_t buf[kCclTilePairs];
+    __shared__ uint64_t buf[kTilePairs];
     __shared__ unsigned long long hset[kPairHash];
     __shared__ uint32_t nbuf;
     const uint32_t j = threadIdx.x;
@@ -480,7 +454,7 @@ __global__ void __launch_bounds__(kBlock) k_ccl_boundary(const uint32_t* __restr
             h = (h + 1) & (kPairHash - 1);
         }
         const uint32_t i = atomicAdd(&nbuf, 1u);
-        if (i < kCclTilePairs) buf[i] = key;
+        if (i < kTilePairs) buf[i] = key;
         else uf_unite(parent, ra, rb);
     };
     __shared__ uint32_t wtot[kBlock / kWave];
@@ -494,65 +468,36 @@ __global__ void __launch_bounds__(kBlock) k_ccl_boundary(const uint32_t* __restr
         const uint32_t tx = t % tg.ntx, ty = (t / tg.ntx) % tg.nty, tz = t / (tg.ntx * tg.nty);
         const uint32_t x0 = tx * kTX;
         const int y = (int)(ty * kTY) + yl, z = (int)(tz * kTZ) + zl;
-        uint32_t key0;
-        const uint32_t v = row_bits(bits, nwords, d, x0, (uint32_t)y, (uint32_t)z, &key0);
+        const Segment own = segment_at(bits, nwords, wrank, d, x0, (uint32_t)y, (uint32_t)z);
+        const uint32_t v = own.v, r0 = own.rank0;
         // first the voxel pairs (no loads of parents yet): each thread finds
         // and counts its row's, a block scan places them in the raw list
         const bool face = yl == 0 || yl == kTY - 1 || zl == 0;
         const bool first = (v & 1u) && x0 > 0, last = (v >> 31) & 1u;
-        uint32_t r0 = 0, cnt = 0;
+        uint32_t cnt = 0;
         HookMasks hm[4];
-        uint32_t fw[4], fn0[4];
-        uint32_t fr[5], lr[4], fmask = 0, lmask = 0;
+        Segment nb[4];
+        uint32_t fmask = 0, lmask = 0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             hm[q].a = hm[q].b = hm[q].c = 0;
-            fw[q] = fn0[q] = 0;
+            nb[q].v = nb[q].rank0 = 0;
+            nb[q].prev = nb[q].next = false;
         }
         if (v && (face || first || last)) {
-            r0 = seg_rank0(bits, wrank, key0);
-            if (face) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int dy = (q == 0) ? -1 : (q - 2);
-                    const int dz = (q == 0) ? 0 : -1;
-                    const int ly = yl + dy, lz = zl + dz;
-                    if (ly >= 0 && ly < kTY && lz >= 0) continue;   // same tile
-                    uint32_t nkey0;
-                    const uint32_t w = row_bits(bits, nwords, d, x0, (uint32_t)(y + dy), (uint32_t)(z + dz), &nkey0);
-                    if (!w) continue;
-                    fw[q] = w;
-                    fn0[q] = seg_rank0(bits, wrank, nkey0);
-                    hm[q] = hook_masks(v, w);
-                    cnt += (uint32_t)(__popc(hm[q].a) + __popc(hm[q].b) + __popc(hm[q].c));
-                }
-            }
-            if (first) {
-                const int x = (int)x0;
+            for (int q = 0; q < 4; ++q)
+                nb[q] = segment_at(bits, nwords, wrank, d, x0, (uint32_t)(y + (q == 0 ? -1 : q - 2)),
+                                   (uint32_t)(z + (q == 0 ? 0 : -1)));
 #pragma unroll
-                for (int q = 0; q < 5; ++q) {
-                    const int dy = (q < 3) ? q - 1 : (q == 3 ? -1 : 0);
-                    const int dz = (q < 3) ? -1 : 0;
-                    fr[q] = 0;
-                    if (!occ_cell(bits, d, x - 1, y + dy, z + dz)) continue;
-                    const uint32_t nk = (uint32_t)(x - 1) + d.nx * ((uint32_t)(y + dy) + d.ny * (uint32_t)(z + dz));
-                    fr[q] = rank_of(bits, wrank, nk);
-                    fmask |= 1u << q;
-                }
+            for (int q = 0; q < 4; ++q) {
+                const int ly = yl + (q == 0 ? -1 : q - 2), lz = zl + (q == 0 ? 0 : -1);
+                if (ly < 0 || ly >= kTY || lz < 0) hm[q] = hook_masks(v, nb[q].v);   // (else the same tile)
+                cnt += (uint32_t)(__popc(hm[q].a) + __popc(hm[q].b) + __popc(hm[q].c));
+                fmask |= first && nb[q].prev ? 1u << q : 0u;
+                lmask |= last && nb[q].next ? 1u << q : 0u;
             }
-            if (last) {
-                const int x = (int)x0 + 31;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int dy = (q < 3) ? q - 1 : -1;
-                    const int dz = (q < 3) ? -1 : 0;
-                    lr[q] = 0;
-                    if (!occ_cell(bits, d, x + 1, y + dy, z + dz)) continue;
-                    const uint32_t nk = (uint32_t)(x + 1) + d.nx * ((uint32_t)(y + dy) + d.ny * (uint32_t)(z + dz));
-                    lr[q] = rank_of(bits, wrank, nk);
-                    lmask |= 1u << q;
-                }
-            }
+            fmask |= first && own.prev ? 1u << 4 : 0u;
             cnt += (uint32_t)(__popc(fmask) + __popc(lmask));
         }
         uint32_t inc = cnt;
@@ -581,7 +526,7 @@ __global__ void __launch_bounds__(kBlock) k_ccl_boundary(const uint32_t* __restr
                 };
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const uint32_t w = fw[q], n0 = fn0[q];
+                    const uint32_t w = nb[q].v, n0 = nb[q].rank0;
                     for (uint32_t m = hm[q].a; m; m &= m - 1) {
                         const int xa = __ffs(m) - 1;
                         emit(r0 + __popc(v & ((1u << xa) - 1u)), n0 + __popc(w & ((1u << xa) - 1u)));
@@ -597,11 +542,11 @@ __global__ void __launch_bounds__(kBlock) k_ccl_boundary(const uint32_t* __restr
                 }
 #pragma unroll
                 for (int q = 0; q < 5; ++q)
-                    if ((fmask >> q) & 1u) emit(r0, fr[q]);
+                    if ((fmask >> q) & 1u) emit(r0, (q < 4 ? nb[q].rank0 : r0) - 1u);
                 const uint32_t rl = r0 + (uint32_t)__popc(v) - 1u;
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    if ((lmask >> q) & 1u) emit(rl, lr[q]);
+                    if ((lmask >> q) & 1u) emit(rl, nb[q].rank0 + (uint32_t)__popc(nb[q].v));
             }
             __syncthreads();
             const uint32_t nr = min(nraw - q0, kRawPairs);
@@ -611,25 +556,11 @@ __global__ void __launch_bounds__(kBlock) k_ccl_boundary(const uint32_t* __restr
             }
             __syncthreads();
         }
-        const uint32_t np = min(nbuf, kCclTilePairs);
-        for (uint32_t i = j; i < np; i += kBlock) pairs[(uint64_t)t * kCclTilePairs + i] = buf[i];
-        if (j == 0) npair[t] = np;
+        const uint32_t np = min(nbuf, kTilePairs);
+        for (uint32_t i = j; i < np; i += kBlock) uf_unite(parent, (uint32_t)(buf[i] >> 32), (uint32_t)buf[i]);
         // LDS is reused by the next tile (a block with no next tile skips the
         // barrier, which would wait for the stores above to complete)
         if (v0 + gridDim.x < nv) __syncthreads();
-    }
-}
-
-// Unions of the buffered cross-tile pairs, one pair per thread.
-__global__ void __launch_bounds__(kBlock) k_ccl_pairs(uint32_t ntiles, const uint64_t* __restrict__ pairs,
-                                                      const uint32_t* __restrict__ npair, uint32_t* parent)
-{
-    for (uint32_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        const uint32_t np = npair[t];
-        for (uint32_t i = threadIdx.x; i < np; i += blockDim.x) {
-            const uint64_t pr = pairs[(uint64_t)t * kCclTilePairs + i];
-            uf_unite(parent, (uint32_t)(pr >> 32), (uint32_t)pr);
-        }
     }
 }
 
@@ -637,47 +568,45 @@ __global__ void __launch_bounds__(kBlock) k_ccl_pairs(uint32_t ntiles, const uin
 // writing anything on the way (a path-halving store here could overwrite the
 // root another thread has just stored for that node) and stores only its own
 // entry; every value a walk can read is an ancestor, so walks stay correct.
-__global__ void __launch_bounds__(kBlock) k_ccl_flatten(const DevCounters* __restrict__ ctr, uint32_t* parent,
-                                                        uint32_t* csize)
+// A tile-local root joined to another tile's component hands its count to the
+// component's root; a large component has many local roots, so a workgroup
+// gathers the counts of its roots in LDS first (an atomic per wave and root,
+// most of them on a floor's word, took most of the kernel's time: 2.4M voxels 33 us, so 21).
+constexpr int kFlatBlock = 1024;
+constexpr uint32_t kFlatSlots = 64;
+
+__global__ void __launch_bounds__(kFlatBlock) k_ccl_flatten(const DevCounters* __restrict__ ctr, uint32_t* parent,
+                                                            uint32_t* csize)
 {
+    __shared__ uint32_t root_of[kFlatSlots], count[kFlatSlots];
     const uint32_t V = ctr->n_occ;
-    const int lane = threadIdx.x & (kWave - 1);
-    const uint32_t stride = gridDim.x * blockDim.x;
-    // every lane runs the same iterations (the wave-wide sums below need them all)
-    for (uint32_t b0 = blockIdx.x * blockDim.x + (threadIdx.x & ~(kWave - 1)); b0 < V; b0 += stride) {
-        const uint32_t r = b0 + (uint32_t)lane;
-        uint32_t x = r, cs = 0;
-        if (r < V) {
-            // only roots receive counts below, and the count is used only
-            // when r is not a root: it can be read before the walk
-            const uint32_t own = csize[r];
-            const uint32_t p0 = ld_parent(&parent[r]);
-            uint32_t p = p0;
-            while (p != x) {
-                x = p;
-                p = ld_parent(&parent[x]);
-            }
-            if (x != p0) st_parent(&parent[r], x);   // most voxels already point at their root
-            // a tile-local root joined to another tile's component hands its
-            // count to the component's root (only roots receive counts, so
-            // the count read here is final)
-            if (x != r) cs = own;
-        }
-        // one atomic per distinct root in the wave (a large component has
-        // many local roots)
-        uint64_t pending = __ballot(cs != 0);
-        while (pending) {
-            const int leader = __ffsll((long long)pending) - 1;
-            const uint32_t root = __shfl(x, leader, kWave);
-            const bool same = cs != 0 && x == root;
-            uint32_t v = same ? cs : 0u;
-#pragma unroll
-            for (int d = kWave / 2; d > 0; d >>= 1) v += __shfl_xor(v, d, kWave);
-            if (lane == leader) atomicAdd(&csize[root], v);
-            pending &= ~__ballot(same);
-        }
+    if (threadIdx.x < kFlatSlots) {
+        root_of[threadIdx.x] = kEmpty;
+        count[threadIdx.x] = 0;
     }
+    __syncthreads();
+    const uint32_t stride = gridDim.x * blockDim.x;
+    for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < V; r += stride) {
+        // only roots receive counts below, and the count is used only when r
+        // is not a root: it is final, and can be read before the walk
+        const uint32_t own = csize[r];
+        const uint32_t p0 = ld_parent(&parent[r]);
+        uint32_t p = p0, x = r;
+        while (p != x) {
+            x = p;
+            p = ld_parent(&parent[x]);
+        }
+        if (x != p0) st_parent(&parent[r], x);   // most voxels already point at their root
+        if (x == r || own == 0) continue;
+        const uint32_t at = (x * 0x9E3779B1u) >> 26;
+        const uint32_t old = atomicCAS(&root_of[at], kEmpty, x);
+        if (old == kEmpty || old == x) atomicAdd(&count[at], own);
+        else atomicAdd(&csize[x], own);   // another root has the slot
+    }
+    __syncthreads();
+    if (threadIdx.x < kFlatSlots && count[threadIdx.x]) atomicAdd(&csize[root_of[threadIdx.x]], count[threadIdx.x]);
 }
+static_assert(kFlatSlots == 1u << (32 - 26), "the slot is a hash's top bits");
 
 // ---- grouping -------------------------------------------------------------------
 // One fused scan over the ranks gives, in rank order: the cluster id of each
@@ -826,12 +755,6 @@ Dims dims_of(const Geom& g)
 
 }  // namespace
 
-uint64_t ccl_tiles(const Geom& g)
-{
-    const Dims d = dims_of(g);
-    return (uint64_t)((d.nx + kTX - 1) / kTX) * ((d.ny + kTY - 1) / kTY) * ((d.nz + kTZ - 1) / kTZ);
-}
-
 hipError_t launch_ccl(const Geom& g, const uint32_t* bits, SegBuffers& b, uint32_t cap, DevCounters* ctr,
                       hipStream_t s)
 {
@@ -840,8 +763,6 @@ hipError_t launch_ccl(const Geom& g, const uint32_t* bits, SegBuffers& b, uint32
     tg.ntx = (d.nx + kTX - 1) / kTX;
     tg.nty = (d.ny + kTY - 1) / kTY;
     tg.ntz = (d.nz + kTZ - 1) / kTZ;
-    const uint64_t ntiles = (uint64_t)tg.ntx * tg.nty * tg.ntz;
-    const int tgrid = (int)(ntiles < 16384 ? ntiles : 16384);
     // the labelling and face kernels walk the XCD-ordered tile indices (a
     // multiple of 8, and so is 16384)
     const uint32_t nv = xcd_virtual_tiles(tg);
@@ -852,9 +773,8 @@ hipError_t launch_ccl(const Geom& g, const uint32_t* bits, SegBuffers& b, uint32
     }
     {
         StageScope t(VM_STAGE_CCL_LINK, s);
-        k_ccl_boundary<<<vgrid, kBlock, 0, s>>>(bits, g.nwords, b.wrank, d, tg, b.parent, b.pairs, b.npair);
-        k_ccl_pairs<<<tgrid, kBlock, 0, s>>>((uint32_t)ntiles, b.pairs, b.npair, b.parent);
-        k_ccl_flatten<<<grid_for(cap), kBlock, 0, s>>>(ctr, b.parent, b.csize);
+        k_ccl_boundary<<<vgrid, kBlock, 0, s>>>(bits, g.nwords, b.wrank, d, tg, b.parent);
+        k_ccl_flatten<<<grid_for(cap, kFlatBlock, 1024), kFlatBlock, 0, s>>>(ctr, b.parent, b.csize);
     }
     return hipGetLastError();
 }

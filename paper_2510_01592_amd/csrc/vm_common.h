@@ -114,12 +114,8 @@ struct SegBuffers {
     uint32_t* wrank;       // [nwords+1] exclusive popcount prefix of the occupancy words
     uint32_t* blk;         // block partials for scans (sized generously)
     uint32_t* hist;        // radix histograms
-    uint64_t* pairs;       // [ccl_tiles * kCclTilePairs] cross-tile hook pairs, per tile
-    uint32_t* npair;       // [ccl_tiles] pairs stored per tile
 };
 
-constexpr uint32_t kCclTilePairs = 256;   // cross-tile hook pairs buffered per labelling tile
-uint64_t ccl_tiles(const Geom& g);        // labelling tiles covering the grid
 
 // Number of clusters a pass may process: min(meta[0], k_cap) if the offsets
 // are a valid CSR (off[0] = 0, non-decreasing, off[K] = meta[1] <= n_cap),

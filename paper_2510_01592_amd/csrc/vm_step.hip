@@ -478,7 +478,7 @@ hipError_t launch_steppable(const Geom& g, const Hash& h, const uint32_t* bits, 
     else k_step_classify<2><<<grid, kBlock, 0, s>>>(a, ctr);
     k_step_runs<<<grid, kBlock, 0, s>>>(a, ctr, b.parent);
     k_step_hook<<<grid, kBlock, 0, s>>>(a, ctr, b.parent);
-    k_step_flatten<<<grid_for(cap, kFlatBlock), kFlatBlock, 0, s>>>(ctr, sb.step, b.parent, b.csize);
+    k_step_flatten<<<grid_for(cap, kFlatBlock, 1024), kFlatBlock, 0, s>>>(ctr, sb.step, b.parent, b.csize);
     if (d_normal || d_steppable) k_step_export<<<grid, kBlock, 0, s>>>(ctr, sb.normal, sb.step, d_normal, d_steppable);
     return hipGetLastError();
 }
