@@ -21,6 +21,8 @@
 #include "vm_common.h"
 #include "vm_tilescan.h"
 
+#include <algorithm>
+
 namespace vm {
 namespace {
 
@@ -610,44 +612,42 @@ static_assert(kFlatSlots == 1u << (32 - 26), "the slot is a hash's top bits");
 
 // ---- grouping -------------------------------------------------------------------
 // One fused scan over the ranks gives, in rank order: the cluster id of each
-// kept root (roots of components with at least min_cluster voxels), the
-// cluster offsets (running sum of the kept roots' sizes, i.e. clusters in
-// label order), and each kept voxel's position among the kept voxels.
+// root (kEmpty for components below min_cluster voxels) and the cluster
+// offsets (running sum of the kept roots' sizes, i.e. clusters in label
+// order).
 struct GroupF {
     const uint32_t* parent;
     const uint32_t* csize;
     uint32_t min_cluster;
-    __device__ Vec<3> operator()(uint32_t r) const
+    __device__ Vec<2> operator()(uint32_t r) const
     {
-        const uint32_t root = parent[r];
-        const uint32_t sz = csize[root];
-        const bool kept = sz >= min_cluster;
-        const bool rt = kept && root == r;
-        Vec<3> x;
-        x.v[0] = rt ? 1u : 0u;
-        x.v[1] = rt ? sz : 0u;
-        x.v[2] = kept ? 1u : 0u;
+        const uint32_t sz = parent[r] == r ? csize[r] : 0u;
+        const bool kept = sz >= min_cluster;   // (min_cluster is at least 1)
+        Vec<2> x;
+        x.v[0] = kept ? 1u : 0u;
+        x.v[1] = kept ? sz : 0u;
         return x;
     }
 };
 
 struct GroupG {
-    uint32_t* cid;        // cluster id, at kept roots
-    uint32_t* kpos;       // position among kept voxels, at kept voxels
+    const uint32_t* parent;
+    uint32_t* cid;        // cluster id, at roots
     uint32_t* cl_off;
     uint32_t* cl_tag;
     const uint32_t* occ_key;
     DevCounters* ctr;
-    __device__ void operator()(uint32_t r, const Vec<3>& x, const Vec<3>& pre) const
+    __device__ void operator()(uint32_t r, const Vec<2>& x, const Vec<2>& pre) const
     {
-        if (x.v[2]) kpos[r] = pre.v[2];
         if (x.v[0]) {
             cid[r] = pre.v[0];
             cl_off[pre.v[0]] = pre.v[1];
             cl_tag[pre.v[0]] = occ_key[r];
+        } else if (parent[r] == r) {
+            cid[r] = kEmpty;
         }
     }
-    __device__ void total(const Vec<3>& t) const
+    __device__ void total(const Vec<2>& t) const
     {
         ctr->meta[0] = t.v[0];
         ctr->meta[1] = t.v[1];
@@ -656,80 +656,276 @@ struct GroupG {
     }
 };
 
-__global__ void __launch_bounds__(kBlock) k_group_pairs(const DevCounters* __restrict__ ctr,
-                                                        const uint32_t* __restrict__ parent,
-                                                        const uint32_t* __restrict__ csize, uint32_t min_cluster,
-                                                        const uint32_t* __restrict__ cid_scan,
-                                                        const uint32_t* __restrict__ pos_scan,
-                                                        const uint32_t* __restrict__ occ_key,
-                                                        uint32_t* __restrict__ out_cid, uint32_t* __restrict__ out_key)
+// The kept voxels in cluster-major order: a stable radix sort by cluster id
+// (ascending keys inside each cluster).  11-bit digits: ids up to 2048, the
+// usual case, take one pass, up to 4M two; the passes that the largest id of
+// the frame does not need do nothing.  A pass is three launches:
+//   hist:    digits per tile, digit-major; a tile is as many steps of 1024
+//            items as leave about 1024 tiles (for 916k voxels one, and the
+//            scatter takes 23 us, 30 with 2048 items a step; for 2.4M voxels
+//            three, and the first two kernels take 28 us, 49 with one);
+//   rows:    a workgroup per digit turns its row into prefixes and a total;
+//   scatter: the digits' totals are scanned by every workgroup (2048 words
+//            from L2), then the tile's voxels go to their places.
+// The first pass takes the voxels by rank, straight from their roots, and
+// leaves out those of no cluster; the last one that runs also looks up each
+// voxel and writes the cluster points themselves.  (As pairs made by a kernel
+// of their own, a sort with two scan kernels per pass and a gather after it,
+// 916k voxels took 74 us from the scan on, and take 60; 29k took 47 and take 36.)
+constexpr int kSortBits = 11;
+constexpr uint32_t kSortBins = 1u << kSortBits;
+constexpr int kSortIters = 4;
+constexpr uint32_t kSortStep = kBlock * kSortIters;   // 1024 items, a workgroup's step
+constexpr uint32_t kSortTiles = 1024;                 // tiles aimed at: a row of a histogram stays short
+constexpr int kWaveSpan = kWave * kSortIters;         // a wave's voxels, consecutive
+
+struct GroupSort {
+    const DevCounters* ctr;
+    const uint32_t* parent;
+    const uint32_t* cid;
+    const uint32_t* occ_key;
+    uint32_t* k[2];       // cluster id and key of each kept voxel, between passes; k[1]: first every voxel's id
+    uint32_t* v[2];
+    uint32_t* hist;       // [digits * tiles]
+    uint32_t* tot;        // [kSortBins]
+    Geom g;
+    Hash h;
+    uint32_t* cl_key;
+    float* cl_x;
+    float* cl_y;
+    float* cl_z;
+};
+
+// What pass p (shift = p * kSortBits) covers.
+struct SortPass {
+    uint32_t n, bins;     // items, digits in use
+    uint32_t tile, nt;    // items per tile, tiles
+    bool last, runs;
+};
+
+__device__ __forceinline__ SortPass sort_pass(const GroupSort& a, int shift)
 {
-    const uint32_t V = ctr->n_occ;
-    for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < V; r += gridDim.x * blockDim.x) {
-        const uint32_t root = parent[r];
-        if (csize[root] >= min_cluster) {
-            const uint32_t p = pos_scan[r];
-            out_cid[p] = cid_scan[root];
-            out_key[p] = occ_key[r];
+    const uint32_t top = a.ctr->kmax >> shift;
+    SortPass p;
+    p.n = shift == 0 ? a.ctr->n_occ : a.ctr->meta[1];
+    p.last = top < kSortBins;
+    p.bins = p.last ? top + 1u : kSortBins;
+    p.runs = shift == 0 || top != 0u;
+    const uint32_t steps = (p.n + kSortStep - 1) / kSortStep;
+    p.tile = max((steps + kSortTiles - 1) / kSortTiles, 1u) * kSortStep;
+    p.nt = (p.n + p.tile - 1) / p.tile;
+    return p;
+}
+
+template <bool kFirst>
+__global__ void __launch_bounds__(kBlock) k_group_hist(GroupSort a, int shift)
+{
+    __shared__ uint32_t cnt[kSortBins];
+    const SortPass sp = sort_pass(a, shift);
+    if (!sp.runs) return;
+    const int src = (shift / kSortBits + 1) & 1, lane = threadIdx.x & (kWave - 1);
+    for (uint32_t t = blockIdx.x; t < sp.nt; t += gridDim.x) {
+        for (uint32_t d = threadIdx.x; d < sp.bins; d += kBlock) cnt[d] = 0;
+        __syncthreads();
+        const uint32_t end = min((t + 1) * sp.tile, sp.n);
+        for (uint32_t i0 = t * sp.tile + threadIdx.x; i0 - threadIdx.x < end; i0 += kSortStep) {
+            uint32_t k[kSortIters];
+#pragma unroll
+            for (int j = 0; j < kSortIters; ++j) {
+                const uint32_t i = i0 + j * kBlock;
+                k[j] = i < end ? (kFirst ? a.cid[a.parent[i]] : a.k[src][i]) : kEmpty;
+            }
+            if (kFirst) {
+#pragma unroll
+                for (int j = 0; j < kSortIters; ++j)
+                    if (i0 + j * kBlock < end) a.k[src][i0 + j * kBlock] = k[j];
+            }
+#pragma unroll
+            for (int j = 0; j < kSortIters; ++j) {
+                // neighbours are mostly of one cluster: the first one's lanes add together
+                const bool in = k[j] != kEmpty;
+                const uint32_t d = (k[j] >> shift) & (kSortBins - 1);
+                const uint64_t m = __ballot(in);
+                if (m == 0) continue;
+                const int lead = __ffsll((long long)m) - 1;
+                const uint32_t dl = __shfl(d, lead, kWave);
+                const bool same = in && d == dl;
+                const uint32_t c = (uint32_t)__popcll(__ballot(same));
+                if (lane == lead) atomicAdd(&cnt[d], c);
+                else if (in && !same) atomicAdd(&cnt[d], 1u);
+            }
         }
+        __syncthreads();
+        for (uint32_t d = threadIdx.x; d < sp.bins; d += kBlock) a.hist[(size_t)d * sp.nt + t] = cnt[d];
+        __syncthreads();   // cnt is reused by the next tile
     }
 }
 
-constexpr int kGatherU = 4;
-
-// CSR points: key and Eq. (1) mean of each kept voxel, cluster-major.  Each
-// lane gathers kGatherU voxels kGatherU * stride apart, their first probes
-// issued together; a probe loads the whole 32-byte slot, so a hit needs no
-// second load for the sums.
-__global__ void __launch_bounds__(kBlock) k_group_gather(Geom g, Hash h, const DevCounters* __restrict__ ctr,
-                                                         const uint32_t* __restrict__ sorted_key0,
-                                                         const uint32_t* __restrict__ sorted_key1,
-                                                         uint32_t* __restrict__ cl_key, float* __restrict__ cl_x,
-                                                         float* __restrict__ cl_y, float* __restrict__ cl_z)
+__global__ void __launch_bounds__(kBlock) k_group_rows(GroupSort a, int shift)
 {
-    const uint32_t* __restrict__ sorted_key = ctr->group_sel ? sorted_key1 : sorted_key0;
-    const uint32_t n = ctr->meta[1];
-    const uint32_t nx = (uint32_t)g.dims[0], ny = (uint32_t)g.dims[1];
-    const uint32_t stride = gridDim.x * blockDim.x;
-    const uint32_t nprobe = h.mask < kMaxProbe ? h.mask + 1u : kMaxProbe;
-    for (uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x; i0 < n; i0 += kGatherU * stride) {
-        uint32_t k[kGatherU], s[kGatherU];
-        Slot sl[kGatherU];
+    __shared__ Vec<1> lds[kBlock / kWave];
+    const SortPass sp = sort_pass(a, shift);
+    if (!sp.runs) return;
+    const uint32_t nt = sp.nt;
+    for (uint32_t d = blockIdx.x; d < sp.bins; d += gridDim.x) {
+        uint32_t* row = a.hist + (size_t)d * nt;
+        uint32_t carry = 0;
+        for (uint32_t t0 = 0; t0 < nt; t0 += 4 * kBlock) {
+            const uint32_t t = t0 + 4 * threadIdx.x;
+            uint32_t x[4];
+            Vec<1> s{{0u}}, all;
 #pragma unroll
-        for (int u = 0; u < kGatherU; ++u) {
-            const uint32_t i = i0 + (uint32_t)u * stride;
-            k[u] = i < n ? sorted_key[i] : kEmpty;
+            for (int j = 0; j < 4; ++j) {
+                x[j] = t + j < nt ? row[t + j] : 0u;
+                s.v[0] += x[j];
+            }
+            uint32_t run = carry + ts_block_excl(s, lds, &all).v[0];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (t + j < nt) row[t + j] = run;
+                run += x[j];
+            }
+            carry += all.v[0];
         }
+        if (threadIdx.x == 0) a.tot[d] = carry;
+    }
+}
+
+// LDS written by some lanes of a wave is read by others of it
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <bool kFirst>
+__global__ void __launch_bounds__(kBlock) k_group_scatter(GroupSort a, int shift)
+{
+    constexpr int kWaves = kBlock / kWave;
+    constexpr uint32_t kOwn = kSortBins / kBlock;   // digits of a thread, consecutive
+    __shared__ uint32_t place[kWaves][kSortBins];   // counts, then places, of each wave's digits
+    __shared__ Vec<1> lds[kWaves];
+    const SortPass sp = sort_pass(a, shift);
+    if (!sp.runs) return;
+    const uint32_t bins = sp.bins;
+    const bool last = sp.last;
+    const int src = (shift / kSortBits + 1) & 1;
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t wave = threadIdx.x / kWave;
+    if (blockIdx.x >= sp.nt) return;
+    uint32_t tot[kOwn];
+    Vec<1> s{{0u}}, all;
 #pragma unroll
-        for (int u = 0; u < kGatherU; ++u) {
-            s[u] = hash_slot(k[u], h.log2cap);
-            if (k[u] != kEmpty) {
-                sl[u] = h.slot[s[u]];
+    for (uint32_t q = 0; q < kOwn; ++q) {
+        const uint32_t d = threadIdx.x * kOwn + q;
+        tot[q] = d < bins ? a.tot[d] : 0u;
+        s.v[0] += tot[q];
+    }
+    const uint32_t first = ts_block_excl(s, lds, &all).v[0];   // items of the digits before this thread's
+    const uint64_t lt = (1ull << lane) - 1ull;
+    for (uint32_t t = blockIdx.x; t < sp.nt; t += gridDim.x) {
+        // the places of the tile's next item of each of this thread's digits
+        uint32_t at[kOwn], run = first;
+#pragma unroll
+        for (uint32_t q = 0; q < kOwn; ++q) {
+            const uint32_t d = threadIdx.x * kOwn + q;
+            at[q] = run + (d < bins ? a.hist[(size_t)d * sp.nt + t] : 0u);
+            run += tot[q];
+        }
+        const uint32_t end = min((t + 1) * sp.tile, sp.n);
+        for (uint32_t s0 = t * sp.tile; s0 < end; s0 += kSortStep) {
+            const uint32_t i0 = s0 + wave * kWaveSpan + (uint32_t)lane;
+            uint32_t k[kSortIters], v[kSortIters], p[kSortIters];
+#pragma unroll
+            for (int j = 0; j < kSortIters; ++j) {
+                const uint32_t i = i0 + j * kWave;
+                k[j] = i < end ? a.k[src][i] : kEmpty;
+                v[j] = i < end ? (kFirst ? a.occ_key[i] : a.v[src][i]) : 0u;
+            }
+            // the last pass writes the points: the first probes of all its slots
+            // are in flight while the places are found, and a probe loads the
+            // whole 32-byte slot, so a hit needs no second load for the sums
+            Slot sl[kSortIters];
+            if (last) {
+#pragma unroll
+                for (int j = 0; j < kSortIters; ++j)
+                    sl[j] = a.h.slot[k[j] != kEmpty ? hash_slot(v[j], a.h.log2cap) : 0u];
+            }
+            for (uint32_t d = threadIdx.x; d < bins; d += kBlock) {
+#pragma unroll
+                for (int w = 0; w < kWaves; ++w) place[w][d] = 0;
+            }
+            __syncthreads();
+            // a wave counts its digits in item order and notes each item's number
+            // among the wave's items of its digit
+#pragma unroll
+            for (int j = 0; j < kSortIters; ++j) {
+                const bool in = k[j] != kEmpty;
+                const uint32_t d = (k[j] >> shift) & (kSortBins - 1);
+                uint64_t m = __ballot(in);   // the lanes with this lane's digit
+#pragma unroll
+                for (int b = 0; b < kSortBits; ++b) {
+                    const bool bit = (d >> b) & 1u;
+                    const uint64_t bb = __ballot(in && bit);
+                    m &= bit ? bb : ~bb;
+                }
+                p[j] = 0;
+                if (in) p[j] = place[wave][d] + (uint32_t)__popcll(m & lt);
+                wave_fence();
+                if (in && (m & lt) == 0) place[wave][d] += (uint32_t)__popcll(m);
+                wave_fence();
+            }
+            __syncthreads();
+#pragma unroll
+            for (uint32_t q = 0; q < kOwn; ++q) {
+                const uint32_t d = threadIdx.x * kOwn + q;
+                if (d >= bins) continue;
+#pragma unroll
+                for (int w = 0; w < kWaves; ++w) {
+                    const uint32_t c = place[w][d];
+                    place[w][d] = at[q];
+                    at[q] += c;
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < kSortIters; ++j)
+                if (k[j] != kEmpty) p[j] += place[wave][(k[j] >> shift) & (kSortBins - 1)];
+            if (!last) {
+#pragma unroll
+                for (int j = 0; j < kSortIters; ++j)
+                    if (k[j] != kEmpty) {
+                        a.k[src ^ 1][p[j]] = k[j];
+                        a.v[src ^ 1][p[j]] = v[j];
+                    }
             } else {
-                sl[u].key = kEmpty;
-                sl[u].cnt = 0;
-                sl[u].sum[0] = sl[u].sum[1] = sl[u].sum[2] = 0;
-            }
-        }
+                // the points: key and Eq. (1) mean of each voxel
+                const uint32_t nx = (uint32_t)a.g.dims[0], ny = (uint32_t)a.g.dims[1];
+                const uint32_t nprobe = a.h.mask < kMaxProbe ? a.h.mask + 1u : kMaxProbe;
 #pragma unroll
-        for (int u = 0; u < kGatherU; ++u) {
-            const uint32_t i = i0 + (uint32_t)u * stride;
-            if (i >= n) continue;
-            // linear probing as in hash_find
-            for (uint32_t p = 1; sl[u].key != k[u] && sl[u].key != kEmpty && p < nprobe; ++p) {
-                s[u] = (s[u] + 1) & h.mask;
-                sl[u] = h.slot[s[u]];
+                for (int j = 0; j < kSortIters; ++j) {
+                    const uint32_t key = v[j], to = p[j];
+                    if (k[j] == kEmpty) continue;
+                    // linear probing as in hash_find
+                    uint32_t sx = hash_slot(key, a.h.log2cap);
+                    for (uint32_t q = 1; sl[j].key != key && sl[j].key != kEmpty && q < nprobe; ++q) {
+                        sx = (sx + 1) & a.h.mask;
+                        sl[j] = a.h.slot[sx];
+                    }
+                    float mx = 0.0f, my = 0.0f, mz = 0.0f;
+                    if (sl[j].key == key) {
+                        mx = voxel_mean_axis(key % nx, sl[j].sum[0], sl[j].cnt, a.g.voxel_size, a.g.origin[0]);
+                        my = voxel_mean_axis((key / nx) % ny, sl[j].sum[1], sl[j].cnt, a.g.voxel_size, a.g.origin[1]);
+                        mz = voxel_mean_axis(key / (nx * ny), sl[j].sum[2], sl[j].cnt, a.g.voxel_size, a.g.origin[2]);
+                    }
+                    a.cl_key[to] = key;
+                    a.cl_x[to] = mx;
+                    a.cl_y[to] = my;
+                    a.cl_z[to] = mz;
+                }
             }
-            float mx = 0.0f, my = 0.0f, mz = 0.0f;
-            if (sl[u].key == k[u]) {
-                mx = voxel_mean_axis(k[u] % nx, sl[u].sum[0], sl[u].cnt, g.voxel_size, g.origin[0]);
-                my = voxel_mean_axis((k[u] / nx) % ny, sl[u].sum[1], sl[u].cnt, g.voxel_size, g.origin[1]);
-                mz = voxel_mean_axis(k[u] / (nx * ny), sl[u].sum[2], sl[u].cnt, g.voxel_size, g.origin[2]);
-            }
-            cl_key[i] = k[u];
-            cl_x[i] = mx;
-            cl_y[i] = my;
-            cl_z[i] = mz;
+            __syncthreads();   // place is reused by the next step
         }
     }
 }
@@ -779,30 +975,51 @@ hipError_t launch_ccl(const Geom& g, const uint32_t* bits, SegBuffers& b, uint32
     return hipGetLastError();
 }
 
+// words of the sort's histograms and digit totals
+size_t group_hist_words(uint64_t cap)
+{
+    return (size_t)kSortBins * (std::min<uint64_t>((cap + kSortStep - 1) / kSortStep, kSortTiles) + 1);
+}
+
 hipError_t launch_group(const Geom& g, const Hash& h, SegBuffers& b, uint32_t cap, uint32_t min_cluster,
                         uint32_t* d_labels, DevCounters* ctr, hipStream_t s)
 {
     StageScope t(VM_STAGE_GROUP, s);
-    const int grid = grid_for(cap);
     if (min_cluster < 1) min_cluster = 1;
-    uint32_t* cid = b.scan_a;
-    uint32_t* keep = b.sort_k[1];
     const GroupF f{b.parent, b.csize, min_cluster};
-    const GroupG gg{cid, keep, b.cl_off, b.cl_tag, b.occ_key, ctr};
-    Vec<3>* tiles = reinterpret_cast<Vec<3>*>(b.blk);
-    tile_scan<3>(f, gg, &ctr->n_occ, cap, tiles, s);
-    hipError_t e;
-    k_group_pairs<<<grid, kBlock, 0, s>>>(ctr, b.parent, b.csize, min_cluster, cid, keep, b.occ_key, b.sort_k[0],
-                                          b.sort_v[0]);
-    // stable sort by cluster id keeps ascending keys inside each cluster
-    const uint32_t kbound = cap / min_cluster + 1;
-    const int bits_needed = 32 - __builtin_clz(kbound | 1u);
-    if ((e = radix_sort_pairs_dev(b.sort_k, b.sort_v, &ctr->meta[1], cap, bits_needed, &ctr->kmax, b.hist, b.blk,
-                                  &ctr->group_sel, s)) != hipSuccess)
-        return e;
-    k_group_gather<<<grid_for((cap + kGatherU - 1) / kGatherU, kBlock, 2048), kBlock, 0, s>>>(
-        g, h, ctr, b.sort_v[0], b.sort_v[1], b.cl_key, b.cl_x, b.cl_y, b.cl_z);
-    if (d_labels) k_labels<<<grid, kBlock, 0, s>>>(ctr, b.parent, b.occ_key, d_labels);
+    const GroupG gg{b.parent, b.scan_a, b.cl_off, b.cl_tag, b.occ_key, ctr};
+    tile_scan<2>(f, gg, &ctr->n_occ, cap, reinterpret_cast<Vec<2>*>(b.blk), s);
+    GroupSort a;
+    a.ctr = ctr;
+    a.parent = b.parent;
+    a.cid = b.scan_a;
+    a.occ_key = b.occ_key;
+    for (int i = 0; i < 2; ++i) {
+        a.k[i] = b.sort_k[i];
+        a.v[i] = b.sort_v[i];
+    }
+    a.hist = b.hist;
+    a.tot = b.hist + (group_hist_words(cap) - kSortBins);
+    a.g = g;
+    a.h = h;
+    a.cl_key = b.cl_key;
+    a.cl_x = b.cl_x;
+    a.cl_y = b.cl_y;
+    a.cl_z = b.cl_z;
+    int tgrid = grid_for(cap, (int)kSortStep, (int)kSortTiles), dgrid = (int)kSortBins;
+    k_group_hist<true><<<tgrid, kBlock, 0, s>>>(a, 0);
+    k_group_rows<<<dgrid, kBlock, 0, s>>>(a, 0);
+    k_group_scatter<true><<<tgrid, kBlock, 0, s>>>(a, 0);
+    // the further passes mostly have nothing to do: small grids end sooner
+    tgrid = std::min(tgrid, 512);
+    dgrid = 512;
+    const uint32_t kmax = cap / min_cluster;   // no more clusters than this
+    for (int shift = kSortBits; shift < 32 && kmax >> shift; shift += kSortBits) {
+        k_group_hist<false><<<tgrid, kBlock, 0, s>>>(a, shift);
+        k_group_rows<<<dgrid, kBlock, 0, s>>>(a, shift);
+        k_group_scatter<false><<<tgrid, kBlock, 0, s>>>(a, shift);
+    }
+    if (d_labels) k_labels<<<grid_for(cap), kBlock, 0, s>>>(ctr, b.parent, b.occ_key, d_labels);
     return hipGetLastError();
 }
 

@@ -27,10 +27,7 @@ struct DevCounters {
     uint32_t meta[2];                 // clusters view: [0] K, [1] total points
     uint32_t kmax;                    // largest cluster id (K - 1, or 0)
     uint32_t sort_n;                  // points in the current sorted insert batch
-    uint32_t sort_max;                // largest sort key of that batch (2^bits - 1)
     unsigned long long touched;       // distinct voxels updated by the last insert call
-    uint32_t sort_sel;                // buffer (0/1) holding the sorted insert batch
-    uint32_t group_sel;               // buffer (0/1) holding the voxels sorted by cluster
     unsigned long long cleared;       // voxels cleared by ray casting since create/clear
     unsigned long long shifted_out;   // voxels dropped by grid shifts since create/clear
     uint32_t rays[2];                 // lines listed by the clearing pass (batches in turn)
@@ -253,24 +250,13 @@ inline int grid_for(uint64_t n, int block = kBlock, int max_grid = 8192)
     return (int)g;
 }
 
-// ---- scans and sorts (vm_scan.hip) ----------------------------------------
+// ---- scans (vm_scan.hip) ---------------------------------------------------
 // Exclusive prefix sum of n u32 values (n read from *d_n on the device, at
 // most n_cap; or n = n_cap when d_n is null), in place allowed (in == out).  Writes the total to *d_total if
 // non-null.  `blk` needs scan_blk_words(n_cap) words.
 size_t scan_blk_words(uint64_t n_cap);
 hipError_t scan_exclusive_dev(const uint32_t* in, uint32_t* out, const uint32_t* d_n, uint32_t n_cap,
                               uint32_t* d_total, uint32_t* blk, hipStream_t s);
-
-// Stable LSD radix sort of (key, value) pairs by the low `bits` bits of key;
-// n from *d_n (<= n_cap).  Every key is at most *d_max_key; a pass whose
-// digit and all higher digits of that bound are zero does nothing (the
-// passes that run are the first ones).  The result lands in keys[r]/vals[r] with r = *d_sel, written on
-// the device.  `hist` needs radix_hist_words(n_cap) words, `blk` as for the
-// scan.
-size_t radix_hist_words(uint64_t n_cap);
-hipError_t radix_sort_pairs_dev(uint32_t* keys[2], uint32_t* vals[2], const uint32_t* d_n, uint32_t n_cap,
-                                int bits, const uint32_t* d_max_key, uint32_t* hist, uint32_t* blk,
-                                uint32_t* d_sel, hipStream_t s);
 
 // Scratch of the grouped insert path (sized for `cap` points per batch).
 struct InsertScratch {
@@ -305,6 +291,7 @@ hipError_t launch_import(const Geom& g, const Hash& h, uint32_t* bits, DevCounte
 // ---- CCL and grouping (vm_ccl.hip) --------------------------------------------
 hipError_t launch_ccl(const Geom& g, const uint32_t* bits, SegBuffers& b, uint32_t cap, DevCounters* ctr,
                       hipStream_t s);
+size_t group_hist_words(uint64_t cap);   // words of launch_group's histograms
 hipError_t launch_group(const Geom& g, const Hash& h, SegBuffers& b, uint32_t cap, uint32_t min_cluster,
                         uint32_t* d_labels, DevCounters* ctr, hipStream_t s);
 

@@ -191,21 +191,28 @@ __global__ void __launch_bounds__(kBlock) k_tile_down(F f, G g, const uint32_t* 
     if (threadIdx.x == 0 && base + kTsTile >= n) g.total(all);
 }
 
-// exclusive scan of the tile totals in place (one workgroup), for grids of
-// more than kTsDirectTiles tiles
+// Exclusive scan of the tile totals in place (one workgroup), for grids of
+// more than kTsDirectTiles tiles; only the tiles that hold items (7.9M items
+// in room for 33M: 105 us over all tiles, 256 a step, 6.5 us so).
 template <int N>
-__global__ void __launch_bounds__(kBlock) k_tile_totals(Vec<N>* blk, uint32_t ntiles)
+__global__ void __launch_bounds__(kOneBlockThreads) k_tile_totals(Vec<N>* blk, const uint32_t* d_n, uint32_t n_fixed)
 {
-    __shared__ Vec<N> lds[kBlock / kWave];
-    Vec<N> carry = vzero<N>();
-    for (uint32_t b0 = 0; b0 < ntiles; b0 += kBlock) {
-        const uint32_t t = b0 + threadIdx.x;
-        const Vec<N> x = t < ntiles ? blk[t] : vzero<N>();
-        Vec<N> tot;
-        const Vec<N> ex = ts_block_excl(x, lds, &tot);
-        if (t < ntiles) blk[t] = vadd(carry, ex);
-        carry = vadd(carry, tot);
-    }
+    const uint32_t n = d_n ? min(*d_n, n_fixed) : n_fixed;
+    uint32_t total[N];
+    one_block_scan<kOneBlockThreads, 4, N>(
+        (uint32_t)(((uint64_t)n + kTsTile - 1) / kTsTile),
+        [&](uint32_t t, uint32_t(&v)[N]) {
+            const Vec<N> x = blk[t];
+#pragma unroll
+            for (int q = 0; q < N; ++q) v[q] = x.v[q];
+        },
+        [&](uint32_t t, const uint32_t(&e)[N]) {
+            Vec<N> x;
+#pragma unroll
+            for (int q = 0; q < N; ++q) x.v[q] = e[q];
+            blk[t] = x;
+        },
+        total);
 }
 
 // The two (or three) launches of a fused scan over n_fixed item slots.
@@ -215,7 +222,7 @@ inline void tile_scan(F f, G g, const uint32_t* d_n, uint32_t n_fixed, Vec<N>* b
     const uint32_t nt = ts_tiles(n_fixed);
     const bool scanned = nt > kTsDirectTiles;
     k_tile_reduce<N><<<nt, kBlock, 0, s>>>(f, d_n, n_fixed, blk);
-    if (scanned) k_tile_totals<N><<<1, kBlock, 0, s>>>(blk, nt);
+    if (scanned) k_tile_totals<N><<<1, kOneBlockThreads, 0, s>>>(blk, d_n, n_fixed);
     k_tile_down<N><<<nt, kBlock, 0, s>>>(f, g, d_n, n_fixed, blk, scanned);
 }
 
