@@ -301,7 +301,7 @@ vm_status vm_map_create(const vm_map_desc* d, vm_map* out)
     A((void**)&b.cl_z, cap * 4);
     A((void**)&b.wrank, ((size_t)m->g.nwords + 1) * 4);
     const uint32_t batch = 1u << (d->insert_batch_log2 ? d->insert_batch_log2 : 22);
-    const uint64_t scan_n = std::max<uint64_t>(std::max<uint64_t>(cap, m->g.nwords), bucket_hist_words(batch));
+    const uint64_t scan_n = std::max<uint64_t>(cap, m->g.nwords);
     // scan partials; also the fused scans' per-tile totals (3 words per 1024 items)
     A((void**)&b.blk, std::max<size_t>(scan_blk_words(scan_n), 3 * (size_t)ts_tiles(scan_n)) * 4);
     A((void**)&b.hist, group_hist_words(cap) * 4);
@@ -309,9 +309,7 @@ vm_status vm_map_create(const vm_map_desc* d, vm_map* out)
     ins.cap = batch;
     A((void**)&ins.key, (size_t)batch * 4);
     A((void**)&ins.rec, (size_t)batch * 16);
-    A((void**)&ins.packed, (size_t)batch * 8);
     A((void**)&ins.hist, bucket_hist_words(batch) * 4);
-    ins.blk = b.blk;
     if (st != VM_OK) {
         map_free_all(m);
         delete m;

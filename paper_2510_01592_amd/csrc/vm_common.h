@@ -26,7 +26,7 @@ struct DevCounters {
     uint32_t n_occ;                   // occupied voxels ranked by the last rank pass
     uint32_t meta[2];                 // clusters view: [0] K, [1] total points
     uint32_t kmax;                    // largest cluster id (K - 1, or 0)
-    uint32_t sort_n;                  // points in the current sorted insert batch
+    uint32_t pad0;
     unsigned long long touched;       // distinct voxels updated by the last insert call
     unsigned long long cleared;       // voxels cleared by ray casting since create/clear
     unsigned long long shifted_out;   // voxels dropped by grid shifts since create/clear
@@ -260,11 +260,9 @@ hipError_t scan_exclusive_dev(const uint32_t* in, uint32_t* out, const uint32_t*
 
 // Scratch of the grouped insert path (sized for `cap` points per batch).
 struct InsertScratch {
-    uint32_t* key;                // [cap] voxel key of each point (kEmpty if dropped)
-    unsigned long long* packed;   // [cap] fixed-point offsets of each point, 20 bits per axis
-    uint4* rec;                   // [cap] (key, offsets) records grouped by bucket
-    uint32_t* hist;               // bucket histograms, bucket-major
-    uint32_t* blk;
+    uint32_t* key;    // [cap] end cells of the clearing pass
+    uint4* rec;       // [cap] records (key, offsets) grouped by bucket
+    uint32_t* hist;   // buckets of each partition workgroup, bucket totals and starts
     uint32_t cap;
 };
 

@@ -20,34 +20,48 @@ namespace {
 // blocks; threads stride over the points.
 constexpr int kMapGrid = 1024;
 
+// A point's voxel and its offsets in it (20 bits per axis): map_from_sensor in
+// fp64, one fused chain per output coordinate, then whole steps of s * 2^-20
+// from the origin, split exactly (a step's number has at most 52 bits, so the
+// products with 2^-20 and 2^20 and the difference are exact).  False outside
+// the grid; the negated range tests also reject NaN.
+struct Cell {
+    uint32_t key, off[3];
+};
+
+__device__ __forceinline__ bool cell_of(const Pose& pose, const Geom& g, float x, float y, float z, Cell* c)
+{
+    const double px = (double)x, py = (double)y, pz = (double)z;
+    const double wx = fma(pose.R[2], pz, fma(pose.R[1], py, fma(pose.R[0], px, pose.t[0])));
+    const double wy = fma(pose.R[5], pz, fma(pose.R[4], py, fma(pose.R[3], px, pose.t[1])));
+    const double wz = fma(pose.R[8], pz, fma(pose.R[7], py, fma(pose.R[6], px, pose.t[2])));
+    const double fx = floor((wx - g.origin[0]) * g.inv_q);
+    const double fy = floor((wy - g.origin[1]) * g.inv_q);
+    const double fz = floor((wz - g.origin[2]) * g.inv_q);
+    if (!(fx >= 0.0 && fx < (double)g.dims[0] * 0x1p20 && fy >= 0.0 && fy < (double)g.dims[1] * 0x1p20 && fz >= 0.0 &&
+          fz < (double)g.dims[2] * 0x1p20))
+        return false;
+    const double cx = floor(fx * 0x1p-20), cy = floor(fy * 0x1p-20), cz = floor(fz * 0x1p-20);
+    c->key = (uint32_t)cx + (uint32_t)g.dims[0] * ((uint32_t)cy + (uint32_t)g.dims[1] * (uint32_t)cz);
+    c->off[0] = (uint32_t)(fx - cx * 0x1p20);
+    c->off[1] = (uint32_t)(fy - cy * 0x1p20);
+    c->off[2] = (uint32_t)(fz - cz * 0x1p20);
+    return true;
+}
+
 __global__ void __launch_bounds__(kBlock) k_insert(const float* __restrict__ xyz, int64_t n, Pose pose, Geom g,
                                                    Hash h, uint32_t* __restrict__ bits,
                                                    DevCounters* __restrict__ ctr)
 {
     uint32_t n_in = 0, n_drop = 0, n_lost = 0, n_new = 0;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const double lim0 = (double)g.dims[0] * 1048576.0;
-    const double lim1 = (double)g.dims[1] * 1048576.0;
-    const double lim2 = (double)g.dims[2] * 1048576.0;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const double px = (double)xyz[3 * i + 0];
-        const double py = (double)xyz[3 * i + 1];
-        const double pz = (double)xyz[3 * i + 2];
-        // map_from_sensor in fp64, one fused chain per output coordinate
-        const double wx = fma(pose.R[2], pz, fma(pose.R[1], py, fma(pose.R[0], px, pose.t[0])));
-        const double wy = fma(pose.R[5], pz, fma(pose.R[4], py, fma(pose.R[3], px, pose.t[1])));
-        const double wz = fma(pose.R[8], pz, fma(pose.R[7], py, fma(pose.R[6], px, pose.t[2])));
-        const double fx = floor((wx - g.origin[0]) * g.inv_q);
-        const double fy = floor((wy - g.origin[1]) * g.inv_q);
-        const double fz = floor((wz - g.origin[2]) * g.inv_q);
-        // negated range tests also reject NaN
-        if (!(fx >= 0.0 && fx < lim0 && fy >= 0.0 && fy < lim1 && fz >= 0.0 && fz < lim2)) {
+        Cell c;
+        if (!cell_of(pose, g, xyz[3 * i + 0], xyz[3 * i + 1], xyz[3 * i + 2], &c)) {
             ++n_drop;
             continue;
         }
-        const int64_t qx = (int64_t)fx, qy = (int64_t)fy, qz = (int64_t)fz;
-        const uint32_t key = (uint32_t)((uint64_t)(qx >> 20) +
-                                        (uint64_t)g.dims[0] * ((uint64_t)(qy >> 20) + (uint64_t)g.dims[1] * (uint64_t)(qz >> 20)));
+        const uint32_t key = c.key;
         // find or claim the key's slot
         uint32_t s = hash_slot(key, h.log2cap);
         bool ok = false;
@@ -72,9 +86,9 @@ __global__ void __launch_bounds__(kBlock) k_insert(const float* __restrict__ xyz
             atomicOr(&bits[key >> 5], 1u << (key & 31));
             ++n_new;
         }
-        atomicAdd(&sl->sum[0], (unsigned long long)(qx & 0xFFFFF));
-        atomicAdd(&sl->sum[1], (unsigned long long)(qy & 0xFFFFF));
-        atomicAdd(&sl->sum[2], (unsigned long long)(qz & 0xFFFFF));
+        atomicAdd(&sl->sum[0], (unsigned long long)c.off[0]);
+        atomicAdd(&sl->sum[1], (unsigned long long)c.off[1]);
+        atomicAdd(&sl->sum[2], (unsigned long long)c.off[2]);
         ++n_in;
     }
     {
@@ -85,24 +99,27 @@ __global__ void __launch_bounds__(kBlock) k_insert(const float* __restrict__ xyz
     if (n_lost) atomicOr(&ctr->flags, (uint32_t)VM_FLAG_HASH_FULL);
 }
 
-// ---- sorted insert path -------------------------------------------------------
-// 1. voxelise every point: (key, point index) pairs plus its packed offsets;
-//    points outside the grid get a key above every valid one.
-
-// 3. after the sort by key: one lane per run of equal keys sums the run and
-//    updates the voxel's slot once.  Every key occurs in one run only, so no
-//    other lane touches that slot in this pass: the payload is a plain
-//    read-modify-write; only claiming an empty slot needs a CAS.
 // ---- grouped insert (large calls) ---------------------------------------------
-// The points of a batch are voxelised, partitioned into hash buckets of about
-// kBucketAvg points (a bucket is a range of home slots of the map's hash, so
-// every point of a voxel lands in the same bucket), and each bucket is then
-// aggregated by one workgroup in an LDS table: one slot update per distinct
-// voxel, a plain read-modify-write since no other workgroup touches those
-// voxels.
-constexpr uint32_t kBucketTile = 4096;    // points per workgroup in the partition passes (at least)
-constexpr int kPartBlock = 1024;          // partition workgroup: 16 waves, four points per thread per tile
-constexpr uint32_t kBucketBlocks = 1024;  // partition workgroups per batch (at most)
+// The points of a batch are partitioned into hash buckets of about kBucketAvg
+// points (a bucket is a range of home slots of the map's hash, so every point
+// of a voxel lands in the same bucket), and each bucket is then aggregated by
+// one workgroup in an LDS table: one slot update per distinct voxel, a plain
+// read-modify-write since no other workgroup touches those voxels.
+//   count:   a workgroup counts the buckets of its points, a row of the
+//            histogram;
+//   cols:    each bucket's column becomes prefixes and a total;
+//   scatter: the points are voxelised a second time (their 12 bytes are read
+//            again, from the cache for a frame, instead of 12 written and read)
+//            and go to their buckets as 16-byte records;
+//   insert.
+// Rows are written and read whole: with a row per bucket the workgroups'
+// words lay scattered, and two scan kernels passed over them (4M points: count
+// 57 us, scan 34, scatter 81; now
+// 24, 5, 69; 1M points: 14, 14, 16; now 11, 4, 16).
+constexpr int kPartBlock = 1024;          // partition workgroup: 16 waves
+constexpr uint32_t kPartAhead = 4;        // points a thread has in flight
+constexpr uint32_t kBucketBlocks = 256;   // partition workgroups per batch, at most: one per compute unit
+                                          // (512: 3 to 5 us longer for 0.3M and 1M points, the same for 4M)
 constexpr uint32_t kBucketAvg = 512;      // target points per bucket
 constexpr uint32_t kBucketMaxLog2 = 12;   // at most 4096 buckets (LDS counters)
 constexpr uint32_t kBucketChunk = 1024;   // points aggregated per LDS table fill
@@ -110,7 +127,6 @@ constexpr uint32_t kBucketTableLog2 = 10;
 constexpr uint32_t kBucketTable = 1u << kBucketTableLog2;   // LDS table slots: 20 KB, so eight workgroups
                                                              // fit on a CU; a bucket averages kBucketAvg
                                                              // points, so the table is about half full
-static_assert(kBucketTile % kPartBlock == 0, "whole rows of points per partition workgroup");
 static_assert(kBucketTable >= kBucketChunk, "a chunk's distinct keys always fit: every probe ends");
 constexpr uint32_t kRecPerThread = kBucketChunk / kBlock;   // records per thread per fill
 constexpr uint32_t kSlotPerThread = kBucketTable / kBlock;  // table entries per thread
@@ -128,11 +144,32 @@ __device__ __forceinline__ uint32_t table_slot(uint32_t key)
     return (key * 0xCC9E2D51u) >> (32 - kBucketTableLog2);
 }
 
-__global__ void __launch_bounds__(kPartBlock) k_vox_bucket(const float* __restrict__ xyz, uint32_t n, Pose pose, Geom g,
-                                                       uint32_t lb, uint32_t nblk, uint32_t tile, bool first_batch,
-                                                       uint32_t* __restrict__ key_out,
-                                                       unsigned long long* __restrict__ packed,
-                                                       uint32_t* __restrict__ hist, DevCounters* __restrict__ ctr)
+// f(in the grid, cell) for the points of workgroup blockIdx.x's tile
+template <class F>
+__device__ __forceinline__ void each_point(const float* __restrict__ xyz, uint32_t n, const Pose& pose, const Geom& g,
+                                           uint32_t tile, F f)
+{
+    const uint32_t i0 = blockIdx.x * tile, end = min(n - i0, tile) + i0;   // (the grid covers n: i0 < n)
+    for (uint32_t b = i0 + threadIdx.x; b < end; b += kPartAhead * kPartBlock) {
+        float x[kPartAhead], y[kPartAhead], z[kPartAhead];
+#pragma unroll
+        for (uint32_t u = 0; u < kPartAhead; ++u) {
+            const size_t i = min(b + u * kPartBlock, end - 1u);
+            x[u] = xyz[3 * i + 0];
+            y[u] = xyz[3 * i + 1];
+            z[u] = xyz[3 * i + 2];
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < kPartAhead; ++u) {
+            Cell c;
+            if (b + u * kPartBlock < end) f(cell_of(pose, g, x[u], y[u], z[u], &c), c);
+        }
+    }
+}
+
+__global__ void __launch_bounds__(kPartBlock) k_bucket_count(const float* __restrict__ xyz, uint32_t n, Pose pose,
+                                                             Geom g, uint32_t lb, uint32_t tile, bool first_batch,
+                                                             uint32_t* __restrict__ hist, DevCounters* __restrict__ ctr)
 {
     __shared__ uint32_t cnt[1u << kBucketMaxLog2];
     const uint32_t B = 1u << lb;
@@ -140,85 +177,95 @@ __global__ void __launch_bounds__(kPartBlock) k_vox_bucket(const float* __restri
     if (blockIdx.x == 0 && threadIdx.x == 0 && first_batch) ctr->touched = 0;
     __syncthreads();
     uint32_t n_in = 0, n_drop = 0;
-    const double lim0 = (double)g.dims[0] * 1048576.0;
-    const double lim1 = (double)g.dims[1] * 1048576.0;
-    const double lim2 = (double)g.dims[2] * 1048576.0;
-    const uint64_t base = (uint64_t)blockIdx.x * tile;
-    for (uint32_t j = 0; j < tile / kPartBlock; ++j) {
-        const uint64_t i = base + (uint64_t)j * kPartBlock + threadIdx.x;
-        if (i >= n) break;
-        const double px = (double)xyz[3 * (size_t)i + 0];
-        const double py = (double)xyz[3 * (size_t)i + 1];
-        const double pz = (double)xyz[3 * (size_t)i + 2];
-        const double wx = fma(pose.R[2], pz, fma(pose.R[1], py, fma(pose.R[0], px, pose.t[0])));
-        const double wy = fma(pose.R[5], pz, fma(pose.R[4], py, fma(pose.R[3], px, pose.t[1])));
-        const double wz = fma(pose.R[8], pz, fma(pose.R[7], py, fma(pose.R[6], px, pose.t[2])));
-        const double fx = floor((wx - g.origin[0]) * g.inv_q);
-        const double fy = floor((wy - g.origin[1]) * g.inv_q);
-        const double fz = floor((wz - g.origin[2]) * g.inv_q);
-        uint32_t key = kEmpty;
-        unsigned long long pk = 0;
-        // negated range tests also reject NaN
-        if (fx >= 0.0 && fx < lim0 && fy >= 0.0 && fy < lim1 && fz >= 0.0 && fz < lim2) {
-            const int64_t qx = (int64_t)fx, qy = (int64_t)fy, qz = (int64_t)fz;
-            key = (uint32_t)((uint64_t)(qx >> 20) +
-                             (uint64_t)g.dims[0] * ((uint64_t)(qy >> 20) + (uint64_t)g.dims[1] * (uint64_t)(qz >> 20)));
-            pk = (unsigned long long)(qx & 0xFFFFF) | ((unsigned long long)(qy & 0xFFFFF) << 20) |
-                 ((unsigned long long)(qz & 0xFFFFF) << 40);
-            atomicAdd(&cnt[bucket_of(key, lb)], 1u);
+    each_point(xyz, n, pose, g, tile, [&](bool in, const Cell& c) {
+        if (in) {
+            atomicAdd(&cnt[bucket_of(c.key, lb)], 1u);
             ++n_in;
         } else {
             ++n_drop;
         }
-        key_out[i] = key;
-        packed[i] = pk;
-    }
+    });
     __syncthreads();
-    for (uint32_t b = threadIdx.x; b < B; b += kPartBlock) hist[(uint64_t)b * nblk + blockIdx.x] = cnt[b];
+    for (uint32_t b = threadIdx.x; b < B; b += kPartBlock) hist[(size_t)blockIdx.x * B + b] = cnt[b];
     unsigned long long* const dst[2] = {&ctr->points_in, &ctr->points_dropped};
     const uint32_t v[2] = {n_in, n_drop};
     block_add_counters<2, kPartBlock>(dst, v);
 }
 
-// Points to their buckets (hist holds the exclusive scan, bucket-major).
-__global__ void __launch_bounds__(kPartBlock) k_bucket_scatter(const uint32_t* __restrict__ key_in,
-                                                           const unsigned long long* __restrict__ packed, uint32_t n,
-                                                           uint32_t lb, uint32_t nblk, uint32_t tile,
-                                                           const uint32_t* __restrict__ hist,
-                                                           uint4* __restrict__ rec_out)
+// Columns of the histogram (B buckets, a row per partition workgroup): each
+// workgroup takes 32 of them, its 32 groups of lanes an equal share of the rows.
+constexpr uint32_t kCols = 32;
+constexpr uint32_t kColRows = kBucketBlocks / (kPartBlock / kCols);   // rows of a thread, at most
+
+__global__ void __launch_bounds__(kPartBlock) k_bucket_cols(uint32_t* __restrict__ hist, uint32_t B, uint32_t nblk,
+                                                            uint32_t* __restrict__ total)
+{
+    constexpr uint32_t kGroups = kPartBlock / kCols;
+    __shared__ uint32_t sum[kGroups][kCols];
+    const uint32_t col = threadIdx.x % kCols, grp = threadIdx.x / kCols;
+    const uint32_t b = blockIdx.x * kCols + col, rows = (nblk + kGroups - 1) / kGroups, r0 = grp * rows;
+    uint32_t v[kColRows], s = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < kColRows; ++j) {
+        v[j] = j < rows && r0 + j < nblk && b < B ? hist[(size_t)(r0 + j) * B + b] : 0u;
+        s += v[j];
+    }
+    sum[grp][col] = s;
+    __syncthreads();
+    uint32_t run = 0;
+    for (uint32_t q = 0; q < grp; ++q) run += sum[q][col];
+    if (b >= B) return;
+    if (grp == kGroups - 1) total[b] = run + s;
+#pragma unroll
+    for (uint32_t j = 0; j < kColRows; ++j) {
+        if (j < rows && r0 + j < nblk) hist[(size_t)(r0 + j) * B + b] = run;
+        run += v[j];
+    }
+}
+
+// Points to their buckets; workgroup 0 also writes where the buckets start
+// (start[B]: the points in the grid).
+__global__ void __launch_bounds__(kPartBlock) k_bucket_scatter(const float* __restrict__ xyz, uint32_t n, Pose pose,
+                                                               Geom g, uint32_t lb, uint32_t tile,
+                                                               const uint32_t* __restrict__ hist,
+                                                               const uint32_t* __restrict__ total,
+                                                               uint32_t* __restrict__ start,
+                                                               uint4* __restrict__ rec_out)
 {
     __shared__ uint32_t pos[1u << kBucketMaxLog2];
     const uint32_t B = 1u << lb;
-    for (uint32_t b = threadIdx.x; b < B; b += kPartBlock) pos[b] = hist[(uint64_t)b * nblk + blockIdx.x];
+    const uint32_t* row = hist + (size_t)blockIdx.x * B;
+    uint32_t all[1];
+    one_block_scan<kPartBlock, 4, 1>(
+        B, [&](uint32_t b, uint32_t(&v)[1]) { v[0] = total[b]; },
+        [&](uint32_t b, const uint32_t(&e)[1]) {
+            pos[b] = e[0] + row[b];
+            if (blockIdx.x == 0) start[b] = e[0];
+        },
+        all);
+    if (blockIdx.x == 0 && threadIdx.x == 0) start[B] = all[0];
     __syncthreads();
-    const uint64_t base = (uint64_t)blockIdx.x * tile;
-    for (uint32_t j = 0; j < tile / kPartBlock; ++j) {
-        const uint64_t i = base + (uint64_t)j * kPartBlock + threadIdx.x;
-        if (i >= n) break;
-        const uint32_t k = key_in[i];
-        if (k == kEmpty) continue;
-        const unsigned long long pk = packed[i];
-        const uint32_t p = atomicAdd(&pos[bucket_of(k, lb)], 1u);
-        rec_out[p] = make_uint4(k, (uint32_t)pk, (uint32_t)(pk >> 32), 0u);   // one 16-byte store
-    }
+    each_point(xyz, n, pose, g, tile, [&](bool in, const Cell& c) {
+        if (!in) return;
+        const uint32_t p = atomicAdd(&pos[bucket_of(c.key, lb)], 1u);
+        rec_out[p] = make_uint4(c.key, c.off[0], c.off[1], c.off[2]);   // one 16-byte store
+    });
 }
 
 // One workgroup per bucket: sum its points per voxel in LDS (at most
 // kBucketChunk points per fill, so the 32-bit sums of 20-bit offsets cannot
 // overflow), then update each voxel's slot once per fill.
-__global__ void __launch_bounds__(kBlock) k_bucket_insert(const uint4* __restrict__ rec, uint32_t lb, uint32_t nblk,
-                                                          const uint32_t* __restrict__ hist, Hash h,
+__global__ void __launch_bounds__(kBlock) k_bucket_insert(const uint4* __restrict__ rec, uint32_t lb,
+                                                          const uint32_t* __restrict__ first, Hash h,
                                                           uint32_t* __restrict__ bits, DevCounters* __restrict__ ctr)
 {
     __shared__ uint32_t tkey[kBucketTable];
     __shared__ uint32_t tcnt[kBucketTable];
     __shared__ uint32_t tsum[3][kBucketTable];
     const uint32_t B = 1u << lb;
-    const uint32_t total = ctr->sort_n;
     uint32_t n_lost = 0, n_new = 0, n_upd = 0;
     for (uint32_t b = blockIdx.x; b < B; b += gridDim.x) {
-        const uint32_t start = hist[(uint64_t)b * nblk];
-        const uint32_t end = b + 1 < B ? hist[(uint64_t)(b + 1) * nblk] : total;
+        const uint32_t start = first[b], end = first[b + 1];
         for (uint32_t c0 = start; c0 < end; c0 += kBucketChunk) {
             const uint32_t c1 = min(end, c0 + kBucketChunk);
             for (uint32_t q = threadIdx.x; q < kBucketTable; q += kBlock) {
@@ -239,7 +286,6 @@ __global__ void __launch_bounds__(kBlock) k_bucket_insert(const uint4* __restric
             for (uint32_t u = 0; u < kRecPerThread; ++u) {
                 if (c0 + threadIdx.x + u * kBlock >= c1) continue;
                 const uint32_t k = rr[u].x;
-                const unsigned long long pk = (unsigned long long)rr[u].y | ((unsigned long long)rr[u].z << 32);
                 uint32_t q = table_slot(k);
                 for (;;) {   // at most kBucketChunk keys in a table of kBucketTable slots: ends
                     const uint32_t old = atomicCAS(&tkey[q], kEmpty, k);
@@ -247,9 +293,9 @@ __global__ void __launch_bounds__(kBlock) k_bucket_insert(const uint4* __restric
                     q = (q + 1) & (kBucketTable - 1);
                 }
                 atomicAdd(&tcnt[q], 1u);
-                atomicAdd(&tsum[0][q], (uint32_t)(pk & 0xFFFFF));
-                atomicAdd(&tsum[1][q], (uint32_t)((pk >> 20) & 0xFFFFF));
-                atomicAdd(&tsum[2][q], (uint32_t)((pk >> 40) & 0xFFFFF));
+                atomicAdd(&tsum[0][q], rr[u].y);
+                atomicAdd(&tsum[1][q], rr[u].z);
+                atomicAdd(&tsum[2][q], rr[u].w);
             }
             __syncthreads();
             // the thread's kSlotPerThread table entries: first probes (whole
@@ -487,29 +533,44 @@ __global__ void __launch_bounds__(kBlock) k_scroll_scatter(Hash h, uint32_t* __r
 {
     uint32_t n_new = 0, n_out = 0, n_lost = 0;
     const uint32_t V = ctr->n_occ;
-    for (uint32_t r = blockIdx.x * blockDim.x + threadIdx.x; r < V; r += gridDim.x * blockDim.x) {
-        const uint32_t k = st.key[r];
-        if (k == kEmpty) {
-            ++n_out;
-            continue;
-        }
-        uint32_t s = hash_slot(k, h.log2cap);
+    const int lane = threadIdx.x & (kWave - 1);
+    for (uint32_t b0 = blockIdx.x * blockDim.x + (threadIdx.x & ~(kWave - 1)); b0 < V; b0 += gridDim.x * blockDim.x) {
+        const uint32_t r = b0 + (uint32_t)lane, k = r < V ? st.key[r] : kEmpty;
         bool ok = false;
-        for (uint32_t p = 0; p < kMaxProbe && p <= h.mask; ++p) {
-            const uint32_t old = atomicCAS(&h.slot[s].key, kEmpty, k);
-            if (old == kEmpty) { ok = true; break; }   // keys are distinct: never old == k
-            s = (s + 1) & h.mask;
+        if (k != kEmpty) {
+            uint32_t sum[6];
+            const uint32_t cnt = st.cnt[r];   // (read while the slot is claimed)
+#pragma unroll
+            for (int a = 0; a < 6; ++a) sum[a] = st.s[a][r];
+            uint32_t s = hash_slot(k, h.log2cap);
+            for (uint32_t p = 0; p < kMaxProbe && p <= h.mask; ++p) {
+                const uint32_t old = atomicCAS(&h.slot[s].key, kEmpty, k);
+                if (old == kEmpty) { ok = true; break; }   // keys are distinct: never old == k
+                s = (s + 1) & h.mask;
+            }
+            if (ok) {
+                Slot* sl = &h.slot[s];
+                sl->cnt = cnt;
+                for (int a = 0; a < 3; ++a)
+                    sl->sum[a] = (unsigned long long)sum[2 * a] | ((unsigned long long)sum[2 * a + 1] << 32);
+                ++n_new;
+            } else {
+                ++n_lost;
+            }
+        } else if (r < V) {
+            ++n_out;
         }
-        if (!ok) {
-            ++n_lost;
-            continue;
+        // the occupancy bits, one atomic per word: a word's voxels are
+        // neighbours in key order
+        const uint32_t w = ok ? k >> 5 : kEmpty;
+        uint32_t m = ok ? 1u << (k & 31) : 0u;
+#pragma unroll
+        for (int d = 1; d < 32; d <<= 1) {   // (a word has at most 32 of them)
+            const uint32_t om = __shfl_up(m, d, kWave), ow = __shfl_up(w, d, kWave);
+            if (lane >= d && ow == w) m |= om;
         }
-        Slot* sl = &h.slot[s];
-        sl->cnt = st.cnt[r];
-        for (int a = 0; a < 3; ++a)
-            sl->sum[a] = (unsigned long long)st.s[2 * a][r] | ((unsigned long long)st.s[2 * a + 1][r] << 32);
-        atomicOr(&bits[k >> 5], 1u << (k & 31));
-        ++n_new;
+        const uint32_t next = __shfl_down(w, 1, kWave);
+        if (ok && (lane == kWave - 1 || next != w)) atomicOr(&bits[w], m);
     }
     {
         unsigned long long* const dst[2] = {&ctr->occupied, &ctr->shifted_out};
@@ -519,15 +580,15 @@ __global__ void __launch_bounds__(kBlock) k_scroll_scatter(Hash h, uint32_t* __r
     if (n_lost) atomicOr(&ctr->flags, (uint32_t)VM_FLAG_HASH_FULL);
 }
 
+// Empty slots, half a slot per thread so that a wave's stores are one row of
+// 1 KB (with a slot per thread each store left gaps: 64 us for 268 MB, 41 so).
 __global__ void __launch_bounds__(kBlock) k_clear_slots(Slot* __restrict__ slot, uint32_t cap)
 {
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < cap; i += gridDim.x * blockDim.x) {
-        Slot z;
-        z.key = kEmpty;
-        z.cnt = 0;
-        z.sum[0] = z.sum[1] = z.sum[2] = 0;
-        slot[i] = z;
-    }
+    static_assert(sizeof(Slot) == 2 * sizeof(uint4) && offsetof(Slot, key) == 0, "halves of a slot");
+    uint4* p = reinterpret_cast<uint4*>(slot);
+    const uint64_t n = 2 * (uint64_t)cap, stride = (uint64_t)gridDim.x * blockDim.x;
+    const uint4 v = make_uint4(threadIdx.x & 1u ? 0u : kEmpty, 0u, 0u, 0u);   // (the stride is even)
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
 }
 
 __global__ void k_stats(const DevCounters* __restrict__ c, uint32_t log2cap, vm_map_stats_t* out)
@@ -560,11 +621,11 @@ uint32_t bucket_log2(uint32_t m)
     return lb;
 }
 
-// points per partition workgroup: kBucketTile, or more so that a batch takes
-// at most kBucketBlocks workgroups (bounds the histogram)
+// points per partition workgroup: as few rows of them as leave at most
+// kBucketBlocks workgroups (bounds the histogram)
 static uint32_t bucket_tile(uint32_t m)
 {
-    uint32_t t = kBucketTile;
+    uint32_t t = kPartBlock;
     while ((uint64_t)t * kBucketBlocks < m) t <<= 1;
     return t;
 }
@@ -573,7 +634,7 @@ size_t bucket_hist_words(uint32_t batch)
 {
     const uint32_t tile = bucket_tile(batch);
     const uint32_t nblk = (batch + tile - 1) / tile;
-    return ((size_t)nblk << bucket_log2(batch)) + 64;
+    return ((size_t)(nblk + 2) << bucket_log2(batch)) + 1;   // rows, totals and starts
 }
 
 hipError_t launch_insert(const float* xyz, int64_t n, const Pose& pose, const Geom& g, const Hash& h,
@@ -590,13 +651,14 @@ hipError_t launch_insert(const float* xyz, int64_t n, const Pose& pose, const Ge
         const uint32_t lb = bucket_log2(m);
         const uint32_t tile = bucket_tile(m);
         const uint32_t nblk = (m + tile - 1) / tile;
-        k_vox_bucket<<<nblk, kPartBlock, 0, s>>>(xyz + 3 * done, m, pose, g, lb, nblk, tile, done == 0, sc.key,
-                                            sc.packed, sc.hist, ctr);
-        hipError_t e = scan_exclusive_dev(sc.hist, sc.hist, nullptr, (nblk << lb), &ctr->sort_n, sc.blk, s);
+        uint32_t* total = sc.hist + ((size_t)nblk << lb);
+        uint32_t* start = total + (1u << lb);
+        k_bucket_count<<<nblk, kPartBlock, 0, s>>>(xyz + 3 * done, m, pose, g, lb, tile, done == 0, sc.hist, ctr);
+        k_bucket_cols<<<((1u << lb) + kCols - 1) / kCols, kPartBlock, 0, s>>>(sc.hist, 1u << lb, nblk, total);
+        k_bucket_scatter<<<nblk, kPartBlock, 0, s>>>(xyz + 3 * done, m, pose, g, lb, tile, sc.hist, total, start, sc.rec);
+        k_bucket_insert<<<1u << lb, kBlock, 0, s>>>(sc.rec, lb, start, h, bits, ctr);
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        k_bucket_scatter<<<nblk, kPartBlock, 0, s>>>(sc.key, sc.packed, m, lb, nblk, tile, sc.hist, sc.rec);
-        k_bucket_insert<<<1u << lb, kBlock, 0, s>>>(sc.rec, lb, nblk, sc.hist, h, bits, ctr);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;
 }
