@@ -39,6 +39,7 @@ struct vm_map_s {
     // per-sweep change flags of label propagation (device) and their host copy
     uint32_t* lp_flags = nullptr;
     uint32_t* lp_host = nullptr;
+    uint32_t* n_host = nullptr;   // pinned: the number of voxels an export found
 };
 
 namespace vm {
@@ -144,6 +145,8 @@ void map_free_all(vm_map m)
     m->lp_flags = nullptr;
     if (m->lp_host) (void)hipHostFree(m->lp_host);
     m->lp_host = nullptr;
+    if (m->n_host) (void)hipHostFree(m->n_host);
+    m->n_host = nullptr;
 }
 
 bool step_params_ok(const vm_step_params* sp)
@@ -302,14 +305,19 @@ vm_status vm_map_create(const vm_map_desc* d, vm_map* out)
     A((void**)&b.wrank, ((size_t)m->g.nwords + 1) * 4);
     const uint32_t batch = 1u << (d->insert_batch_log2 ? d->insert_batch_log2 : 22);
     const uint64_t scan_n = std::max<uint64_t>(cap, m->g.nwords);
-    // scan partials; also the fused scans' per-tile totals (3 words per 1024 items)
-    A((void**)&b.blk, std::max<size_t>(scan_blk_words(scan_n), 3 * (size_t)ts_tiles(scan_n)) * 4);
+    // scan partials; also the fused scans' per-tile totals (2 words per 1024 items)
+    A((void**)&b.blk, std::max<size_t>(scan_blk_words(scan_n), 2 * (size_t)ts_tiles(scan_n)) * 4);
     A((void**)&b.hist, group_hist_words(cap) * 4);
     InsertScratch& ins = m->ins;
     ins.cap = batch;
     A((void**)&ins.key, (size_t)batch * 4);
     A((void**)&ins.rec, (size_t)batch * 16);
     A((void**)&ins.hist, bucket_hist_words(batch) * 4);
+    if (st == VM_OK && hipHostMalloc((void**)&m->n_host, sizeof(uint32_t), hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        m->n_host = nullptr;
+        st = VM_E_OOM;
+    }
     if (st != VM_OK) {
         map_free_all(m);
         delete m;
@@ -336,7 +344,7 @@ vm_status vm_map_destroy(vm_map m)
 vm_status vm_map_clear(vm_map m, void* stream)
 {
     if (!m) return VM_E_ARG;
-    if (capturing((hipStream_t)stream)) return VM_E_STATE;   // clears with memset nodes
+    if (capturing((hipStream_t)stream)) return VM_E_STATE;   // (a recorded clear is not supported)
     VM_HIP(launch_clear(m->g, m->h, m->bits, m->ctr, (hipStream_t)stream));
     m->have_clusters = false;
     return VM_OK;
@@ -455,12 +463,12 @@ vm_status vm_map_export(vm_map m, uint32_t* d_key, uint32_t* d_count, uint64_t* 
     if (capturing((hipStream_t)stream)) return VM_E_STATE;
     hipStream_t s = (hipStream_t)stream;
     VM_HIP(launch_rank(m->g, m->bits, m->b, m->cap, m->ctr, s));
-    VM_HIP(launch_export(m->g, m->h, m->b, m->ctr, d_key, d_count, (unsigned long long*)d_sum, d_mean, cap, s));
+    VM_HIP(launch_export(m->g, m->h, m->b, m->ctr, d_key, d_count, (unsigned long long*)d_sum, d_mean, cap,
+                         m->n_host, s));
     VM_HIP(hipStreamSynchronize(s));
-    DevCounters c;
-    VM_HIP(hipMemcpy(&c, m->ctr, sizeof c, hipMemcpyDeviceToHost));
-    *n_out = c.n_occ;
-    return c.n_occ > cap ? VM_E_CAPACITY : VM_OK;
+    const uint32_t n = *(volatile uint32_t*)m->n_host;
+    *n_out = n;
+    return n > cap ? VM_E_CAPACITY : VM_OK;
 }
 
 vm_status vm_map_import(vm_map m, const uint32_t* d_key, const uint32_t* d_count, const uint64_t* d_sum, uint64_t n,

@@ -19,6 +19,7 @@
 // 26-neighbourhood never needs the hash: occupancy and ranks come from the
 // 1-bit-per-cell index.
 #include "vm_common.h"
+#include "vm_dev.h"
 #include "vm_tilescan.h"
 
 #include <algorithm>
@@ -791,14 +792,6 @@ __global__ void __launch_bounds__(kBlock) k_group_rows(GroupSort a, int shift)
     }
 }
 
-// LDS written by some lanes of a wave is read by others of it
-__device__ __forceinline__ void wave_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <bool kFirst>
 __global__ void __launch_bounds__(kBlock) k_group_scatter(GroupSort a, int shift)
 {
@@ -872,9 +865,9 @@ __global__ void __launch_bounds__(kBlock) k_group_scatter(GroupSort a, int shift
                 }
                 p[j] = 0;
                 if (in) p[j] = place[wave][d] + (uint32_t)__popcll(m & lt);
-                wave_fence();
+                dev::wave_sync();
                 if (in && (m & lt) == 0) place[wave][d] += (uint32_t)__popcll(m);
-                wave_fence();
+                dev::wave_sync();
             }
             __syncthreads();
 #pragma unroll

@@ -280,9 +280,10 @@ hipError_t launch_clear(const Geom& g, const Hash& h, uint32_t* bits, DevCounter
 // segmentation buffers as staging)
 hipError_t launch_scroll(const Geom& g, const Hash& h, uint32_t* bits, SegBuffers& b, uint32_t cap, int32_t dx,
                          int32_t dy, int32_t dz, DevCounters* ctr, hipStream_t s);
+// (the number of occupied voxels also goes to *n_host, pinned host memory)
 hipError_t launch_export(const Geom& g, const Hash& h, const SegBuffers& b, const DevCounters* ctr,
                          uint32_t* key, uint32_t* cnt, unsigned long long* sum, float* mean, uint64_t cap,
-                         hipStream_t s);
+                         uint32_t* n_host, hipStream_t s);
 hipError_t launch_import(const Geom& g, const Hash& h, uint32_t* bits, DevCounters* ctr, const uint32_t* key,
                          const uint32_t* cnt, const unsigned long long* sum, uint64_t n, hipStream_t s);
 

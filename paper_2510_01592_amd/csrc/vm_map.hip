@@ -12,6 +12,10 @@
 #include "vm_common.h"
 #include "vm_tilescan.h"
 
+#include <stddef.h>
+
+#include <algorithm>
+
 namespace vm {
 namespace {
 
@@ -62,16 +66,12 @@ __global__ void __launch_bounds__(kBlock) k_insert(const float* __restrict__ xyz
             continue;
         }
         const uint32_t key = c.key;
-        // find or claim the key's slot
+        // find or claim the key's slot (a wait less than a read before the claim)
         uint32_t s = hash_slot(key, h.log2cap);
         bool ok = false;
         for (uint32_t p = 0; p < kMaxProbe && p <= h.mask; ++p) {
-            const uint32_t k = h.slot[s].key;
-            if (k == key) { ok = true; break; }
-            if (k == kEmpty) {
-                const uint32_t old = atomicCAS(&h.slot[s].key, kEmpty, key);
-                if (old == kEmpty || old == key) { ok = true; break; }
-            }
+            const uint32_t old = atomicCAS(&h.slot[s].key, kEmpty, key);
+            if (old == kEmpty || old == key) { ok = true; break; }
             s = (s + 1) & h.mask;
         }
         if (!ok) {
@@ -79,6 +79,9 @@ __global__ void __launch_bounds__(kBlock) k_insert(const float* __restrict__ xyz
             continue;
         }
         Slot* sl = &h.slot[s];
+        atomicAdd(&sl->sum[0], (unsigned long long)c.off[0]);
+        atomicAdd(&sl->sum[1], (unsigned long long)c.off[1]);
+        atomicAdd(&sl->sum[2], (unsigned long long)c.off[2]);
         // the point that takes a slot's count from 0 marks the voxel occupied:
         // a newly claimed slot, or one whose voxel was cleared (cleared voxels
         // keep their key, so probe chains stay intact)
@@ -86,9 +89,6 @@ __global__ void __launch_bounds__(kBlock) k_insert(const float* __restrict__ xyz
             atomicOr(&bits[key >> 5], 1u << (key & 31));
             ++n_new;
         }
-        atomicAdd(&sl->sum[0], (unsigned long long)c.off[0]);
-        atomicAdd(&sl->sum[1], (unsigned long long)c.off[1]);
-        atomicAdd(&sl->sum[2], (unsigned long long)c.off[2]);
         ++n_in;
     }
     {
@@ -378,7 +378,9 @@ __global__ void __launch_bounds__(kBlock) k_bucket_insert(const uint4* __restric
 
 // Occupied keys in rank order; the component-size counters of the ranks are
 // cleared on the way (the labelling accumulates into them).  A workgroup
-// takes kCompactWords consecutive grid words per pass: their keys (at most
+// takes kCompactWords consecutive grid words per pass (in the scan's second
+// kernel, with four times the words per workgroup, the dense rows of a floor
+// held few of them up: 23 us instead of 5 + 8): their keys (at most
 // 32 per word) go to LDS at their ranks' offsets from the pass's first rank,
 // then the workgroup stores them, and the cleared counters, as contiguous
 // rows.
@@ -416,20 +418,22 @@ __global__ void __launch_bounds__(kBlock) k_compact(const uint32_t* __restrict__
 __global__ void __launch_bounds__(kBlock) k_export(Geom g, Hash h, const uint32_t* __restrict__ occ_key,
                                                    const DevCounters* __restrict__ ctr, uint32_t* key_out,
                                                    uint32_t* cnt_out, unsigned long long* sum_out, float* mean_out,
-                                                   uint64_t cap)
+                                                   uint64_t cap, uint32_t* __restrict__ n_host)
 {
     const uint64_t n = ctr->n_occ < cap ? ctr->n_occ : cap;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *n_host = ctr->n_occ;
     for (uint64_t r = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n; r += (uint64_t)gridDim.x * blockDim.x) {
         const uint32_t k = occ_key[r];
-        const uint32_t s = hash_find(h, k);
-        uint32_t c = 0;
-        unsigned long long sx = 0, sy = 0, sz = 0;
-        if (s != kEmpty) {
-            c = h.slot[s].cnt;
-            sx = h.slot[s].sum[0];
-            sy = h.slot[s].sum[1];
-            sz = h.slot[s].sum[2];
+        // linear probing as in hash_find, with the whole slot in one read
+        uint32_t s = hash_slot(k, h.log2cap);
+        Slot sl = h.slot[s];
+        for (uint32_t p = 1; sl.key != k && sl.key != kEmpty && p < kMaxProbe && p <= h.mask; ++p) {
+            s = (s + 1) & h.mask;
+            sl = h.slot[s];
         }
+        const bool found = sl.key == k;
+        const uint32_t c = found ? sl.cnt : 0u;
+        const unsigned long long sx = found ? sl.sum[0] : 0, sy = found ? sl.sum[1] : 0, sz = found ? sl.sum[2] : 0;
         if (key_out) key_out[r] = k;
         if (cnt_out) cnt_out[r] = c;
         if (sum_out) {
@@ -582,13 +586,28 @@ __global__ void __launch_bounds__(kBlock) k_scroll_scatter(Hash h, uint32_t* __r
 
 // Empty slots, half a slot per thread so that a wave's stores are one row of
 // 1 KB (with a slot per thread each store left gaps: 64 us for 268 MB, 41 so).
-__global__ void __launch_bounds__(kBlock) k_clear_slots(Slot* __restrict__ slot, uint32_t cap)
+__device__ __forceinline__ void clear_slots(Slot* __restrict__ slot, uint32_t cap)
 {
     static_assert(sizeof(Slot) == 2 * sizeof(uint4) && offsetof(Slot, key) == 0, "halves of a slot");
     uint4* p = reinterpret_cast<uint4*>(slot);
     const uint64_t n = 2 * (uint64_t)cap, stride = (uint64_t)gridDim.x * blockDim.x;
     const uint4 v = make_uint4(threadIdx.x & 1u ? 0u : kEmpty, 0u, 0u, 0u);   // (the stride is even)
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
+}
+
+__global__ void __launch_bounds__(kBlock) k_clear_slots(Slot* __restrict__ slot, uint32_t cap)
+{
+    clear_slots(slot, cap);
+}
+
+// slots, occupancy and counters of an empty map, in one launch
+__global__ void __launch_bounds__(kBlock) k_clear_map(Slot* __restrict__ slot, uint32_t cap, uint32_t* __restrict__ bits,
+                                                      uint32_t nwords, DevCounters* __restrict__ ctr)
+{
+    clear_slots(slot, cap);
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nwords; i += gridDim.x * blockDim.x) bits[i] = 0u;
+    static_assert(sizeof(DevCounters) % 4 == 0 && sizeof(DevCounters) / 4 <= kBlock, "a word per thread");
+    if (blockIdx.x == 0 && threadIdx.x < sizeof(DevCounters) / 4) reinterpret_cast<uint32_t*>(ctr)[threadIdx.x] = 0u;
 }
 
 __global__ void k_stats(const DevCounters* __restrict__ c, uint32_t log2cap, vm_map_stats_t* out)
@@ -695,11 +714,9 @@ hipError_t launch_rank(const Geom& g, const uint32_t* bits, SegBuffers& b, uint3
 hipError_t launch_clear(const Geom& g, const Hash& h, uint32_t* bits, DevCounters* ctr, hipStream_t s)
 {
     const uint32_t cap = h.mask + 1;
-    hipError_t e;
-    k_clear_slots<<<grid_for(cap, kBlock, 16384), kBlock, 0, s>>>(h.slot, cap);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = hipMemsetAsync(bits, 0, (size_t)g.nwords * sizeof(uint32_t), s)) != hipSuccess) return e;
-    return hipMemsetAsync(ctr, 0, sizeof(DevCounters), s);
+    k_clear_map<<<grid_for(std::max<uint64_t>(cap, g.nwords / 4), kBlock, 16384), kBlock, 0, s>>>(h.slot, cap, bits,
+                                                                                                  g.nwords, ctr);
+    return hipGetLastError();
 }
 
 hipError_t launch_scroll(const Geom& g, const Hash& h, uint32_t* bits, SegBuffers& b, uint32_t cap, int32_t dx,
@@ -725,9 +742,10 @@ hipError_t launch_scroll(const Geom& g, const Hash& h, uint32_t* bits, SegBuffer
 }
 
 hipError_t launch_export(const Geom& g, const Hash& h, const SegBuffers& b, const DevCounters* ctr, uint32_t* key,
-                         uint32_t* cnt, unsigned long long* sum, float* mean, uint64_t cap, hipStream_t s)
+                         uint32_t* cnt, unsigned long long* sum, float* mean, uint64_t cap,
+                         uint32_t* n_host, hipStream_t s)
 {
-    k_export<<<grid_for(cap), kBlock, 0, s>>>(g, h, b.occ_key, ctr, key, cnt, sum, mean, cap);
+    k_export<<<grid_for(cap), kBlock, 0, s>>>(g, h, b.occ_key, ctr, key, cnt, sum, mean, cap, n_host);
     return hipGetLastError();
 }
 
