@@ -429,12 +429,36 @@ __device__ __forceinline__ Segment segment_at(const uint32_t* __restrict__ bits,
 // united a thread each; pairs beyond the list are united where they are found.
 // A row's reads (its own words, then those of its four neighbours with
 // smaller keys, which also hold the cells beyond the x faces) are in flight
-// together; cell by cell they were up to 18 waits in turn.  Unions by another
+// together; cell by cell they were up to 18 waits in turn.  Each face pair of
+// rows has a thread of its own: with up to four in a row's thread, the longest
+// row of a wave set the pace of twelve loops in turn.  Unions by another
 // kernel cost a launch and the list's way through memory: boundary and pairs
-// 28 + 12 us for 916k voxels, 18 + 9 for 29k; in one 28 and 18.
+// took 28 + 12 us for 916k voxels, 18 + 9 for 29k (a tile per compute unit);
+// now 28 and 14.
 constexpr uint32_t kPairHash = 1024;   // LDS hash set of root pairs per tile
 constexpr uint32_t kTilePairs = 256;   // distinct pairs listed per tile
 constexpr uint32_t kRawPairs = 1024;   // voxel pairs gathered per tile before the root lookups
+
+// The tile's pairs of a row and a neighbouring row (dy, dz) of smaller key in
+// another tile, a thread each: 16 with dy = -1, dz = 0; 31 with dy = -1, 16
+// with dy = 0 and 31 with dy = 1 at dz = -1 (the rows of the tile's lowest
+// layer, and those at the y face).
+constexpr uint32_t kFacePairs = 4 * kTY + 2 * (kTZ - 1);   // 94
+static_assert(kTY == 16 && kTZ == 16 && kFacePairs <= kBlock, "a thread per face pair");
+
+struct FacePair {
+    int y, z, dy, dz;
+};
+
+__device__ __forceinline__ FacePair face_pair(uint32_t t)
+{
+    if (t < 64u) {   // the four neighbours of 16 rows: at the y face for dz = 0, else of the lowest layer
+        const int i = (int)(t % 16u), q = (int)(t / 16u);
+        return q == 0 ? FacePair{0, i, -1, 0} : FacePair{i, 0, q - 2, -1};
+    }
+    const int i = (int)(t - 64u);   // the higher layers' rows at the y faces, one layer down
+    return i < kTZ - 1 ? FacePair{0, 1 + i, -1, -1} : FacePair{kTY - 1, i - (kTZ - 2), 1, -1};
+}
 
 __global__ void __launch_bounds__(kBlock) k_ccl_boundary(const uint32_t* __restrict__ bits, uint32_t nwords,
                                                          const uint32_t* __restrict__ wrank, Dims d, TileGrid tg,
@@ -472,34 +496,36 @@ __global__ void __launch_bounds__(kBlock) k_ccl_boundary(const uint32_t* __restr
         const uint32_t x0 = tx * kTX;
         const int y = (int)(ty * kTY) + yl, z = (int)(tz * kTZ) + zl;
         const Segment own = segment_at(bits, nwords, wrank, d, x0, (uint32_t)y, (uint32_t)z);
-        const uint32_t v = own.v, r0 = own.rank0;
         // first the voxel pairs (no loads of parents yet): each thread finds
-        // and counts its row's, a block scan places them in the raw list
-        const bool face = yl == 0 || yl == kTY - 1 || zl == 0;
-        const bool first = (v & 1u) && x0 > 0, last = (v >> 31) & 1u;
-        uint32_t cnt = 0;
-        HookMasks hm[4];
-        Segment nb[4];
-        uint32_t fmask = 0, lmask = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            hm[q].a = hm[q].b = hm[q].c = 0;
-            nb[q].v = nb[q].rank0 = 0;
-            nb[q].prev = nb[q].next = false;
+        // and counts those of its row's ends and of one of the tile's face
+        // pairs, a block scan places them in the raw list
+        Segment fa, fb;
+        HookMasks hm = {0, 0, 0};
+        if (j < kFacePairs) {
+            const FacePair fp = face_pair(j);
+            const int fy = (int)(ty * kTY) + fp.y, fz = (int)(tz * kTZ) + fp.z;
+            fa = segment_at(bits, nwords, wrank, d, x0, (uint32_t)fy, (uint32_t)fz);
+            fb = segment_at(bits, nwords, wrank, d, x0, (uint32_t)(fy + fp.dy), (uint32_t)(fz + fp.dz));
+            hm = hook_masks(fa.v, fb.v);
         }
-        if (v && (face || first || last)) {
+        const uint32_t v = own.v, r0 = own.rank0;
+        const bool first = (v & 1u) && x0 > 0, last = (v >> 31) & 1u;
+        uint32_t cnt = (uint32_t)(__popc(hm.a) + __popc(hm.b) + __popc(hm.c));
+        uint32_t fr[5], lr[4], fmask = 0, lmask = 0;
+        if (first || last) {
+            Segment nb[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 nb[q] = segment_at(bits, nwords, wrank, d, x0, (uint32_t)(y + (q == 0 ? -1 : q - 2)),
                                    (uint32_t)(z + (q == 0 ? 0 : -1)));
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int ly = yl + (q == 0 ? -1 : q - 2), lz = zl + (q == 0 ? 0 : -1);
-                if (ly < 0 || ly >= kTY || lz < 0) hm[q] = hook_masks(v, nb[q].v);   // (else the same tile)
-                cnt += (uint32_t)(__popc(hm[q].a) + __popc(hm[q].b) + __popc(hm[q].c));
+                fr[q] = nb[q].rank0 - 1u;
+                lr[q] = nb[q].rank0 + (uint32_t)__popc(nb[q].v);
                 fmask |= first && nb[q].prev ? 1u << q : 0u;
                 lmask |= last && nb[q].next ? 1u << q : 0u;
             }
+            fr[4] = r0 - 1u;
             fmask |= first && own.prev ? 1u << 4 : 0u;
             cnt += (uint32_t)(__popc(fmask) + __popc(lmask));
         }
@@ -527,29 +553,21 @@ __global__ void __launch_bounds__(kBlock) k_ccl_boundary(const uint32_t* __restr
                     if (sl >= q0 && sl < q0 + kRawPairs) raw[sl - q0] = ((uint64_t)a << 32) | b;
                     ++sl;
                 };
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const uint32_t w = nb[q].v, n0 = nb[q].rank0;
-                    for (uint32_t m = hm[q].a; m; m &= m - 1) {
-                        const int xa = __ffs(m) - 1;
-                        emit(r0 + __popc(v & ((1u << xa) - 1u)), n0 + __popc(w & ((1u << xa) - 1u)));
-                    }
-                    for (uint32_t m = hm[q].b; m; m &= m - 1) {
-                        const int xa = __ffs(m) - 1;
-                        emit(r0 + __popc(v & ((1u << xa) - 1u)), n0 + __popc(w & ((1u << (xa - 1)) - 1u)));
-                    }
-                    for (uint32_t m = hm[q].c; m; m &= m - 1) {
-                        const int xa = __ffs(m) - 1;
-                        emit(r0 + __popc(v & ((1u << xa) - 1u)), n0 + __popc(w & ((1u << (xa + 1)) - 1u)));
-                    }
+                for (uint32_t m = hm.a | hm.b | hm.c; m; m &= m - 1) {
+                    const int xa = __ffs(m) - 1;
+                    const uint32_t bit = m & (0u - m), ra = fa.rank0 + (uint32_t)__popc(fa.v & (bit - 1u));
+                    const uint32_t rb = fb.rank0 + (uint32_t)__popc(fb.v & (bit - 1u));   // of cell xa of the other row
+                    if (hm.b & bit) emit(ra, rb - 1u);
+                    if (hm.a & bit) emit(ra, rb);
+                    if (hm.c & bit) emit(ra, rb + ((fb.v >> xa) & 1u));
                 }
 #pragma unroll
                 for (int q = 0; q < 5; ++q)
-                    if ((fmask >> q) & 1u) emit(r0, (q < 4 ? nb[q].rank0 : r0) - 1u);
+                    if ((fmask >> q) & 1u) emit(r0, fr[q]);
                 const uint32_t rl = r0 + (uint32_t)__popc(v) - 1u;
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    if ((lmask >> q) & 1u) emit(rl, nb[q].rank0 + (uint32_t)__popc(nb[q].v));
+                    if ((lmask >> q) & 1u) emit(rl, lr[q]);
             }
             __syncthreads();
             const uint32_t nr = min(nraw - q0, kRawPairs);
