@@ -126,40 +126,47 @@ __device__ __forceinline__ uint32_t set_of(const uint32_t* mset, uint32_t n, uin
     return i;
 }
 
-// validate every set, place it in the merged list (sets that no longer fit
-// contribute nothing and are flagged), write the merged counts
-__global__ void __launch_bounds__(kOneBlockThreads) k_multi_prep(MultiTab tab, MultiWork m, uint32_t k_cap,
-                                                                 uint32_t n_cap)
+// validate the sets, a workgroup each: mset[4 i] and [4 i + 1] are set i's
+// clusters and points (one workgroup for all of them took 18 us for eight;
+// a workgroup each takes 4, and the placing 2)
+__global__ void __launch_bounds__(kOneBlockThreads) k_multi_validate(MultiTab tab, MultiWork m)
 {
     __shared__ int bad;
-    __shared__ uint32_t sk[kMultiMax], sn[kMultiMax];
-    for (uint32_t i = 0; i < tab.n; ++i) {
-        const MultiSet& S = tab.s[i];
-        const uint32_t K = validate_clusters(S.meta, S.off, S.k_in, S.n_cap, S.pstatus, &bad);
-        if (threadIdx.x == 0) {
-            sk[i] = K;
-            sn[i] = K ? S.off[K] : 0u;
-            if (S.meta[0] > S.out_k_cap) atomicOr(S.pstatus, (uint32_t)VM_FLAG_CLUSTERS_CAP);
-        }
-        __syncthreads();
-    }
+    const uint32_t i = blockIdx.x;
+    const MultiSet& S = tab.s[i];
+    const uint32_t K = validate_clusters(S.meta, S.off, S.k_in, S.n_cap, S.pstatus, &bad);
     if (threadIdx.x == 0) {
-        uint32_t kb = 0, pb = 0;
-        for (uint32_t i = 0; i < tab.n; ++i) {
-            uint32_t K = sk[i], N = sn[i];
-            if (kb + K > k_cap || pb + N > n_cap) {   // no room left: the set is skipped
+        m.mset[4 * i + 0] = K;
+        m.mset[4 * i + 1] = K ? S.off[K] : 0u;
+        if (S.meta[0] > S.out_k_cap) atomicOr(S.pstatus, (uint32_t)VM_FLAG_CLUSTERS_CAP);
+    }
+}
+
+// place the sets in the merged list (sets that no longer fit contribute
+// nothing and are flagged), write the merged counts
+__global__ void __launch_bounds__(kWave) k_multi_place(MultiTab tab, MultiWork m, uint32_t k_cap, uint32_t n_cap)
+{
+    const uint32_t lane = threadIdx.x;
+    const uint32_t kn = lane < tab.n ? m.mset[4 * lane + 0] : 0u, nn = lane < tab.n ? m.mset[4 * lane + 1] : 0u;
+    uint32_t kb = 0, pb = 0;
+    for (uint32_t i = 0; i < tab.n; ++i) {
+        uint32_t K = __shfl(kn, (int)i, kWave), N = __shfl(nn, (int)i, kWave);
+        const bool fits = kb + K <= k_cap && pb + N <= n_cap;
+        if (!fits) K = N = 0;   // no room left: the set is skipped
+        if (lane == 0) {
+            if (!fits) {
                 atomicOr(tab.s[i].pstatus, (uint32_t)VM_FLAG_CLUSTERS_CAP);
                 atomicOr(tab.s[i].hstatus, (uint32_t)VM_FLAG_CLUSTERS_CAP);
-                K = 0;
-                N = 0;
             }
             m.mset[4 * i + 0] = K;
             m.mset[4 * i + 1] = N;
             m.mset[4 * i + 2] = kb;
             m.mset[4 * i + 3] = pb;
-            kb += K;
-            pb += N;
         }
+        kb += K;
+        pb += N;
+    }
+    if (lane == 0) {
         m.meta[0] = kb;
         m.meta[1] = pb;
         m.off[kb] = pb;
@@ -168,24 +175,29 @@ __global__ void __launch_bounds__(kOneBlockThreads) k_multi_prep(MultiTab tab, M
     }
 }
 
-// the merged list: offsets, tags, frame words and points of every set
+// The merged list: offsets, tags, frame words and points of every set, each
+// set by workgroups of its own, so that its pointers are scalars (with every
+// point's set searched and its pointers read by lane, eight sets of 700k
+// points took 67 us, 23 so).
 __global__ void __launch_bounds__(kMBlock) k_multi_gather(MultiTab tab, MultiWork m)
 {
-    const uint32_t Kt = m.meta[0], Nt = m.meta[1];
-    const uint32_t stride = gridDim.x * blockDim.x;
-    for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < Kt; k += stride) {
-        const uint32_t i = set_of(m.mset, tab.n, k, 2);
-        const uint32_t kl = k - m.mset[4 * i + 2];
-        m.off[k] = m.mset[4 * i + 3] + tab.s[i].off[kl];
-        m.tag[k] = tab.s[i].tag[kl];
-        m.cframe[k] = tab.s[i].frame;
+    const uint32_t i = blockIdx.y;
+    const MultiSet& S = tab.s[i];
+    const uint32_t K = m.mset[4 * i], N = m.mset[4 * i + 1], k0 = m.mset[4 * i + 2], p0 = m.mset[4 * i + 3];
+    const uint32_t t0 = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
+    for (uint32_t k = t0; k < K; k += stride) {
+        m.off[k0 + k] = p0 + S.off[k];
+        m.tag[k0 + k] = S.tag[k];
+        m.cframe[k0 + k] = S.frame;
     }
-    for (uint32_t q = blockIdx.x * blockDim.x + threadIdx.x; q < Nt; q += stride) {
-        const uint32_t i = set_of(m.mset, tab.n, q, 3);
-        const uint32_t ql = q - m.mset[4 * i + 3];
-        m.x[q] = tab.s[i].x[ql];
-        m.y[q] = tab.s[i].y[ql];
-        m.z[q] = tab.s[i].z[ql];
+    const float* __restrict__ x = S.x;
+    const float* __restrict__ y = S.y;
+    const float* __restrict__ z = S.z;
+#pragma unroll 4
+    for (uint32_t q = t0; q < N; q += stride) {
+        m.x[p0 + q] = x[q];
+        m.y[p0 + q] = y[q];
+        m.z[p0 + q] = z[q];
     }
 }
 
@@ -228,60 +240,50 @@ __global__ void __launch_bounds__(kOneBlockThreads) k_multi_scan(MultiTab tab, M
     }
 }
 
-// Each set's outputs, every array by output position (a huge inlier list is
-// copied by many workgroups): per-cluster scalars and offsets, all
-// hypotheses' counts and planes when asked for, inlier indices, vertices.
+// Each set's outputs, by workgroups of its own and every array by output
+// position (a huge inlier list is copied by many of them): per-cluster scalars
+// and offsets, all hypotheses' counts and planes when asked for, inlier
+// indices, vertices.
 __global__ void __launch_bounds__(kMBlock) k_multi_copy(MultiTab tab, MultiWork m, uint32_t H, int with_all)
 {
-    const uint32_t Kt = m.meta[0];
-    const uint32_t stride = gridDim.x * blockDim.x;
-    const uint32_t t0 = blockIdx.x * blockDim.x + threadIdx.x;
-    for (uint32_t k = t0; k < Kt; k += stride) {
-        uint32_t i;
-        const bool fits = fits_set(tab, m, k, &i);
-        const MultiSet& S = tab.s[i];
-        const uint32_t k0 = m.mset[4 * i + 2], kl = k - k0;
+    const uint32_t i = blockIdx.y;
+    const MultiSet& S = tab.s[i];
+    const uint32_t K = m.mset[4 * i], k0 = m.mset[4 * i + 2];
+    const uint32_t i0 = m.in_off[k0], i1 = m.in_off[k0 + K], v0 = m.v_off[k0], v1 = m.v_off[k0 + K], s0 = m.sv[k0];
+    const uint32_t t0 = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
+    const auto fits = [&](uint32_t k) { return m.in_off[k + 1] - i0 <= S.in_cap; };   // as fits_set
+    for (uint32_t kl = t0; kl < K; kl += stride) {
+        const uint32_t k = k0 + kl;
         S.plane[kl] = m.plane[k];
         S.best[kl] = m.best[k];
         S.nin[kl] = m.nin[k];
-        S.in_off[kl] = m.in_off[k] - m.in_off[k0];
-        S.v_off[kl] = m.sv[k] - m.sv[k0];
-        S.area[kl] = fits ? m.area[k] : 0.0;
+        S.in_off[kl] = m.in_off[k] - i0;
+        S.v_off[kl] = m.sv[k] - s0;
+        S.area[kl] = fits(k) ? m.area[k] : 0.0;
     }
     if (with_all) {
-        const uint64_t kh = (uint64_t)Kt * H;
+        const uint64_t kh = (uint64_t)K * H, q0 = (uint64_t)k0 * H;
         for (uint64_t q = t0; q < kh; q += stride) {
-            const uint32_t k = (uint32_t)(q / H), h = (uint32_t)(q % H);
-            const uint32_t i = set_of(m.mset, tab.n, k, 2);
-            const MultiSet& S = tab.s[i];
-            const size_t dst = (size_t)(k - m.mset[4 * i + 2]) * H + h;
-            if (S.counts) S.counts[dst] = m.counts[q];
-            if (S.hyp) S.hyp[dst] = m.hyp[q];
+            if (S.counts) S.counts[q] = m.counts[q0 + q];
+            if (S.hyp) S.hyp[q] = m.hyp[q0 + q];
         }
     }
-    // inlier indices (cluster-local, the same in the merged list): set i's
+    // inlier indices (cluster-local, the same in the merged list): the set's
     // entries are one contiguous range of the merged list
-    const uint32_t ni = m.in_off[Kt];
-    for (uint32_t g = t0; g < ni; g += stride) {
-        uint32_t i = 0;
-        for (uint32_t q = 1; q < tab.n; ++q)
-            if (m.in_off[m.mset[4 * q + 2]] <= g) i = q;
-        const uint32_t j = g - m.in_off[m.mset[4 * i + 2]];
-        if (j < tab.s[i].in_cap) tab.s[i].in_idx[j] = m.in_idx[g];
-    }
+    const uint32_t ni = min(i1 - i0, S.in_cap);
+    uint32_t* __restrict__ in_idx = S.in_idx;
+#pragma unroll 4
+    for (uint32_t j = t0; j < ni; j += stride) in_idx[j] = m.in_idx[i0 + j];
     // vertices of the clusters that keep their polygon
-    const uint32_t nv = m.v_off[Kt];
-    for (uint32_t g = t0; g < nv; g += stride) {
-        uint32_t lo = 0, hi = Kt;   // the cluster: largest k with v_off[k] <= g
+    for (uint32_t g = v0 + t0; g < v1; g += stride) {
+        uint32_t lo = k0, hi = k0 + K;   // the cluster: largest k with v_off[k] <= g
         while (hi - lo > 1) {
             const uint32_t mid = (lo + hi) >> 1;
             if (m.v_off[mid] <= g) lo = mid;
             else hi = mid;
         }
-        uint32_t i;
-        if (!fits_set(tab, m, lo, &i)) continue;
-        const MultiSet& S = tab.s[i];
-        const uint32_t pos = m.sv[lo] - m.sv[m.mset[4 * i + 2]] + (g - m.v_off[lo]);
+        if (!fits(lo)) continue;
+        const uint32_t pos = m.sv[lo] - s0 + (g - m.v_off[lo]);
         if (pos >= S.v_cap) continue;   // flagged by the scan
         S.v_idx[pos] = m.v_idx[g];
         S.v_xyz[3 * (size_t)pos + 0] = m.v_xyz[3 * (size_t)g + 0];
@@ -340,8 +342,9 @@ vm_status planes_hulls_multi(uint32_t n, const vm_clusters* sets, const uint32_t
     }
     {
         StageScope t(VM_STAGE_GROUP, s);
-        k_multi_prep<<<1, kOneBlockThreads, 0, s>>>(tab, m, k_cap, n_cap);
-        k_multi_gather<<<1024, kMBlock, 0, s>>>(tab, m);
+        k_multi_validate<<<n, kOneBlockThreads, 0, s>>>(tab, m);
+        k_multi_place<<<1, kWave, 0, s>>>(tab, m, k_cap, n_cap);
+        k_multi_gather<<<dim3(2048 / n, n), kMBlock, 0, s>>>(tab, m);
         VM_HIP(hipGetLastError());
     }
     vm_clusters mc;
@@ -380,7 +383,7 @@ vm_status planes_hulls_multi(uint32_t n, const vm_clusters* sets, const uint32_t
     if (st != VM_OK) return st;
     StageScope t(VM_STAGE_HULL, s);
     k_multi_scan<<<1, kOneBlockThreads, 0, s>>>(tab, m);
-    k_multi_copy<<<2048, kMBlock, 0, s>>>(tab, m, H, with_all ? 1 : 0);
+    k_multi_copy<<<dim3(2048 / n, n), kMBlock, 0, s>>>(tab, m, H, with_all ? 1 : 0);
     VM_HIP(hipGetLastError());
     return VM_OK;
 }
