@@ -142,10 +142,14 @@ __device__ __forceinline__ uint32_t bucket_of(uint32_t key, uint32_t lb)
     return lb ? (key * 2654435769u) >> (32 - lb) : 0u;
 }
 
-__device__ __forceinline__ uint32_t table_slot(uint32_t key)
+// The next bits of the same hash, so that the table's order is the order of the
+// home slots and the lanes of a wave update neighbouring lines (4M points: 111
+// -> 107 us when every voxel is new, 190 -> 181 when few are; bound by the
+// random 32-byte accesses themselves: probing a thread's four entries together
+// instead of one after another changed nothing).
+__device__ __forceinline__ uint32_t table_slot(uint32_t key, uint32_t lb)
 {
-    // independent of the bucket bits: a different multiplier
-    return (key * 0xCC9E2D51u) >> (32 - kBucketTableLog2);
+    return ((key * 2654435769u) << lb) >> (32 - kBucketTableLog2);
 }
 
 // f(in the grid, cell) for the points of workgroup blockIdx.x's tile
@@ -290,7 +294,7 @@ __global__ void __launch_bounds__(kBlock) k_bucket_insert(const uint4* __restric
             for (uint32_t u = 0; u < kRecPerThread; ++u) {
                 if (c0 + threadIdx.x + u * kBlock >= c1) continue;
                 const uint32_t k = rr[u].x;
-                uint32_t q = table_slot(k);
+                uint32_t q = table_slot(k, lb);
                 for (;;) {   // at most kBucketChunk keys in a table of kBucketTable slots: ends
                     const uint32_t old = atomicCAS(&tkey[q], kEmpty, k);
                     if (old == kEmpty || old == k) break;
