@@ -39,6 +39,7 @@ constexpr int kTileItems = 4;
 constexpr int kHullTile = kTileThreads * kTileItems;   // inliers per tile
 constexpr int kDirs = 64;          // support directions of the filter polygon, a lane each
 constexpr double kMargin = 4e-9;   // of the extent's square: the margin of the polygon's corners and of the filter
+constexpr int kTileGrid = 16384;   // workgroups of the tile kernels, at most
 constexpr int kPolyGrid = 2048;    // workgroups of the polygon kernel
 constexpr int kFinishGrid = 512;   // workgroups of the hull kernel: two per compute unit (67 KB of LDS)
 constexpr int kLdsCap = 2048;      // survivors sorted in LDS
@@ -770,9 +771,11 @@ vm_status hulls(const vm_clusters& cl, const vm_planes& planes, const vm_hulls_o
                                                      planes.d_in_idx, planes.in_cap, w.hull_tile_off, out.d_status);
         VM_HIP(scan_exclusive_dev(w.hull_tile_off, w.hull_tile_off, w.small + 4, kc, w.small + 6, w.blk, s));
     }
-    // grids sized for a few workgroups per CU; the kernels stride over the
-    // device-side counts, so empty workgroups are not launched by the thousand
-    const int tgrid = grid_for(hull_tiles_bound(kc, cl.n_cap), 1, 2048);
+    // the tile kernels stride over the device-side counts; many more workgroups
+    // than fit at once even out what they find (34k tiles of 2000 clusters:
+    // extremes 259 us and filter 316 with 2048, of which 1792 fit, 226 and 228
+    // with 16384; a frame's few hundred tiles: 17 us either way)
+    const int tgrid = grid_for(hull_tiles_bound(kc, cl.n_cap), 1, kTileGrid);
     // the tiles' extremes lie where the survivors go afterwards: a filtered
     // cluster of m > 64 inliers has at most m / 1024 + 1 tiles of 256 bytes in
     // each table, less than the 8 m bytes of its part of hull_u or hull_v
