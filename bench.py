@@ -57,11 +57,11 @@ HOST_THREADS = max(1, min(16, os.cpu_count() or 1))
 
 # kernels of each measured unit, and the source file each lives in
 UNITS = {
-    "ccl": (["k_ccl_tile", "k_ccl_boundary", "k_ccl_pairs", "k_ccl_flatten"], "vm_ccl.hip"),
+    "ccl": (["k_ccl_tile", "k_ccl_boundary", "k_ccl_flatten"], "vm_ccl.hip"),
     "count": (["k_count_small", "k_count"], "vm_ransac.hip"),
-    "insert": (["k_vox_bucket", "k_bucket_scatter", "k_bucket_insert"], "vm_map.hip"),
-    "group": (["k_group_pairs", "k_group_gather"], "vm_ccl.hip"),
-    "fused": (["k_fused_hyp", "k_fused"], "vm_fused.hip"),
+    "insert": (["k_bucket_count", "k_bucket_cols", "k_bucket_scatter", "k_bucket_insert"], "vm_map.hip"),
+    "group": (["k_group_hist", "k_group_rows", "k_group_scatter"], "vm_ccl.hip"),
+    "fused": (["k_fused"], "vm_fused.hip"),
 }
 # headers every kernel file includes: part of each unit's source fingerprint
 SHARED_HEADERS = ("vm_common.h", "vm_dev.h", "vm_tilescan.h")
@@ -323,13 +323,13 @@ def main() -> int:
     traffic = _traffic_per_unit()
     ccl_ms = stage_ms["ccl"] + stage_ms["ccl_link"]
     rooflines = {
-        "ccl": _hbm_roof("labelling + linking (k_ccl_tile, k_ccl_boundary, k_ccl_pairs, k_ccl_flatten), one frame",
+        "ccl": _hbm_roof("labelling + linking (k_ccl_tile, k_ccl_boundary, k_ccl_flatten), one frame",
                          8.0 * v_stage + 64.0 * bricks, ccl_ms, peaks, traffic.get("ccl"),
                          f"8 B per occupied voxel x {v_stage:.0f} + 64 B per touched 8^3 brick x {bricks}"),
-        "insert": _hbm_roof("grouped insert (k_vox_bucket, scan, k_bucket_scatter, k_bucket_insert), one frame",
+        "insert": _hbm_roof("grouped insert (k_bucket_count, k_bucket_cols, k_bucket_scatter, k_bucket_insert), one frame",
                             12.0 * sc.n_points + 64.0 * touched, stage_ms["insert"], peaks, traffic.get("insert"),
                             f"12 B per point x {sc.n_points} + 64 B per touched voxel x {touched:.0f}"),
-        "group": _hbm_roof("grouping (scan, sort, gather), one frame", 24.0 * kept, stage_ms["group"], peaks,
+        "group": _hbm_roof("grouping (scan, sort with the points' gather in its last pass), one frame", 24.0 * kept, stage_ms["group"], peaks,
                            traffic.get("group"), f"24 B per kept voxel x {kept:.0f}"),
         "count": _alu_roof(tests, count_ms, peaks, traffic.get("count"),
                            f"{n_pts} points x {H} hypotheses (the last stage frame's clusters)",
@@ -504,8 +504,8 @@ def _batched(vm, torch, dev, stream, replays: int = 100, peaks=None):
     """2000 clusters of log-uniform size (50..200k points, about 48.5M in all),
     1024 hypotheses: planes and polygons of all clusters per frame.  Forms:
     two-pass (vm_ransac_planes + vm_hulls, a dozen dependent launches) and
-    persistent (vm_planes_hulls: one preparation, one persistent launch, the
-    tail chain, one pack); the persistent form's split is autotuned, the frame
+    persistent (vm_planes_hulls: one preparation, the counting as one persistent
+    launch, then the tiled passes); the persistent form's split is autotuned, the frame
     captured as a graph and replayed `replays` times with the frame number
     advanced in device memory (the data stays resident)."""
     import scenes

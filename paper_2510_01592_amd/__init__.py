@@ -538,7 +538,7 @@ def hulls(cl: Clusters, planes: PlaneBuffers, out: HullBuffers, work, stream=Non
 
 def planes_hulls(cl: Clusters, params: RansacParams, planes: PlaneBuffers, hulls_out: "HullBuffers", work,
                  stream=None) -> None:
-    """vm_planes_hulls: RANSAC planes and polygons of every cluster in one persistent launch."""
+    """vm_planes_hulls: RANSAC planes and polygons of every cluster, counted in one persistent launch."""
     pc, hc = planes.c(), hulls_out.c()
     _check(lib().vm_planes_hulls(ctypes.byref(cl), ctypes.byref(params), ctypes.byref(pc), ctypes.byref(hc),
                                  _ptr(work), int(work.numel() * work.element_size()), _stream(stream)),
@@ -551,7 +551,7 @@ def multi_workspace_bytes(k_cap: int, n_cap: int, n_hyp: int) -> int:
 
 def planes_hulls_multi(sets, frames, params: RansacParams, planes, hulls_out, k_cap: int, n_cap: int, work,
                        stream=None) -> None:
-    """vm_planes_hulls_multi: several cluster sets (vm_clusters views) in one persistent pass; set i uses
+    """vm_planes_hulls_multi: several cluster sets (vm_clusters views) in one merged pass; set i uses
     RNG frame word frames[i] and writes planes[i] / hulls_out[i]."""
     n = len(sets)
     cs = (Clusters * n)(*sets)
