@@ -384,42 +384,68 @@ __global__ void __launch_bounds__(kBlock) k_bucket_insert(const uint4* __restric
     }
 }
 
-// Occupied keys in rank order; the component-size counters of the ranks are
-// cleared on the way (the labelling accumulates into them).  A workgroup
-// takes kCompactWords consecutive grid words per pass (in the scan's second
-// kernel, with four times the words per workgroup, the dense rows of a floor
-// held few of them up: 23 us instead of 5 + 8): their keys (at most
-// 32 per word) go to LDS at their ranks' offsets from the pass's first rank,
-// then the workgroup stores them, and the cleared counters, as contiguous
-// rows.
-constexpr uint32_t kCompactWords = kBlock;
+// ---- occupancy index ------------------------------------------------------------
+// Word ranks (exclusive popcount prefixes) and the occupied keys in rank order,
+// in two kernels over tiles of 256 grid words: the tiles' popcounts, a tile
+// per wave; then, per tile, the sum of the tiles before it (scanned by one
+// workgroup in between if there are many), the ranks of its words, and their
+// keys, laid out in LDS at their ranks (at most 32 per word) and stored as
+// contiguous rows with the component-size counters of the ranks, cleared on
+// the way (the labelling accumulates into them).  With the ranks and the keys
+// in a kernel each, the second read bits and ranks again: a 400x400x200 grid
+// took 18 us and takes 14.5, one of 800x800x400 85 and 67.  (With the keys of
+// 1024 words per workgroup 28: the dense rows of a floor hold few of them up.)
+constexpr uint32_t kRankTile = kBlock;          // words per tile
+constexpr uint32_t kRankDirectTiles = 4096;     // up to this many a tile sums those before it itself
 
-__global__ void __launch_bounds__(kBlock) k_compact(const uint32_t* __restrict__ bits, uint32_t nwords,
-                                                    const uint32_t* __restrict__ wrank,
-                                                    uint32_t* __restrict__ occ_key, uint32_t* __restrict__ csize)
+__global__ void __launch_bounds__(kBlock) k_rank_tiles(const uint32_t* __restrict__ bits, uint32_t nwords, uint32_t nt,
+                                                       Vec<1>* __restrict__ blk)
 {
-    __shared__ uint32_t keys[kCompactWords * 32];
-    __shared__ uint32_t s_base, s_end;
-    for (uint32_t w0 = blockIdx.x * kCompactWords; w0 < nwords; w0 += gridDim.x * kCompactWords) {
-        const uint32_t w = w0 + threadIdx.x;
-        const uint32_t wl = (nwords - w0 < kCompactWords ? nwords : w0 + kCompactWords) - 1;   // last word
-        uint32_t b = 0, r = 0;
-        if (w < nwords) {
-            b = bits[w];
-            r = wrank[w];
+    constexpr int kPerLane = kRankTile / kWave;
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t waves = gridDim.x * (kBlock / kWave);
+    for (uint32_t t = blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave; t < nt; t += waves) {
+        uint32_t c = 0;
+#pragma unroll
+        for (int j = 0; j < kPerLane; ++j) {
+            const uint32_t w = t * kRankTile + j * kWave + lane;
+            c += w < nwords ? (uint32_t)__popc(bits[w]) : 0u;
         }
-        if (w == w0) s_base = r;
-        if (w == wl) s_end = r + (uint32_t)__popc(b);
-        __syncthreads();
-        const uint32_t base = s_base;
-        for (uint32_t q = r - base; b; b &= b - 1, ++q) keys[q] = (w << 5) | (uint32_t)(__ffs(b) - 1);
-        __syncthreads();
-        const uint32_t n = s_end - base;   // at most 32 keys per word
-        for (uint32_t i = threadIdx.x; i < n; i += kBlock) {
-            occ_key[base + i] = keys[i];
-            csize[base + i] = 0u;
+#pragma unroll
+        for (int d = kWave / 2; d >= 1; d >>= 1) c += __shfl_xor(c, d, kWave);
+        if (lane == 0) blk[t].v[0] = c;
+    }
+}
+
+__global__ void __launch_bounds__(kBlock) k_rank_keys(const uint32_t* __restrict__ bits, uint32_t nwords, uint32_t nt,
+                                                      const Vec<1>* __restrict__ blk, bool scanned,
+                                                      uint32_t* __restrict__ wrank, uint32_t* __restrict__ occ_key,
+                                                      uint32_t* __restrict__ csize, DevCounters* __restrict__ ctr)
+{
+    __shared__ uint16_t keys[kRankTile * 32];   // from the tile's first cell
+    __shared__ Vec<1> lds[kBlock / kWave];
+    for (uint32_t t = blockIdx.x; t < nt; t += gridDim.x) {
+        const uint32_t w = t * kRankTile + threadIdx.x;
+        uint32_t b = w < nwords ? bits[w] : 0u;
+        Vec<1> pre{{0u}}, n, c{{(uint32_t)__popc(b)}};
+        if (scanned) {
+            pre = blk[t];
+        } else {
+            Vec<1> p{{0u}};
+#pragma unroll 4
+            for (uint32_t q = threadIdx.x; q < t; q += kBlock) p.v[0] += blk[q].v[0];
+            ts_block_excl(p, lds, &pre);
         }
-        __syncthreads();   // keys, s_base and s_end are reused by the next pass
+        uint32_t q = ts_block_excl(c, lds, &n).v[0];
+        if (w < nwords) wrank[w] = pre.v[0] + q;
+        for (; b; b &= b - 1, ++q) keys[q] = (uint16_t)((threadIdx.x << 5) | (uint32_t)(__ffs(b) - 1));
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i < n.v[0]; i += kBlock) {
+            occ_key[pre.v[0] + i] = t * kRankTile * 32u + keys[i];
+            csize[pre.v[0] + i] = 0u;
+        }
+        if (t + 1 == nt && threadIdx.x == 0) ctr->n_occ = pre.v[0] + n.v[0];
+        __syncthreads();   // keys is reused by the next tile
     }
 }
 
@@ -690,32 +716,19 @@ hipError_t launch_insert(const float* xyz, int64_t n, const Pose& pose, const Ge
     return hipSuccess;
 }
 
-namespace {
-// the occupancy index's scan: the popcount of each word is taken as the
-// scan reads it, and the exclusive prefixes are the word ranks
-struct RankF {
-    const uint32_t* bits;
-    __device__ Vec<1> operator()(uint32_t w) const
-    {
-        Vec<1> x;
-        x.v[0] = (uint32_t)__popc(bits[w]);
-        return x;
-    }
-};
-
-struct RankG {
-    uint32_t* wrank;
-    DevCounters* ctr;
-    __device__ void operator()(uint32_t w, const Vec<1>&, const Vec<1>& pre) const { wrank[w] = pre.v[0]; }
-    __device__ void total(const Vec<1>& t) const { ctr->n_occ = t.v[0]; }
-};
-}   // namespace
+// words of launch_rank's tile totals
+size_t rank_blk_words(uint32_t nwords) { return (size_t)(nwords + kRankTile - 1) / kRankTile; }
 
 hipError_t launch_rank(const Geom& g, const uint32_t* bits, SegBuffers& b, uint32_t /*cap*/, DevCounters* ctr,
                        hipStream_t s)
 {
-    tile_scan<1>(RankF{bits}, RankG{b.wrank, ctr}, nullptr, g.nwords, reinterpret_cast<Vec<1>*>(b.blk), s);
-    k_compact<<<grid_for(g.nwords), kBlock, 0, s>>>(bits, g.nwords, b.wrank, b.occ_key, b.csize);
+    Vec<1>* blk = reinterpret_cast<Vec<1>*>(b.blk);
+    const uint32_t nt = (uint32_t)rank_blk_words(g.nwords);
+    const bool scanned = nt > kRankDirectTiles;
+    k_rank_tiles<<<grid_for((uint64_t)nt * kWave), kBlock, 0, s>>>(bits, g.nwords, nt, blk);
+    if (scanned) k_tile_totals<1><<<1, kOneBlockThreads, 0, s>>>(blk, nt);
+    k_rank_keys<<<grid_for(nt, 1, 16384), kBlock, 0, s>>>(bits, g.nwords, nt, blk, scanned, b.wrank, b.occ_key, b.csize,
+                                                          ctr);
     return hipGetLastError();
 }
 
