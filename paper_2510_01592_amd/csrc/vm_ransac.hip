@@ -330,36 +330,58 @@ __global__ void __launch_bounds__(kBlock) k_select(const uint32_t* __restrict__ 
                                                    int32_t* __restrict__ nin_out, int32_t* __restrict__ counts_out,
                                                    float4* __restrict__ hyp_out)
 {
+    constexpr uint32_t kAhead = 4;
     const uint32_t K = small[0];
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t waves = gridDim.x * (blockDim.x / kWave);
     for (uint32_t k = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave; k < K; k += waves) {
+        const float4* hk = hyp + (size_t)k * H;
+        const int32_t* ck = counts + (size_t)k * H;
         int32_t bc = -1;
         uint32_t bh = 0xFFFFFFFFu;
-        for (uint32_t h = lane; h < H; h += kWave) {
-            const float4 pl = hyp[(size_t)k * H + h];
-            const bool degen = pl.x != pl.x;
-            const int32_t c = degen ? -1 : counts[(size_t)k * H + h];
-            if (c > bc) { bc = c; bh = h; }
-            if (counts_out) counts_out[(size_t)k * H + h] = c;
-            if (hyp_out) hyp_out[(size_t)k * H + h] = degen ? make_float4(0.f, 0.f, 0.f, 0.f) : pl;
+        float4 bp = make_float4(0.f, 0.f, 0.f, 0.f);
+        // kAhead rounds' reads are in flight together, and the best plane is
+        // kept, not read again (one round after another, 512 hypotheses took
+        // a frame's clusters 7.7 us, 4.7 so; 1024 took 13 us and 6.6)
+        for (uint32_t h0 = lane; h0 < H; h0 += kAhead * kWave) {
+            float4 pl[kAhead];
+            int32_t c[kAhead];
+#pragma unroll
+            for (uint32_t j = 0; j < kAhead; ++j) {
+                const uint32_t h = min(h0 + j * kWave, H - 1u);
+                pl[j] = hk[h];
+                c[j] = ck[h];
+            }
+#pragma unroll
+            for (uint32_t j = 0; j < kAhead; ++j) {
+                const uint32_t h = h0 + j * kWave;
+                if (h >= H) break;
+                const bool degen = pl[j].x != pl[j].x;
+                if (degen) {
+                    c[j] = -1;
+                    pl[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+                }
+                if (c[j] > bc) {
+                    bc = c[j];
+                    bh = h;
+                    bp = pl[j];
+                }
+                if (counts_out) counts_out[(size_t)k * H + h] = c[j];
+                if (hyp_out) hyp_out[(size_t)k * H + h] = pl[j];
+            }
         }
+        const uint32_t own = bh;
 #pragma unroll
         for (int d = kWave / 2; d >= 1; d >>= 1) {
             const int32_t oc = __shfl_xor(bc, d, kWave);
             const uint32_t oh = __shfl_xor(bh, d, kWave);
             if (oc > bc || (oc == bc && oh < bh)) { bc = oc; bh = oh; }
         }
-        if (lane == 0) {
-            if (bc < 0) {
-                best_out[k] = -1;
-                nin_out[k] = 0;
-                plane_out[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-            } else {
-                best_out[k] = (int32_t)bh;
-                nin_out[k] = bc;
-                plane_out[k] = hyp[(size_t)k * H + bh];
-            }
+        // the lane that found it, or without one any (its plane is zero then)
+        if (bc < 0 ? lane == 0 : own == bh) {
+            best_out[k] = bc < 0 ? -1 : (int32_t)bh;
+            nin_out[k] = bc < 0 ? 0 : bc;
+            plane_out[k] = bp;
         }
     }
 }
