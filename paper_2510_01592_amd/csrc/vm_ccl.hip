@@ -637,11 +637,14 @@ static_assert(kFlatSlots == 1u << (32 - 26), "the slot is a hash's top bits");
 struct GroupF {
     const uint32_t* parent;
     const uint32_t* csize;
+    uint32_t* cid;
     uint32_t min_cluster;
     __device__ Vec<2> operator()(uint32_t r) const
     {
-        const uint32_t sz = parent[r] == r ? csize[r] : 0u;
+        const bool root = parent[r] == r;
+        const uint32_t sz = root ? csize[r] : 0u;
         const bool kept = sz >= min_cluster;   // (min_cluster is at least 1)
+        if (root && !kept) cid[r] = kEmpty;
         Vec<2> x;
         x.v[0] = kept ? 1u : 0u;
         x.v[1] = kept ? sz : 0u;
@@ -650,21 +653,16 @@ struct GroupF {
 };
 
 struct GroupG {
-    const uint32_t* parent;
     uint32_t* cid;        // cluster id, at roots
     uint32_t* cl_off;
     uint32_t* cl_tag;
     const uint32_t* occ_key;
     DevCounters* ctr;
-    __device__ void operator()(uint32_t r, const Vec<2>& x, const Vec<2>& pre) const
+    __device__ void operator()(uint32_t r, const Vec<2>&, const Vec<2>& pre) const
     {
-        if (x.v[0]) {
-            cid[r] = pre.v[0];
-            cl_off[pre.v[0]] = pre.v[1];
-            cl_tag[pre.v[0]] = occ_key[r];
-        } else if (parent[r] == r) {
-            cid[r] = kEmpty;
-        }
+        cid[r] = pre.v[0];
+        cl_off[pre.v[0]] = pre.v[1];
+        cl_tag[pre.v[0]] = occ_key[r];
     }
     __device__ void total(const Vec<2>& t) const
     {
@@ -997,8 +995,8 @@ hipError_t launch_group(const Geom& g, const Hash& h, SegBuffers& b, uint32_t ca
 {
     StageScope t(VM_STAGE_GROUP, s);
     if (min_cluster < 1) min_cluster = 1;
-    const GroupF f{b.parent, b.csize, min_cluster};
-    const GroupG gg{b.parent, b.scan_a, b.cl_off, b.cl_tag, b.occ_key, ctr};
+    const GroupF f{b.parent, b.csize, b.scan_a, min_cluster};
+    const GroupG gg{b.scan_a, b.cl_off, b.cl_tag, b.occ_key, ctr};
     tile_scan<2>(f, gg, &ctr->n_occ, cap, reinterpret_cast<Vec<2>*>(b.blk), s);
     GroupSort a;
     a.ctr = ctr;
