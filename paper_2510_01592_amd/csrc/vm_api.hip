@@ -304,8 +304,8 @@ vm_status vm_map_create(const vm_map_desc* d, vm_map* out)
     A((void**)&b.cl_z, cap * 4);
     A((void**)&b.wrank, ((size_t)m->g.nwords + 1) * 4);
     const uint32_t batch = 1u << (d->insert_batch_log2 ? d->insert_batch_log2 : 22);
-    // the fused scans' per-tile totals (2 words per 1024 voxels; 1 per tile of grid words)
-    A((void**)&b.blk, std::max<size_t>(2 * (size_t)ts_tiles(cap), rank_blk_words(m->g.nwords)) * 4);
+    // the fused scans' per-tile totals (2 words per 1024 voxels; 1 per tile of grid words), in whole 16-byte reads
+    A((void**)&b.blk, ((std::max<size_t>(2 * (size_t)ts_tiles(cap), rank_blk_words(m->g.nwords)) + 3) & ~(size_t)3) * 4);
     A((void**)&b.hist, group_hist_words(cap) * 4);
     InsertScratch& ins = m->ins;
     ins.cap = batch;
