@@ -72,26 +72,6 @@ __device__ __forceinline__ ClusterFrame cluster_frame(uint32_t k, const uint32_t
     return f;
 }
 
-// The same projection in fp32, for the choice of the polygon and the first
-// test of a point against it.
-struct FrameF {
-    float u[3], v[3], ox, oy, oz;
-};
-
-__device__ __forceinline__ FrameF frame_f(const ClusterFrame& f)
-{
-    return {{(float)f.B.u[0], (float)f.B.u[1], (float)f.B.u[2]},
-            {(float)f.B.v[0], (float)f.B.v[1], (float)f.B.v[2]},
-            (float)f.ox, (float)f.oy, (float)f.oz};
-}
-
-__device__ __forceinline__ float2 project_f(const FrameF& f, float x, float y, float z)
-{
-    const float dx = x - f.ox, dy = y - f.oy, dz = z - f.oz;
-    return make_float2(fmaf(f.u[0], dx, fmaf(f.u[1], dy, f.u[2] * dz)),
-                       fmaf(f.v[0], dx, fmaf(f.v[1], dy, f.v[2] * dz)));
-}
-
 // largest k with tile_off[k] <= t (tile_off is an exclusive scan of K entries),
 // found by a whole wave, 64 probes at a time: two dependent reads for up to
 // 4096 clusters, which is what a tile waits for before anything else
@@ -172,7 +152,11 @@ __global__ void __launch_bounds__(kOneBlockThreads) k_hull_prepare(
 // The polygon that the extremes give may be through any inliers (it only has to
 // lie inside the hull), so the extremes are compared in fp32, with a point's
 // number in the value's lowest bits: one instruction makes the key,
-// half of one keeps the largest.  Opposite directions share the product, and
+// half of one keeps the largest.  The points are projected in fp64 and rounded
+// then: an fp32 projection errs by the whole distance from the first inlier,
+// which along the normal may be any multiple of the cluster's width.  (An
+// eighth of the coordinates is compared, so that none of them overflows: an
+// extreme lost would let the polygon say nothing about the cluster's extent.)  Opposite directions share the product, and
 // a lane has four directions (q, q + 16 and their opposites) for a quarter of
 // its wave's points: a point per lane and direction took 64 LDS reads per
 // wave and 5 instructions each and was bound by both (526 us for the 34M
@@ -223,7 +207,6 @@ __global__ void __launch_bounds__(kTileThreads) k_hull_extremes(
     for (uint32_t t = blockIdx.x; t < T; t += gridDim.x) {
         const uint32_t k = cluster_of_tile(tile_off, K, t);
         const ClusterFrame f = cluster_frame(k, off, X, Y, Z, plane, in_off, in_idx);
-        const FrameF ff = frame_f(f);
         const uint32_t j0 = (t - tile_off[k]) * kHullTile, m = min((uint32_t)kHullTile, f.m - j0);
         // a wave projects and then searches its own quarter of the tile; what
         // is not a point of the cluster is NaN and never an extreme
@@ -238,8 +221,10 @@ __global__ void __launch_bounds__(kTileThreads) k_hull_extremes(
 #pragma unroll
         for (int it = 0; it < kQuarter / kWave; ++it) {
             const uint32_t i = f.pb + min(li[it], f.nk - 1u);
-            const float2 p = project_f(ff, X[i], Y[i], Z[i]);
-            uv[q0 + it * kWave + lane] = li[it] < f.nk ? p : make_float2(__builtin_nanf(""), 0.0f);
+            double u, v;
+            project(f, X[i], Y[i], Z[i], &u, &v);
+            uv[q0 + it * kWave + lane] =
+                li[it] < f.nk ? make_float2((float)(0.125 * u), (float)(0.125 * v)) : make_float2(__builtin_nanf(""), 0.0f);
         }
         wave_sync();
         float hi0 = -INFINITY, hi1 = -INFINITY, lo0 = INFINITY, lo1 = INFINITY;
@@ -413,13 +398,18 @@ __device__ __forceinline__ bool inside_polygon(const F2* P, int np, F mg, F u, F
     return (b.x - a.x) * (v - a.y) - (b.y - a.y) * (u - a.x) > mg && side(1) > mg && side(np - 1) < -mg;
 }
 
-// A point is first tested in fp32, by a margin far above the rounding there
-// (1e-6 of the extent in a coordinate, 8e-6 of its square in a product).  The
+// A point is first tested in fp32, by a margin above the rounding there; the
 // few near the border or outside are collected and tested in fp64 by margin[k],
 // so that one wave does for a tile what else nearly every wave would run for a
 // lane or two (34M inliers in no order: 277 us with fp64 alone, 355 us with
-// both in place, 312 us so).
-constexpr double kMarginF = 3e-5;   // of the extent's square
+// both in place, 312 us so).  The fp32 coordinates are the fp64 ones relative
+// to corner 0, rounded: each errs by 2^-24 of itself and none exceeds the
+// extent E of the inliers in the plane, wherever they lie along the normal.
+// Differences then err by 3 * 2^-24 E, a product of two of them by 7 * 2^-24
+// E^2, and a side's value by 16 * 2^-24 E^2.  E is at most 2.0001 spans (the
+// extremes hold the largest and the smallest of both coordinates to 2^-16), so
+// that is 4e-6 of the span's square.
+constexpr double kMarginF = 3e-5;   // of the span's square
 
 // (extents whose square leaves fp32's range are left to fp64)
 __device__ __forceinline__ float margin_f(double mg)
@@ -437,7 +427,8 @@ __global__ void __launch_bounds__(kTileThreads) k_hull_filter(
 {
     __shared__ double2 poly[kDirs];
     __shared__ float2 polyf[kDirs];
-    __shared__ float4 rest[kHullTile];   // the points left for the fp64 test, with their numbers
+    __shared__ double2 rest[kHullTile];   // the points left for the fp64 test, and their numbers in the tile
+    __shared__ uint16_t rest_no[kHullTile];
     __shared__ uint32_t nrest;
     const uint32_t K = small[4];
     const uint32_t T = small[6];
@@ -445,7 +436,6 @@ __global__ void __launch_bounds__(kTileThreads) k_hull_filter(
     for (uint32_t t = blockIdx.x; t < T; t += gridDim.x) {
         const uint32_t k = cluster_of_tile(tile_off, K, t);
         const ClusterFrame f = cluster_frame(k, off, X, Y, Z, plane, in_off, in_idx);
-        const FrameF ff = frame_f(f);
         const uint32_t* corner = hull_tmp + f.ib + k;
         const int np = (int)corner[kDirs];
         const double mg = margin[k];
@@ -469,33 +459,34 @@ __global__ void __launch_bounds__(kTileThreads) k_hull_filter(
             z[it] = Z[pt[it]];
         }
         if ((int)threadIdx.x < np) {
-            const uint32_t i = f.pb + in_idx[f.ib + corner[threadIdx.x]];
-            const float cx = X[i], cy = Y[i], cz = Z[i];
-            double2 c;
-            project(f, cx, cy, cz, &c.x, &c.y);
+            const uint32_t i = f.pb + in_idx[f.ib + corner[threadIdx.x]], i0 = f.pb + in_idx[f.ib + corner[0]];
+            double2 c, c0;
+            project(f, X[i], Y[i], Z[i], &c.x, &c.y);
+            project(f, X[i0], Y[i0], Z[i0], &c0.x, &c0.y);
             poly[threadIdx.x] = c;
-            polyf[threadIdx.x] = project_f(ff, cx, cy, cz);
+            polyf[threadIdx.x] = make_float2((float)(c.x - c0.x), (float)(c.y - c0.y));
         }
         if (threadIdx.x == 0) nrest = 0;
         __syncthreads();
 #pragma unroll
         for (int it = 0; it < kTileItems; ++it) {
-            const float2 p = project_f(ff, x[it], y[it], z[it]);
-            if (in[it] && !(np >= 3 && inside_polygon(polyf, np, mgf, p.x, p.y)))
-                rest[atomicAdd(&nrest, 1u)] =
-                    make_float4(x[it], y[it], z[it], __uint_as_float(j0 + it * kTileThreads + threadIdx.x));
+            double2 p;
+            project(f, x[it], y[it], z[it], &p.x, &p.y);
+            if (in[it] && !(np >= 3 && inside_polygon(polyf, np, mgf, (float)(p.x - poly[0].x), (float)(p.y - poly[0].y)))) {
+                const uint32_t r = atomicAdd(&nrest, 1u);
+                rest[r] = p;
+                rest_no[r] = (uint16_t)(it * kTileThreads + threadIdx.x);
+            }
         }
         __syncthreads();
         const uint32_t n = nrest;
         for (uint32_t r0 = 0; r0 < n; r0 += kTileThreads) {
             const uint32_t r = r0 + threadIdx.x;
-            double u = 0.0, v = 0.0;
-            float4 p;
+            double2 p;
             bool out = false;
             if (r < n) {
                 p = rest[r];
-                project(f, p.x, p.y, p.z, &u, &v);
-                out = !(np >= 3 && inside_polygon(poly, np, mg, u, v));
+                out = !(np >= 3 && inside_polygon(poly, np, mg, p.x, p.y));
             }
             const uint64_t b = __ballot(out);
             if (b == 0) continue;
@@ -504,9 +495,9 @@ __global__ void __launch_bounds__(kTileThreads) k_hull_filter(
             base = __shfl(base, 0, kWave);
             if (out) {
                 const uint32_t dst = f.ib + base + (uint32_t)__popcll(b & ((1ull << lane) - 1ull));
-                gu[dst] = u;
-                gv[dst] = v;
-                gi[dst] = __float_as_uint(p.w);
+                gu[dst] = p.x;
+                gv[dst] = p.y;
+                gi[dst] = j0 + rest_no[r];
             }
         }
         __syncthreads();
