@@ -2,8 +2,8 @@
 and under planes that tilt (the edges' points then differ by 1e-6 m in the
 plane, and coincident points meet at the corners).  Vertex lists exact against
 the oracle, and the hull stage within ten times what it takes for as many points
-spread over a patch: with a corner of the filter polygon lost, all edge points
-are left to one thread (20 to 80 times)."""
+spread over a patch: with a corner of the filter polygon lost, or its extremes
+compared too coarsely, all edge points are left to one thread (20 to 80 times)."""
 import numpy as np
 import pytest
 
@@ -32,7 +32,7 @@ def _hulls(vm, torch, xyz, tag, n_hyp=16):
     return planes_np(pb), hulls_np(hb), min(times)
 
 
-@pytest.mark.parametrize("side,n,count", [(60, 6666, 60), (150, 60_000, 12)])
+@pytest.mark.parametrize("side,n,count", [(60, 6666, 60), (150, 60_000, 12), (400, 600_000, 4)])
 def test_edges_full_of_points(side, n, count):
     import torch
     import paper_2510_01592_amd as vm
