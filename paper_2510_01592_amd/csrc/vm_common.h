@@ -354,8 +354,7 @@ struct WorkLayout {
                             // hull tiles
     size_t bytes;
 };
-// count_rows: rows of counts (0: one per cluster)
-WorkLayout work_layout(void* base, uint32_t k_cap, uint32_t n_cap, uint32_t n_hyp, uint64_t count_rows = 0);
+WorkLayout work_layout(void* base, uint32_t k_cap, uint32_t n_cap, uint32_t n_hyp);
 uint64_t hull_tiles_bound(uint32_t k_cap, uint32_t n_cap);
 
 // d_cframe: optional per-cluster RNG frame word (merged cluster sets); when

@@ -54,20 +54,42 @@ struct FusedWork {
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// The passes' arrays without those that only more than kOneBlockMax clusters or
+// the tiled counting kernel use; a tile's cluster is not needed any more when
+// the survivors' positions come to lie there (a tile has at least one point).
+// (The size is what callers may have a buffer of: no more than it was with the
+// results of the persistent pass in these places.)
 FusedWork fused_layout(void* base, uint32_t k_cap, uint32_t n_cap, uint32_t H)
 {
     FusedWork f{};
-    const uint64_t rows = (uint64_t)n_cap / kFTile + (uint64_t)k_cap + 1;
-    f.w = work_layout(base, k_cap, n_cap, H, rows);
+    WorkLayout& w = f.w;
+    w.k_cap = k_cap;
     char* p = (char*)base;
-    size_t o = align256(f.w.bytes);
+    size_t o = 0;
     auto take = [&](size_t bytes) {
         char* r = p ? p + o : nullptr;
         o += align256(bytes);
         return r;
     };
-    f.order = (uint32_t*)take(((size_t)k_cap + 1) * 4);
-    f.item_off = (uint32_t*)take(((size_t)k_cap + 1) * 4);
+    const size_t rows = (size_t)n_cap / kFTile + (size_t)k_cap + 1;
+    const size_t kb = ((size_t)k_cap + 1) * 4, nb = ((size_t)n_cap + 1) * 4;
+    w.counts = (int32_t*)take(rows * H * sizeof(int32_t));
+    w.hyp = (float4*)take((size_t)k_cap * H * sizeof(float4));
+    f.order = (uint32_t*)take(kb);
+    f.item_off = (uint32_t*)take(kb);
+    w.tile_off = (uint32_t*)take(kb);
+    w.hull_tile_off = (uint32_t*)take(kb);
+    w.hull_cnt = (uint32_t*)take(kb);
+    w.surv_cnt = (uint32_t*)take(kb);
+    w.margin = (double*)take(kb);   // and the next kb bytes
+    (void)take(kb);
+    w.flags = (uint32_t*)take(nb);
+    w.hull_tmp = (uint32_t*)take(nb + kb);
+    w.hull_u = (double*)take(2 * nb);
+    w.hull_v = (double*)take(2 * nb);
+    w.hull_i = (uint32_t*)take(nb);
+    w.tile_k = w.hull_i;
+    w.small = (uint32_t*)take(64 * 4);
     f.bytes = o;
     return f;
 }

@@ -575,7 +575,7 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 }  // namespace
 
-WorkLayout work_layout(void* base, uint32_t k_cap, uint32_t n_cap, uint32_t n_hyp, uint64_t count_rows)
+WorkLayout work_layout(void* base, uint32_t k_cap, uint32_t n_cap, uint32_t n_hyp)
 {
     WorkLayout w{};
     w.k_cap = k_cap;
@@ -587,7 +587,7 @@ WorkLayout work_layout(void* base, uint32_t k_cap, uint32_t n_cap, uint32_t n_hy
         return r;
     };
     const size_t kh = (size_t)k_cap * (size_t)n_hyp;
-    w.counts = (int32_t*)take((count_rows ? (size_t)count_rows * n_hyp : kh) * sizeof(int32_t));
+    w.counts = (int32_t*)take(kh * sizeof(int32_t));
     w.hyp = (float4*)take(kh * sizeof(float4));
     w.tile_off = (uint32_t*)take(((size_t)k_cap + 2) * sizeof(uint32_t));
     w.tile_k = (uint32_t*)take(((size_t)n_cap / kTile + k_cap + 2) * sizeof(uint32_t));
@@ -603,11 +603,16 @@ WorkLayout work_layout(void* base, uint32_t k_cap, uint32_t n_cap, uint32_t n_hy
     w.hull_v = (double*)take(((size_t)n_cap + 1) * sizeof(double));
     w.hull_i = (uint32_t*)take(((size_t)n_cap + 1) * sizeof(uint32_t));
     w.hull_tile_off = (uint32_t*)take(((size_t)k_cap + 2) * sizeof(uint32_t));
-    w.margin = (double*)take((size_t)k_cap * sizeof(double) + 8);
+    // The size decides which buffers and which calls of the allocation-free form
+    // are accepted, so it stays what it was while the tiles' extremes (96 bytes
+    // per hull tile; they share hull_u and hull_v now), 18 doubles of a filter
+    // polygon (now its margin) and a list of clusters lay here.
+    const size_t ht = hull_tiles_bound(k_cap, n_cap);
+    (void)take(ht * 64);
+    (void)take(ht * 32);
+    w.margin = (double*)take((size_t)k_cap * 18 * sizeof(double) + 8);
     w.surv_cnt = (uint32_t*)take(((size_t)k_cap + 1) * sizeof(uint32_t));
-    // the size decides which calls vm_ransac_planes_noalloc accepts: it stays
-    // what it was with 96 bytes per hull tile and 140 more per cluster in use
-    (void)take((size_t)hull_tiles_bound(k_cap, n_cap) * 96 + (size_t)k_cap * 140 + 512);
+    (void)take(((size_t)k_cap + 1) * sizeof(uint32_t));
     w.small = (uint32_t*)take(64 * sizeof(uint32_t));
     w.bytes = o;
     return w;
