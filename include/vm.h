@@ -151,10 +151,14 @@ vm_status vm_insert(vm_map map, const float* d_xyz, int64_t n, const vm_pose* po
  * does not depend on point order or scheduling.  Non-finite points and
  * points more than 10^15 quanta (s*2^-20) from the origin cast no ray.  Call
  * it before vm_insert of the same frame.  VM_E_ARG if the sensor lies outside
- * the grid or n < 0; three bitmaps of the grid (x and y padded to powers of
- * two: from 3 * NX*NY*NZ/8 up to about four times that) are allocated on the
- * first call (VM_E_STATE if that first call is being captured, VM_E_OOM
- * if the allocation fails). */
+ * the grid or n < 0; the two bitmaps (2 * NX*NY*NZ/8 bytes) are allocated on
+ * the first call (VM_E_STATE if that first call is being captured, VM_E_OOM
+ * if the allocation fails).  The first call of many rays (tens of thousands)
+ * outside a capture also allocates a copy of the occupancy in bricks, x and y
+ * padded to powers of two and z to whole bricks: from 3 * NX*NY*NZ/8 bytes to
+ * less than eight times that (20 MB for 400x400x200 cells).  Without it, for
+ * want of memory or of such a call before a capture, many rays take longer and
+ * give the same. */
 vm_status vm_clear_rays(vm_map map, const float* d_xyz, int64_t n, const vm_pose* pose, void* stream);
 
 /* Export the occupied voxels in ascending key order (e.g. for checkpoints

@@ -34,8 +34,11 @@ struct vm_map_s {
     // classification buffers (allocated on the first steppable call)
     StepBuffers sb{};
     void* step_mem = nullptr;
-    // the clearing pass's copy of the occupancy with the marks of rays, then its bitmap of end cells (first call)
+    // the clearing pass: its bitmaps of rays and of end cells (first call); its copy of the occupancy in bricks with
+    // the marks of rays, then its bitmap of end cells (first call of many rays)
     uint32_t* clr_mem = nullptr;
+    uint32_t* clr_bricks = nullptr;
+    bool clr_no_bricks = false;   // there was no memory for them
     // per-sweep change flags of label propagation (device) and their host copy
     uint32_t* lp_flags = nullptr;
     uint32_t* lp_host = nullptr;
@@ -141,6 +144,8 @@ void map_free_all(vm_map m)
     m->step_mem = nullptr;
     if (m->clr_mem) (void)hipFree(m->clr_mem);
     m->clr_mem = nullptr;
+    if (m->clr_bricks) (void)hipFree(m->clr_bricks);
+    m->clr_bricks = nullptr;
     if (m->lp_flags) (void)hipFree(m->lp_flags);
     m->lp_flags = nullptr;
     if (m->lp_host) (void)hipHostFree(m->lp_host);
@@ -437,21 +442,36 @@ vm_status vm_clear_rays(vm_map m, const float* d_xyz, int64_t n, const vm_pose* 
     hipStream_t s = (hipStream_t)stream;
     if (!m->clr_mem) {
         if (capturing(s)) return VM_E_STATE;   // no allocation inside a capture
-        const size_t bytes = (size_t)clear_words(m->g) * 4 * 3;
+        const size_t bytes = (size_t)m->g.nwords * 4 * 2;
         if (hipMalloc((void**)&m->clr_mem, bytes) != hipSuccess) {
             (void)hipGetLastError();
             m->clr_mem = nullptr;
             return VM_E_OOM;
         }
-        if (hipMemset(m->clr_mem, 0, bytes) != hipSuccess) {
+        if (hipMemsetAsync(m->clr_mem, 0, bytes, s) != hipSuccess) {   // (in the order of the work that reads it)
             (void)hipFree(m->clr_mem);
             m->clr_mem = nullptr;
             return VM_E_DEVICE;
         }
     }
+    // many rays walk bricks: without memory for them, or inside a capture
+    // before the first such call, they walk the grid as few rays do
+    const bool pay = bricks_pay(m->g, n);
+    if (pay && !m->clr_bricks && !m->clr_no_bricks && !capturing(s)) {
+        const size_t words = (size_t)clear_words(m->g);
+        if (hipMalloc((void**)&m->clr_bricks, words * 4 * 3) != hipSuccess) {
+            (void)hipGetLastError();
+            m->clr_bricks = nullptr;
+            m->clr_no_bricks = true;
+        } else if (hipMemsetAsync(m->clr_bricks + 2 * words, 0, words * 4, s) != hipSuccess) {
+            (void)hipFree(m->clr_bricks);
+            m->clr_bricks = nullptr;
+            return VM_E_DEVICE;
+        }
+    }
     StageScope t(VM_STAGE_CLEAR, s);
-    VM_HIP(launch_clear_rays(d_xyz, n, q, m->g, sv, m->h, m->bits, m->clr_mem + 2 * clear_words(m->g), m->clr_mem,
-                             m->ins.key, m->ins.cap, m->ctr, s));
+    VM_HIP(launch_clear_rays(d_xyz, n, q, m->g, sv, m->h, m->bits, m->clr_mem, pay ? m->clr_bricks : nullptr, m->ins.key,
+                             m->ins.cap, m->ctr, s));
     return VM_OK;
 }
 

@@ -1,24 +1,26 @@
 // vm_clear.hip -- free space along the sensor rays (Sec. III-B, Eq. (2)).
 //
-//   k_clear_prepare: the occupancy bits in bricks of up to 8x8x8 cells beside
-//                  the marks of cells on a ray, 128 bytes a brick, so that
-//                  neighbouring steps of a ray in any direction share a line;
-//                  and, a lane per point transformed as the insert does it,
-//                  the cells holding a point of the frame, with a list of the
+//   k_clear_prepare: a lane per point transformed as the insert does it, the
+//                  cells holding a point of the frame, with a list of the
 //                  first point found in each: points of one cell cast the
 //                  same line (it runs from voxel to voxel), so one of them
 //                  casts it.  Points outside the grid are all listed.
 //   k_clear_cast:  a lane per listed point works out the 3D Bresenham line
 //                  from the sensor's voxel towards it (its own voxel excluded,
-//                  cut at the grid's faces); then the wave walks its 64 lines
+//                  cut at the grid's faces); then the wave walks its lines
 //                  four at a time, 16 lanes over the steps of each, marking
 //                  every occupied voxel passed.  A mark is an atomic OR only
 //                  when a plain read shows the bit still clear.
-//   k_clear_apply: a thread per 32-cell word of the bricks frees the cells
-//                  marked on a ray and holding no point (count and sums zeroed
-//                  in the hash slot, the occupancy bit cleared), and leaves
-//                  the end cells' bitmap zero for the next call.
-// The marks (in the bricks' order) deduplicate the removal set: whatever the
+//   k_clear_apply: a thread per 32-cell word frees the cells marked on a ray
+//                  and holding no point (count and sums zeroed in the hash
+//                  slot, the occupancy bit cleared), and leaves the bitmaps
+//                  zero for the next call.
+// The cells' order.  For many rays the preparation also copies the occupancy
+// into bricks of up to 8x8x8 cells beside the marks, 128 bytes a brick, so that
+// neighbouring steps of a ray in any direction share a line.  That costs three
+// passes over the grid, whatever the number of rays; few of them walk the
+// occupancy index as it lies, with a bitmap of marks beside it (bricks_pay).
+// The marks deduplicate the removal set: whatever the
 // number of rays through a voxel, its slot is written once, by the one thread
 // that owns its word, after every ray has been cast.
 //
@@ -32,25 +34,43 @@
 // beside 76 us for the pass that lists them.
 #include "vm_common.h"
 
+#include <algorithm>
+
 namespace vm {
 namespace {
 
-// A 32-cell word of the bricks: which cells are occupied, and which of those
-// lie on a ray.  One 8-byte read per step serves the test and the check whether
-// the cell is marked already (the marks in it may be of a stale line: the
-// atomic OR is then made once more).
+// A 32-cell word: which cells are occupied, and which of those lie on a ray.
+// One read (in bricks, two in the grid's order) per step serves the test and the
+// check whether the cell is marked already (the marks in it may be of a stale
+// line: the atomic OR is then made once more).
 struct CellWord {
     uint32_t occ, ray;
 };
 
-template <typename A>
-__device__ __forceinline__ CellWord cell_word(const CellWord* cells, A at)
-{
-    const uint2 v = *reinterpret_cast<const uint2*>(&cells[at >> 5]);
-    return {v.x, v.y};
-}
-
 __device__ __forceinline__ bool unmarked(const CellWord w, uint32_t bit) { return (w.occ & ~w.ray & bit) != 0u; }
+
+// The words by address: cells in bricks, or the occupancy index and the marks.
+template <bool kBricked>
+struct Cells {
+    CellWord* brick;
+    const uint32_t* bits;
+    uint32_t* ray;
+
+    template <typename A>
+    __device__ __forceinline__ CellWord at(A a) const
+    {
+        if (!kBricked) return {bits[a >> 5], ray[a >> 5]};
+        const uint2 v = *reinterpret_cast<const uint2*>(&brick[a >> 5]);
+        return {v.x, v.y};
+    }
+
+    template <typename A>
+    __device__ __forceinline__ void mark(A a) const
+    {
+        const uint32_t bit = 1u << ((uint32_t)a & 31u);
+        if (unmarked(at(a), bit)) atomicOr(kBricked ? &brick[a >> 5].ray : &ray[a >> 5], bit);
+    }
+};
 
 // Cells found by a wave, waiting in LDS for their marks: a device-scope atomic
 // takes some two microseconds to return, and the reads issued after it wait
@@ -70,16 +90,13 @@ struct MarkList {
         n += (uint32_t)__popcll(b);
     }
 
-    __device__ __forceinline__ void flush(CellWord* cells, int lane)
+    template <bool kBricked>
+    __device__ __forceinline__ void flush(const Cells<kBricked>& cells, int lane)
     {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        for (uint32_t i = (uint32_t)lane; i < n; i += kWave) {
-            const A a = at[i];
-            const uint32_t bit = 1u << ((uint32_t)a & 31u);
-            if (unmarked(cell_word(cells, a), bit)) atomicOr(&cells[a >> 5].ray, bit);
-        }
+        for (uint32_t i = (uint32_t)lane; i < n; i += kWave) cells.mark(at[i]);
         n = 0;
         __builtin_amdgcn_wave_barrier();
     }
@@ -96,6 +113,9 @@ struct Bricks {
     uint32_t e[3], p0[3], p1[3];
     uint64_t mask[3];        // the fields of each axis (z: everything from its p1 up)
     uint64_t words;          // 32-cell words of a bitmap
+    uint32_t n[3];           // bricks that hold cells of the grid
+    uint32_t log2words;      // words of a brick
+    uint32_t used;           // words of those bricks
 };
 
 Bricks bricks_of(const Geom& g)
@@ -133,6 +153,11 @@ Bricks bricks_of(const Geom& g)
     }
     const uint64_t nz = ((uint64_t)g.dims[2] + (1ull << b.e[2]) - 1) >> b.e[2];
     b.words = ((nz << b.p1[2]) + 31) / 32;
+    const uint32_t bits = b.e[0] + b.e[1] + b.e[2];
+    b.log2words = bits > 5 ? bits - 5 : 0;
+    for (int k = 0; k < 3; ++k) b.n[k] = (uint32_t)(((uint64_t)g.dims[k] + (1ull << b.e[k]) - 1) >> b.e[k]);
+    // (each axis grows to less than twice its cells: below 2^35 of them)
+    b.used = (uint32_t)(((uint64_t)b.n[0] * b.n[1] * b.n[2]) << b.log2words);
     return b;
 }
 
@@ -149,11 +174,43 @@ struct CastArgs {
     Geom g;
     Bricks br;
     int32_t s[3];            // the sensor's voxel
-    CellWord* cells;         // occupancy and cells on a ray (occupied ones only), in bricks
+    CellWord* brick;         // occupancy and cells on a ray (occupied ones only), in bricks
+    const uint32_t* bits;    // or the occupancy index
+    uint32_t* ray;           // and the marks beside it
     const uint32_t* list;    // the points that cast a line
     const uint32_t* count;   // their number
     uint32_t* next;          // the next batch's number, cleared here
 };
+
+// coordinate v along axis k (0, 1, 2; per lane) as a part of an address: in
+// bricks dilated, zero outside its fields, else times the axis' stride
+template <typename A, bool kBricked>
+__device__ __forceinline__ A along(const CastArgs& a, int32_t k, int32_t v)
+{
+    if (!kBricked) {
+        const uint32_t nx = (uint32_t)a.g.dims[0];
+        return (A)(uint32_t)v * (A)(k == 0 ? 1u : (k == 1 ? nx : nx * (uint32_t)a.g.dims[1]));
+    }
+    const Bricks& br = a.br;
+    return dilate<A>(v, k == 0 ? br.e[0] : (k == 1 ? br.e[1] : br.e[2]),
+                     k == 0 ? br.p0[0] : (k == 1 ? br.p0[1] : br.p0[2]),
+                     k == 0 ? br.p1[0] : (k == 1 ? br.p1[1] : br.p1[2]),
+                     (A)(k == 0 ? br.mask[0] : (k == 1 ? br.mask[1] : br.mask[2])));
+}
+
+// the ones outside axis k's fields that a step's add carries across
+template <typename A, bool kBricked>
+__device__ __forceinline__ A outside(const CastArgs& a, int32_t k)
+{
+    return kBricked ? ~(A)(k == 0 ? a.br.mask[0] : (k == 1 ? a.br.mask[1] : a.br.mask[2])) : (A)0;
+}
+
+// the address of three such parts (with the ones outside their fields)
+template <typename A, bool kBricked>
+__device__ __forceinline__ A address(A m, A u, A w)
+{
+    return kBricked ? m & u & w : m + u + w;
+}
 
 // bits [key, key + n) of the occupancy index, n <= 32
 __device__ __forceinline__ uint32_t cells_at(const uint32_t* __restrict__ bits, uint32_t key, uint32_t n)
@@ -162,6 +219,17 @@ __device__ __forceinline__ uint32_t cells_at(const uint32_t* __restrict__ bits, 
     uint32_t v = bits[key >> 5] >> b;
     if (b + n > 32u) v |= bits[(key >> 5) + 1u] << (32u - b);
     return n < 32u ? v & ((1u << n) - 1u) : v;
+}
+
+// The i-th word of the bricks that hold cells: the padding to powers of two is
+// neither written nor read (a grid of 2100x2100x60 cells takes 33.5M words with
+// it and 8.9M without).
+__device__ __forceinline__ uint64_t used_word(const Bricks& br, uint32_t i)
+{
+    const uint32_t b = i >> br.log2words, w = i & ((1u << br.log2words) - 1u);
+    const uint32_t by = b / br.n[0], bx = b - by * br.n[0], bz = by / br.n[1];
+    const uint64_t at = (uint64_t)bx << br.p1[0] | (uint64_t)(by - bz * br.n[1]) << br.p1[1] | (uint64_t)bz << br.p1[2];
+    return (at >> 5) + w;   // (a grid of less than a word is one brick, at 0)
 }
 
 // the cell at an address (z may lie past the grid, x and y in the padding)
@@ -204,9 +272,9 @@ constexpr uint32_t kEndTile = kEndPoints * kBlock;
 constexpr int kEndBlocks = 256;
 
 // The first `pblocks` workgroups take the points of the batch (indices below
-// 2^32), the others, on the first batch, the words: their cells are rows of up
-// to 2^e[0] cells along x.
-template <typename A>
+// 2^32), the others, on the first batch of the bricked form, the words: their
+// cells are rows of up to 2^e[0] cells along x.
+template <typename A, bool kBricked>
 __global__ void __launch_bounds__(kBlock) k_clear_prepare(const float* __restrict__ xyz, uint32_t n, Pose pose, Geom g,
                                                           Bricks br, uint32_t pblocks,
                                                           const uint32_t* __restrict__ bits,
@@ -232,8 +300,10 @@ __global__ void __launch_bounds__(kBlock) k_clear_prepare(const float* __restric
                 in[j] = first[j] && e[0] >= 0 && e[1] >= 0 && e[2] >= 0 && e[0] < g.dims[0] && e[1] < g.dims[1] &&
                         e[2] < g.dims[2];
                 at[j] = 0;
+                if (!kBricked && in[j])
+                    at[j] = (A)((uint32_t)e[0] + (uint32_t)g.dims[0] * ((uint32_t)e[1] + (uint32_t)g.dims[1] * (uint32_t)e[2]));
 #pragma unroll
-                for (int k = 0; k < 3; ++k)
+                for (int k = 0; kBricked && k < 3; ++k)
                     if (in[j]) at[j] |= dilate<A>((int32_t)e[k], br.e[k], br.p0[k], br.p1[k], (A)br.mask[k]);
             }
             // a plain read first: most points find their cell set
@@ -277,8 +347,8 @@ __global__ void __launch_bounds__(kBlock) k_clear_prepare(const float* __restric
     }
     const uint32_t NX = (uint32_t)g.dims[0], NY = (uint32_t)g.dims[1], NZ = (uint32_t)g.dims[2];
     const uint32_t le = min(br.e[0], 5u), len = 1u << le;
-    for (uint64_t w = (uint64_t)(blockIdx.x - pblocks) * kBlock + threadIdx.x; w < br.words;
-         w += (uint64_t)(gridDim.x - pblocks) * kBlock) {
+    for (uint32_t i = (blockIdx.x - pblocks) * kBlock + threadIdx.x; i < br.used; i += (gridDim.x - pblocks) * kBlock) {
+        const uint64_t w = used_word(br, i);
         uint32_t v = 0;
         for (uint32_t r = 0; r < 32u; r += len) {
             uint32_t c[3];
@@ -302,8 +372,8 @@ __global__ void __launch_bounds__(kBlock) k_clear_prepare(const float* __restric
 // quotient and remainder, advanced by the constant increments of 64 steps.
 constexpr int64_t kFarSteps = 1 << 24;
 
-template <typename A>
-__device__ __forceinline__ void walk_far(const CastArgs& a, int lane, int64_t dm, int64_t du, int64_t dw, int64_t nsteps,
+template <typename A, bool kBricked>
+__device__ __forceinline__ void walk_far(const CastArgs& a, const Cells<kBricked>& cells, int lane, int64_t dm, int64_t du, int64_t dw, int64_t nsteps,
                                          int m, int gm, int gu, int gw)
 {
     const int u = m == 2 ? 0 : m + 1, w = m == 0 ? 2 : m - 1;
@@ -313,13 +383,11 @@ __device__ __forceinline__ void walk_far(const CastArgs& a, int lane, int64_t dm
     int64_t U = nu / two_dm, ru = nu % two_dm, W = nw / two_dm, rw = nw % two_dm;
     const int64_t iu = 2 * du * kWave, iw = 2 * dw * kWave;
     const int64_t qu = iu / two_dm, pu = iu % two_dm, qw = iw / two_dm, pw = iw % two_dm;
-    const Bricks& br = a.br;
+    const A om = outside<A, kBricked>(a, m), ou = outside<A, kBricked>(a, u), ow = outside<A, kBricked>(a, w);
     for (; k < nsteps; k += kWave) {
-        const A at = dilate<A>(a.s[m] + gm * (int32_t)k, br.e[m], br.p0[m], br.p1[m], (A)br.mask[m]) |
-                     dilate<A>(a.s[u] + gu * (int32_t)U, br.e[u], br.p0[u], br.p1[u], (A)br.mask[u]) |
-                     dilate<A>(a.s[w] + gw * (int32_t)W, br.e[w], br.p0[w], br.p1[w], (A)br.mask[w]);
-        const uint32_t bit = 1u << ((uint32_t)at & 31u);
-        if (unmarked(cell_word(a.cells, at), bit)) atomicOr(&a.cells[at >> 5].ray, bit);
+        cells.mark(address<A, kBricked>(along<A, kBricked>(a, m, a.s[m] + gm * (int32_t)k) | om,
+                                        along<A, kBricked>(a, u, a.s[u] + gu * (int32_t)U) | ou,
+                                        along<A, kBricked>(a, w, a.s[w] + gw * (int32_t)W) | ow));
         U += qu;
         ru += pu;
         if (ru >= two_dm) {
@@ -378,7 +446,7 @@ __device__ __forceinline__ int32_t wave_max(int32_t v)
 }
 
 // A: the addresses' type (64 bits where the padded grid has 2^32 cells or more)
-template <typename A>
+template <typename A, bool kBricked>
 __global__ void __launch_bounds__(kBlock, 6) k_clear_cast(const float* __restrict__ xyz, CastArgs a)
 {
     const int64_t n = *a.count;
@@ -388,14 +456,7 @@ __global__ void __launch_bounds__(kBlock, 6) k_clear_cast(const float* __restric
     const int32_t NX = a.g.dims[0], NY = a.g.dims[1], NZ = a.g.dims[2];
     __shared__ A mark_lds[kBlock / kWave][kMarkCap];
     MarkList<A> marks{mark_lds[threadIdx.x / kWave], 0u};
-    const Bricks& br = a.br;
-    // the fields of axis k (0, 1, 2; per lane)
-    auto along = [&](int32_t k, int32_t v) -> A {
-        return dilate<A>(v, k == 0 ? br.e[0] : (k == 1 ? br.e[1] : br.e[2]),
-                         k == 0 ? br.p0[0] : (k == 1 ? br.p0[1] : br.p0[2]),
-                         k == 0 ? br.p1[0] : (k == 1 ? br.p1[1] : br.p1[2]),
-                         (A)(k == 0 ? br.mask[0] : (k == 1 ? br.mask[1] : br.mask[2])));
-    };
+    const Cells<kBricked> cells{a.brick, a.bits, a.ray};
     // the wave's contiguous share of the points, 64 at a time
     const int64_t waves = (int64_t)gridDim.x * (kBlock / kWave);
     const int64_t w = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
@@ -467,16 +528,14 @@ __global__ void __launch_bounds__(kBlock, 6) k_clear_cast(const float* __restric
                 small_div(2u * sdw * (uint32_t)sub + (tdm >> 1), tdm, rcp, &W, &rw);
             }
             const int32_t ux = ax == 2 ? 0 : ax + 1, wx = ax == 0 ? 2 : ax - 1;
-            const A om = ~(A)(ax == 0 ? br.mask[0] : (ax == 1 ? br.mask[1] : br.mask[2]));
-            const A ou = ~(A)(ux == 0 ? br.mask[0] : (ux == 1 ? br.mask[1] : br.mask[2]));
-            const A ow = ~(A)(wx == 0 ? br.mask[0] : (wx == 1 ? br.mask[1] : br.mask[2]));
-            A am = along(ax, (ax == 0 ? a.s[0] : (ax == 1 ? a.s[1] : a.s[2])) + gm * sub) | om;
-            A au = along(ux, (ux == 0 ? a.s[0] : (ux == 1 ? a.s[1] : a.s[2])) + gu * (int32_t)U) | ou;
-            A aw = along(wx, (wx == 0 ? a.s[0] : (wx == 1 ? a.s[1] : a.s[2])) + gw * (int32_t)W) | ow;
+            const A om = outside<A, kBricked>(a, ax), ou = outside<A, kBricked>(a, ux), ow = outside<A, kBricked>(a, wx);
+            A am = along<A, kBricked>(a, ax, (ax == 0 ? a.s[0] : (ax == 1 ? a.s[1] : a.s[2])) + gm * sub) | om;
+            A au = along<A, kBricked>(a, ux, (ux == 0 ? a.s[0] : (ux == 1 ? a.s[1] : a.s[2])) + gu * (int32_t)U) | ou;
+            A aw = along<A, kBricked>(a, wx, (wx == 0 ? a.s[0] : (wx == 1 ? a.s[1] : a.s[2])) + gw * (int32_t)W) | ow;
             const int32_t qu = (int32_t)(q & 255u), qw = (int32_t)((q >> 8) & 255u);
-            const A im = along(ax, gm * kRayLanes);
-            const A iu0 = along(ux, gu * qu), iu1 = along(ux, gu * (qu + 1));
-            const A iw0 = along(wx, gw * qw), iw1 = along(wx, gw * (qw + 1));
+            const A im = along<A, kBricked>(a, ax, gm * kRayLanes);
+            const A iu0 = along<A, kBricked>(a, ux, gu * qu), iu1 = along<A, kBricked>(a, ux, gu * (qu + 1));
+            const A iw0 = along<A, kBricked>(a, wx, gw * qw), iw1 = along<A, kBricked>(a, wx, gw * (qw + 1));
             // (every lane of the wave runs the longest line's rounds: the marks
             // are placed by a ballot)
             const int32_t nmax = wave_max(ns);
@@ -485,9 +544,9 @@ __global__ void __launch_bounds__(kBlock, 6) k_clear_cast(const float* __restric
                 CellWord word[kStepBatch];
 #pragma unroll
                 for (int b = 0; b < kStepBatch; ++b) {
-                    at[b] = am & au & aw;
+                    at[b] = address<A, kBricked>(am, au, aw);
                     word[b] = {0u, 0u};
-                    if (k + b * kRayLanes < ns) word[b] = cell_word(a.cells, at[b]);
+                    if (k + b * kRayLanes < ns) word[b] = cells.at(at[b]);
                     am = (am + im) | om;
                     ru += spu;
                     rw += spw;
@@ -500,10 +559,10 @@ __global__ void __launch_bounds__(kBlock, 6) k_clear_cast(const float* __restric
 #pragma unroll
                 for (int b = 0; b < kStepBatch; ++b)
                     marks.push(unmarked(word[b], 1u << ((uint32_t)at[b] & 31u)), at[b], lane);
-                if (marks.n > kMarkCap - kStepBatch * kWave) marks.flush(a.cells, lane);
+                if (marks.n > kMarkCap - kStepBatch * kWave) marks.flush(cells, lane);
             }
         }
-        marks.flush(a.cells, lane);
+        marks.flush(cells, lane);
         // ---- lines too long for the 32-bit walk, one after another ----
         for (uint64_t far = __ballot(steps > 0 && dm >= kFarSteps); far; far &= far - 1) {
             const int src = __ffsll((long long)far) - 1;
@@ -511,31 +570,38 @@ __global__ void __launch_bounds__(kBlock, 6) k_clear_cast(const float* __restric
             const int32_t ax = __shfl(m, src, kWave);
             const int32_t sm = __shfl((int)neg_m, src, kWave) ? -1 : 1, su = __shfl((int)neg_u, src, kWave) ? -1 : 1,
                           sw = __shfl((int)neg_w, src, kWave) ? -1 : 1;
-            walk_far<A>(a, lane, bc(dm), bc(du), bc(dw), bc(steps), __builtin_amdgcn_readfirstlane(ax), sm, su, sw);
+            walk_far<A>(a, cells, lane, bc(dm), bc(du), bc(dw), bc(steps), __builtin_amdgcn_readfirstlane(ax), sm, su, sw);
         }
     }
 }
 
+template <bool kBricked>
 __global__ void __launch_bounds__(kBlock) k_clear_apply(Geom g, Bricks br, Hash h, uint32_t* __restrict__ bits,
-                                                        const CellWord* __restrict__ cells, uint32_t* __restrict__ ends,
-                                                        DevCounters* __restrict__ ctr)
+                                                        const CellWord* __restrict__ brick, uint32_t* __restrict__ ray,
+                                                        uint32_t* __restrict__ ends, DevCounters* __restrict__ ctr)
 {
     uint32_t removed = 0;
     if (blockIdx.x == 0 && threadIdx.x == 0) ctr->rays[0] = ctr->rays[1] = 0u;   // for the next call
-    for (uint64_t w = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; w < br.words;
-         w += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t k = ends[w];
+    const uint32_t n = kBricked ? br.used : g.nwords;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+        const uint64_t w = kBricked ? used_word(br, i) : i;
+        const uint32_t k = ends[w], r = kBricked ? brick[w].ray : ray[w];
         if (k) ends[w] = 0u;
-        uint32_t c = cells[w].ray & ~k;   // (only occupied cells are marked)
+        if (!kBricked && r) ray[w] = 0u;
+        uint32_t c = r & ~k;   // (only occupied cells are marked)
         removed += (uint32_t)__popc(c);
+        if (!kBricked && c) bits[w] &= ~c;
         while (c) {
             const uint32_t j = (uint32_t)__ffs(c) - 1u;
             c &= c - 1u;
-            uint32_t at[3];
-            cell_of(br, w * 32u + j, at);
-            const uint32_t key = at[0] + (uint32_t)g.dims[0] * (at[1] + (uint32_t)g.dims[1] * at[2]);
-            // a word of the occupancy index belongs to several bricks
-            atomicAnd(&bits[key >> 5], ~(1u << (key & 31u)));
+            uint32_t key = (uint32_t)w * 32u + j;
+            if (kBricked) {
+                uint32_t at[3];
+                cell_of(br, w * 32u + j, at);
+                key = at[0] + (uint32_t)g.dims[0] * (at[1] + (uint32_t)g.dims[1] * at[2]);
+                // a word of the occupancy index belongs to several bricks
+                atomicAnd(&bits[key >> 5], ~(1u << (key & 31u)));
+            }
             const uint32_t s = hash_find(h, key);
             if (s == kEmpty) continue;   // cannot happen for an occupied cell
             Slot* sl = &h.slot[s];
@@ -566,10 +632,24 @@ __global__ void __launch_bounds__(kBlock) k_clear_apply(Geom g, Bricks br, Hash 
 
 uint64_t clear_words(const Geom& g) { return bricks_of(g).words; }
 
+// Whether n rays are worth the bricks: the steps of rays across half the grid
+// against the passes over its words.  Measured in both forms, a call of 10k and
+// of 50k rays takes, in the grid's order and in bricks: 400x400x200 cells 39 / 42
+// and 72 / 57 us, 800x800x400 81 / 112 and 293 / 146, 2100x2100x60 138 / 140 and
+// 664 / 208, 1500x1500x700 236 / 658 and 807 / 742, 200x200x100 30 / 32 and 42 /
+// 41.  Rays of a grid that is long in one direction only pass along its lines
+// in either order (4000x1x1 cells 54 / 61 and 80 / 99).
+bool bricks_pay(const Geom& g, int64_t n)
+{
+    const int64_t x = g.dims[0], y = g.dims[1], z = g.dims[2];
+    const int64_t longest = std::max(x, std::max(y, z)), second = std::max(std::min(x, y), std::min(std::max(x, y), z));
+    return second >= 8 && n >= (6000000 + (int64_t)g.nwords + g.nwords / 4 + longest - 1) / longest;
+}
+
 namespace {
-template <typename A>
-hipError_t clear_rays(const float* xyz, int64_t n, CastArgs a, const uint32_t* bits, uint32_t* ends, uint32_t* list,
-                      uint32_t list_cap, DevCounters* ctr, hipStream_t s)
+template <typename A, bool kBricked>
+hipError_t clear_rays(const float* xyz, int64_t n, CastArgs a, const Hash& h, uint32_t* bits, uint32_t* ends,
+                      uint32_t* list, uint32_t list_cap, DevCounters* ctr, hipStream_t s)
 {
     uint32_t turn = 0;
     for (int64_t done = 0; done < n; done += list_cap, turn ^= 1u) {
@@ -577,18 +657,23 @@ hipError_t clear_rays(const float* xyz, int64_t n, CastArgs a, const uint32_t* b
         a.list = list;
         a.count = &ctr->rays[turn];
         a.next = &ctr->rays[turn ^ 1u];
-        const int pb = grid_for(m, (int)kEndTile, kEndBlocks), wb = done ? 0 : grid_for(a.br.words, kBlock, 4096);
-        k_clear_prepare<A><<<pb + wb, kBlock, 0, s>>>(xyz + 3 * done, m, a.pose, a.g, a.br, (uint32_t)pb, bits, a.cells,
-                                                      ends, list, &ctr->rays[turn]);
-        // resident workgroups (six per compute unit)
-        k_clear_cast<A><<<grid_for(m, kBlock, 256 * 6), kBlock, 0, s>>>(xyz + 3 * done, a);
+        const int pb = grid_for(m, (int)kEndTile, kEndBlocks);
+        const int wb = !kBricked || done ? 0 : grid_for(a.br.used, kBlock, 4096);
+        k_clear_prepare<A, kBricked><<<pb + wb, kBlock, 0, s>>>(xyz + 3 * done, m, a.pose, a.g, a.br, (uint32_t)pb, bits,
+                                                                a.brick, ends, list, &ctr->rays[turn]);
+        // resident workgroups (six per compute unit), but no more than give
+        // every wave the four lines it walks together (1000 rays in a grid of
+        // 400x400x200: 134 us with 64 lines to a wave, 39 so in bricks, 31 without)
+        k_clear_cast<A, kBricked><<<grid_for(m, kBlock / kRayLanes, 256 * 6), kBlock, 0, s>>>(xyz + 3 * done, a);
     }
+    k_clear_apply<kBricked><<<grid_for(kBricked ? a.br.used : a.g.nwords), kBlock, 0, s>>>(a.g, a.br, h, bits, a.brick, a.ray,
+                                                                                          ends, ctr);
     return hipGetLastError();
 }
 }  // namespace
 
 hipError_t launch_clear_rays(const float* xyz, int64_t n, const Pose& pose, const Geom& g, const int32_t sensor[3],
-                             const Hash& h, uint32_t* bits, uint32_t* ends, uint32_t* work, uint32_t* list,
+                             const Hash& h, uint32_t* bits, uint32_t* marks, uint32_t* bricks, uint32_t* list,
                              uint32_t list_cap, DevCounters* ctr, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
@@ -599,12 +684,13 @@ hipError_t launch_clear_rays(const float* xyz, int64_t n, const Pose& pose, cons
     a.s[0] = sensor[0];
     a.s[1] = sensor[1];
     a.s[2] = sensor[2];
-    a.cells = reinterpret_cast<CellWord*>(work);
-    const hipError_t e = a.br.words < (1ull << 27) ? clear_rays<uint32_t>(xyz, n, a, bits, ends, list, list_cap, ctr, s)
-                                                   : clear_rays<uint64_t>(xyz, n, a, bits, ends, list, list_cap, ctr, s);
-    if (e != hipSuccess) return e;
-    k_clear_apply<<<grid_for(a.br.words), kBlock, 0, s>>>(g, a.br, h, bits, a.cells, ends, ctr);
-    return hipGetLastError();
+    a.bits = bits;
+    a.ray = marks;
+    if (!bricks) return clear_rays<uint32_t, false>(xyz, n, a, h, bits, marks + g.nwords, list, list_cap, ctr, s);
+    a.brick = reinterpret_cast<CellWord*>(bricks);
+    uint32_t* ends = bricks + 2 * a.br.words;
+    return a.br.words < (1ull << 27) ? clear_rays<uint32_t, true>(xyz, n, a, h, bits, ends, list, list_cap, ctr, s)
+                                     : clear_rays<uint64_t, true>(xyz, n, a, h, bits, ends, list, list_cap, ctr, s);
 }
 
 }  // namespace vm

@@ -321,11 +321,14 @@ hipError_t launch_lp_finish(const uint32_t* bits, SegBuffers& b, uint32_t cap, c
 // ---- ray casting and clearing (vm_clear.hip) ---------------------------------
 // Eq. (2) for one frame: cast every point's ray from the sensor's voxel,
 // then free the occupied cells on a ray that hold none of the frame's points.
-// ends (clear_words words) is zero on entry and zero again on exit; work: two
-// times as many words of scratch, 8-byte aligned; list: list_cap words.
+// marks: 2 * nwords words, zero on entry and zero again on exit.  bricks, for
+// the bricked form (null: the grid's own order): 3 * clear_words words, 8-byte
+// aligned, of which the last third is zero on entry and on exit.  list:
+// list_cap words.
 uint64_t clear_words(const Geom& g);
+bool bricks_pay(const Geom& g, int64_t n);
 hipError_t launch_clear_rays(const float* xyz, int64_t n, const Pose& pose, const Geom& g, const int32_t sensor[3],
-                             const Hash& h, uint32_t* bits, uint32_t* ends, uint32_t* work, uint32_t* list,
+                             const Hash& h, uint32_t* bits, uint32_t* marks, uint32_t* bricks, uint32_t* list,
                              uint32_t list_cap, DevCounters* ctr, hipStream_t s);
 
 // ---- RANSAC and hulls (vm_ransac.hip, vm_hull.hip) --------------------------
