@@ -406,6 +406,22 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// largest k < K with off[k] <= x (off does not decrease, off[0] <= x), found by a
+// whole wave, 64 probes at a time: two dependent reads for up to 4096 entries,
+// three for 262144, where a bisection takes 12 and 18
+__device__ __forceinline__ uint32_t last_at_or_below(const uint32_t* __restrict__ off, uint32_t K, uint32_t x)
+{
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    uint32_t lo = 0, n = K;
+    while (n > 1) {
+        const uint32_t step = (n + kWave - 1) / kWave, i = lo + lane * step;
+        const bool le = lane * step < n && off[min(i, K - 1u)] <= x;
+        lo += ((uint32_t)__popcll(__ballot(le)) - 1u) * step;
+        n = min(step, K - lo);
+    }
+    return lo;
+}
+
 __device__ __forceinline__ double wave_max_d(double v)
 {
 #pragma unroll

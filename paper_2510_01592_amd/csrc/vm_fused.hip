@@ -8,7 +8,8 @@
 // (4096-point tile, chunk of hypotheses), or, for a cluster of at most
 // small_max points, one for all its hypotheses.  A grid-wide pass draws and
 // fits every hypothesis plane.  The persistent workgroups then take items
-// from the queue with one atomic each (no workgroup ever waits for another);
+// from the queue with one atomic each (no workgroup ever waits for another),
+// then those of the smallest clusters in turn;
 // each wave keeps up to 128 of the item's planes in registers, sweeps the
 // tile's points on the matrix cores (PlaneGroups) and stores its integer
 // counts in the tile's own row, so the sums do not depend on the order.
@@ -42,8 +43,16 @@ constexpr uint32_t kFMaxChunk = kFGroups * kFBlock;  // hypotheses per item (512
 constexpr uint32_t kFSmallMax = 256;                 // most points of a cluster with one item
 constexpr int kBuckets = 33;                         // cost classes: floor(log2(points)) + 1
 
+// Clusters of fewer points are not queued: their items, the last in cost order,
+// go to the workgroups in turn.  The queue's head takes an atomic every 12 ns,
+// which is all that 60000 clusters of at most 11 points waited for (700 us for
+// their counting, 162 so); items this small need no balance.
+constexpr uint32_t kFQueueMin = 256;
+constexpr int kFQueueClass = kBuckets - 1 - 8;   // the last class of queued clusters
+static_assert(kFQueueMin == 1u << 8, "a class boundary");
+
 // device scalars of the queue, beside those of the shared passes
-constexpr int kQueueItems = 16, kQueueHead = 17;
+constexpr int kQueueItems = 16, kQueueHead = 17, kAllItems = 18;
 
 struct FusedWork {
     WorkLayout w;          // the shared passes'; its counts hold the tiles' rows, [tiles][H]
@@ -142,7 +151,10 @@ __global__ void __launch_bounds__(kOneBlockThreads) k_fused_prepare(const uint32
         f.w.small[0] = K;
         f.w.small[1] = tiles[0];
         f.w.small[3] = 0;
-        f.w.small[kQueueItems] = tot[0];
+        // (a class' start has moved to its end: the queued clusters' number)
+        const uint32_t queued = bucket[kFQueueClass];
+        f.w.small[kQueueItems] = queued < K ? f.item_off[queued] : tot[0];
+        f.w.small[kAllItems] = tot[0];
         f.w.small[kQueueHead] = 0;
         f.item_off[K] = tot[0];
         if (meta[0] > out_k_cap) atomicOr(status, (uint32_t)VM_FLAG_CLUSTERS_CAP);
@@ -169,23 +181,27 @@ __global__ void __launch_bounds__(kFBlock, 4) k_fused(FusedArgs a)
     const FusedWork& f = a.f;
     const Split& sp = a.sp;
     const uint32_t H = sp.H;
-    const uint32_t K = f.w.small[0], total = f.w.small[kQueueItems];
+    const uint32_t K = f.w.small[0], queued = f.w.small[kQueueItems], total = f.w.small[kAllItems];
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    for (;;) {
-        if (threadIdx.x == 0) s_item = atomicAdd(&f.w.small[kQueueHead], 1u);
-        __syncthreads();
-        const uint32_t item = __builtin_amdgcn_readfirstlane(s_item);
-        __syncthreads();   // s_item is rewritten for the next item
-        if (item >= total) break;   // workgroup-uniform: every wave leaves
-        // the queue position holding the item: largest i with item_off[i] <= item
-        uint32_t lo = 0, hi = K;
-        while (hi - lo > 1) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (f.item_off[mid] <= item) lo = mid;
-            else hi = mid;
+    uint32_t own = queued + blockIdx.x;   // the next item in turn
+    for (bool queue = queued != 0;;) {
+        uint32_t item = own;
+        if (queue) {
+            if (threadIdx.x == 0) s_item = atomicAdd(&f.w.small[kQueueHead], 1u);
+            __syncthreads();
+            item = __builtin_amdgcn_readfirstlane(s_item);
+            __syncthreads();   // s_item is rewritten for the next item
+            queue = item < queued;   // (workgroup-uniform)
+            if (!queue) item = own;
         }
-        const uint32_t k = f.order[lo], j = item - f.item_off[lo];
+        if (!queue) {
+            if (item >= total) break;   // workgroup-uniform: every wave leaves
+            own += gridDim.x;
+        }
+        // the queue position holding the item
+        const uint32_t i = __builtin_amdgcn_readfirstlane(last_at_or_below(f.item_off, K, item));
+        const uint32_t k = f.order[i], j = item - f.item_off[i];
         const uint32_t base = a.off[k], n = a.off[k + 1] - base;
         const bool small = is_small(n, sp);
         const uint32_t c0 = small ? 0u : j % sp.nch, c1 = small ? sp.nch : c0 + 1, t = small ? 0u : j / sp.nch;

@@ -72,22 +72,6 @@ __device__ __forceinline__ ClusterFrame cluster_frame(uint32_t k, const uint32_t
     return f;
 }
 
-// largest k with tile_off[k] <= t (tile_off is an exclusive scan of K entries),
-// found by a whole wave, 64 probes at a time: two dependent reads for up to
-// 4096 clusters, which is what a tile waits for before anything else
-__device__ __forceinline__ uint32_t cluster_of_tile(const uint32_t* __restrict__ tile_off, uint32_t K, uint32_t t)
-{
-    const uint32_t lane = threadIdx.x & (kWave - 1);
-    uint32_t lo = 0, n = K;
-    while (n > 1) {
-        const uint32_t step = (n + kWave - 1) / kWave, i = lo + lane * step;
-        const bool le = lane * step < n && tile_off[min(i, K - 1u)] <= t;
-        lo += ((uint32_t)__popcll(__ballot(le)) - 1u) * step;
-        n = min(step, K - lo);
-    }
-    return lo;
-}
-
 // tiles of cluster k: [tile_off[k], end)
 __device__ __forceinline__ uint32_t tiles_end(const uint32_t* tile_off, uint32_t k, uint32_t K, uint32_t total)
 {
@@ -205,7 +189,7 @@ __global__ void __launch_bounds__(kTileThreads) k_hull_extremes(
     float sn, cs;
     sincospif((float)dir / (kDirs / 2), &sn, &cs);
     for (uint32_t t = blockIdx.x; t < T; t += gridDim.x) {
-        const uint32_t k = cluster_of_tile(tile_off, K, t);
+        const uint32_t k = last_at_or_below(tile_off, K, t);
         const ClusterFrame f = cluster_frame(k, off, X, Y, Z, plane, in_off, in_idx);
         const uint32_t j0 = (t - tile_off[k]) * kHullTile, m = min((uint32_t)kHullTile, f.m - j0);
         // a wave projects and then searches its own quarter of the tile; what
@@ -451,7 +435,7 @@ __global__ void __launch_bounds__(kTileThreads) k_hull_filter(
     const uint32_t T = small[6];
     const int lane = threadIdx.x & (kWave - 1);
     for (uint32_t t = blockIdx.x; t < T; t += gridDim.x) {
-        const uint32_t k = cluster_of_tile(tile_off, K, t);
+        const uint32_t k = last_at_or_below(tile_off, K, t);
         const ClusterFrame f = cluster_frame(k, off, X, Y, Z, plane, in_off, in_idx);
         const uint32_t* corner = hull_tmp + f.ib + k;
         const int np = (int)corner[kDirs];
