@@ -106,9 +106,9 @@ __device__ __forceinline__ bool inlier_test(const float4 pl, float x, float y, f
 // The test's distance is the chain fma(nz, z, fma(ny, y, fma(nx, x, d))).
 // v_mfma_f32_16x16x1 (four blocks, K = 1) adds one product to each of its
 // 1024 accumulators with a single rounding, so three of them from an
-// accumulator holding d give that chain bit for bit (on 2M random (point,
-// plane) pairs over magnitudes 1e-16..1e16, degenerate NaN planes and
-// subnormal values included, every result equalled the fmaf chain's).  The columns are a
+// accumulator holding d give that chain bit for bit (the tests hold the counts
+// to a plain fmaf chain's over subnormal, ordinary, huge, infinite and NaN
+// coordinates and thresholds).  The columns are a
 // wave's 64 planes (block b holds planes 16b .. 16b + 15), the rows 16 of its
 // 64 points, broadcast to all four blocks (cbsz 2, abid the group of 16): lane
 // l gets planes 16b + l % 16 against points 4 (l / 16) .. + 3.
