@@ -397,7 +397,7 @@ vm_status vm_map_shift(vm_map m, int32_t dx, int32_t dy, int32_t dz, void* strea
     hipStream_t s = (hipStream_t)stream;
     if (capturing(s)) return VM_E_STATE;
     if (dx == 0 && dy == 0 && dz == 0) return VM_OK;
-    VM_HIP(launch_rank(m->g, m->bits, m->b, m->cap, m->ctr, s));
+    VM_HIP(launch_rank(m->g, m->bits, m->b, m->ctr, s));
     VM_HIP(launch_scroll(m->g, m->h, m->bits, m->b, m->cap, dx, dy, dz, m->ctr, s));
     const int32_t d[3] = {dx, dy, dz};
     for (int k = 0; k < 3; ++k) m->g.origin[k] = m->g.origin[k] + (double)d[k] * m->g.voxel_size;
@@ -481,7 +481,7 @@ vm_status vm_map_export(vm_map m, uint32_t* d_key, uint32_t* d_count, uint64_t* 
     if (!m || !n_out) return VM_E_ARG;
     if (capturing((hipStream_t)stream)) return VM_E_STATE;
     hipStream_t s = (hipStream_t)stream;
-    VM_HIP(launch_rank(m->g, m->bits, m->b, m->cap, m->ctr, s));
+    VM_HIP(launch_rank(m->g, m->bits, m->b, m->ctr, s));
     VM_HIP(launch_export(m->g, m->h, m->b, m->ctr, d_key, d_count, (unsigned long long*)d_sum, d_mean, cap,
                          m->n_host, s));
     VM_HIP(hipStreamSynchronize(s));
@@ -509,7 +509,7 @@ vm_status vm_ccl(vm_map m, uint32_t min_cluster, uint32_t* d_labels, vm_clusters
     hipStream_t s = (hipStream_t)stream;
     {
         StageScope t(VM_STAGE_RANK, s);
-        VM_HIP(launch_rank(m->g, m->bits, m->b, m->cap, m->ctr, s));
+        VM_HIP(launch_rank(m->g, m->bits, m->b, m->ctr, s));
     }
     VM_HIP(launch_ccl(m->g, m->bits, m->b, m->cap, m->ctr, s));
     VM_HIP(launch_group(m->g, m->h, m->b, m->cap, min_cluster, d_labels, m->ctr, s));
@@ -542,7 +542,7 @@ vm_status vm_ccl_propagate(vm_map m, uint32_t min_cluster, uint32_t* d_labels, v
     }
     {
         StageScope t(VM_STAGE_RANK, s);
-        VM_HIP(launch_rank(m->g, m->bits, m->b, m->cap, m->ctr, s));
+        VM_HIP(launch_rank(m->g, m->bits, m->b, m->ctr, s));
     }
     uint32_t* label = m->b.sort_v[1];   // free until the grouping step
     uint32_t total = 0;
@@ -597,7 +597,7 @@ vm_status vm_ccl_steppable(vm_map m, const vm_step_params* sp, uint32_t min_clus
     }
     {
         StageScope t(VM_STAGE_RANK, s);
-        VM_HIP(launch_rank(m->g, m->bits, m->b, m->cap, m->ctr, s));
+        VM_HIP(launch_rank(m->g, m->bits, m->b, m->ctr, s));
     }
     {
         StageScope t(VM_STAGE_CCL, s);

@@ -77,7 +77,7 @@ __device__ __forceinline__ void uf_unite(uint32_t* parent, uint32_t a, uint32_t 
 }
 
 struct Dims {
-    uint32_t nx, ny, nz, nxy;
+    uint32_t nx, ny, nz;
 };
 
 
@@ -968,7 +968,6 @@ Dims dims_of(const Geom& g)
     d.nx = (uint32_t)g.dims[0];
     d.ny = (uint32_t)g.dims[1];
     d.nz = (uint32_t)g.dims[2];
-    d.nxy = d.nx * d.ny;
     return d;
 }
 

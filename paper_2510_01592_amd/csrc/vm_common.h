@@ -274,8 +274,7 @@ hipError_t launch_insert(const float* xyz, int64_t n, const Pose& pose, const Ge
                          uint32_t* bits, DevCounters* ctr, const InsertScratch& sc, hipStream_t s);
 hipError_t launch_stats(const DevCounters* ctr, uint32_t log2cap, vm_map_stats_t* out, hipStream_t s);
 size_t rank_blk_words(uint32_t nwords);
-hipError_t launch_rank(const Geom& g, const uint32_t* bits, SegBuffers& b, uint32_t cap,
-                       DevCounters* ctr, hipStream_t s);
+hipError_t launch_rank(const Geom& g, const uint32_t* bits, SegBuffers& b, DevCounters* ctr, hipStream_t s);
 hipError_t launch_clear(const Geom& g, const Hash& h, uint32_t* bits, DevCounters* ctr, hipStream_t s);
 // the map's content shifted by whole voxels (after launch_rank; uses the
 // segmentation buffers as staging)

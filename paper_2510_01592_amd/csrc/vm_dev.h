@@ -334,14 +334,13 @@ __device__ __forceinline__ void swap3(double* U, double* V, uint32_t* I, uint32_
 }
 
 // One thread's chain over the points idx[0..m) (indices into U, V) in that
-// order: a point pops the stack top while it turns right of the top two
-// (strict: only strictly right; otherwise also collinear and repeated
-// points); the kept indices go to out[0..h) and h is returned.  out may be
+// order: a point pops the stack top while it does not turn left of the top
+// two (collinear and repeated points too); the kept indices go to out[0..h) and h is returned.  out may be
 // idx itself (a store lands at or below the read position).  The two top
 // entries' coordinates stay in registers, the next point's coordinates and
 // the index after it are loaded a step ahead, so a step waits for one LDS
 // load at most when it does not pop.
-template <bool kStrict, typename S>
+template <typename S>
 __device__ __forceinline__ uint32_t chain_run(const double* U, const double* V, const S* idx, uint32_t m, S* out)
 {
     uint32_t h = 0;
@@ -359,8 +358,7 @@ __device__ __forceinline__ uint32_t chain_run(const double* U, const double* V, 
         }
         if (j + 2 < m) i2 = idx[j + 2];
         while (h >= 2) {
-            const double c = cross3(au, av, bu, bv, iu, iv);
-            if (!(kStrict ? c < 0.0 : c <= 0.0)) break;
+            if (!(cross3(au, av, bu, bv, iu, iv) <= 0.0)) break;
             --h;
             bu = au;
             bv = av;
@@ -505,7 +503,7 @@ __device__ __forceinline__ WaveHull wave_hull(double u, double v, uint32_t i, ui
         uint32_t h = 0;
         if (lane < 2) {
             uint8_t* s = st + (lane ? kWave + 1 : 0);
-            h = chain_run<false>(su, sv, s, (uint32_t)__popcll(lane ? up : lo), s);
+            h = chain_run(su, sv, s, (uint32_t)__popcll(lane ? up : lo), s);
         }
         hl = __shfl(h, 0, kWave);
         hu = __shfl(h, 1, kWave);
@@ -696,7 +694,7 @@ __device__ __forceinline__ uint32_t block_chain(ChainLds<Cap>& L, uint32_t ns, L
         __syncthreads();
     }
     __syncthreads();
-    if (!settled && t == 0) L.cnt[half] = chain_run<false>(L.su, L.sv, L.list[half][buf], n, L.list[half][buf]);
+    if (!settled && t == 0) L.cnt[half] = chain_run(L.su, L.sv, L.list[half][buf], n, L.list[half][buf]);
     __syncthreads();
     // hull = lower chain, then the upper chain without its end points
     // (they are the lower chain's last and first points); the

@@ -29,7 +29,6 @@
 #include <map>
 #include <mutex>
 #include <tuple>
-#include <type_traits>
 
 namespace vm {
 namespace {

@@ -748,8 +748,7 @@ hipError_t launch_insert(const float* xyz, int64_t n, const Pose& pose, const Ge
 // words of launch_rank's tile totals
 size_t rank_blk_words(uint32_t nwords) { return (size_t)(nwords + kRankTile - 1) / kRankTile; }
 
-hipError_t launch_rank(const Geom& g, const uint32_t* bits, SegBuffers& b, uint32_t /*cap*/, DevCounters* ctr,
-                       hipStream_t s)
+hipError_t launch_rank(const Geom& g, const uint32_t* bits, SegBuffers& b, DevCounters* ctr, hipStream_t s)
 {
     Vec<1>* blk = reinterpret_cast<Vec<1>*>(b.blk);
     const uint32_t nt = (uint32_t)rank_blk_words(g.nwords);

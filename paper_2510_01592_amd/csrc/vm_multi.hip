@@ -116,13 +116,12 @@ MultiWork multi_layout(void* base, uint32_t k_cap, uint32_t n_cap, uint32_t H)
     return m;
 }
 
-// the set holding merged cluster (field 2) or point (field 3) k: the largest
-// i whose first one is at or before k
-__device__ __forceinline__ uint32_t set_of(const uint32_t* mset, uint32_t n, uint32_t k, int field)
+// the set holding merged cluster k: the largest i whose first one is at or before k
+__device__ __forceinline__ uint32_t set_of(const uint32_t* mset, uint32_t n, uint32_t k)
 {
     uint32_t i = 0;
     for (uint32_t q = 1; q < n; ++q)
-        if (mset[4 * q + field] <= k) i = q;
+        if (mset[4 * q + 2] <= k) i = q;
     return i;
 }
 
@@ -205,7 +204,7 @@ __global__ void __launch_bounds__(kMBlock) k_multi_gather(MultiTab tab, MultiWor
 // set's own in_cap (the rule of vm_hulls on the set alone).
 __device__ __forceinline__ bool fits_set(const MultiTab& tab, const MultiWork& m, uint32_t k, uint32_t* set)
 {
-    const uint32_t i = set_of(m.mset, tab.n, k, 2);
+    const uint32_t i = set_of(m.mset, tab.n, k);
     *set = i;
     return m.in_off[k + 1] - m.in_off[m.mset[4 * i + 2]] <= tab.s[i].in_cap;
 }
