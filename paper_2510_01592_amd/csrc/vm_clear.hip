@@ -20,9 +20,9 @@
 // neighbouring steps of a ray in any direction share a line.  That costs three
 // passes over the grid, whatever the number of rays; few of them walk the
 // occupancy index as it lies, with a bitmap of marks beside it (bricks_pay).
-// The marks deduplicate the removal set: whatever the
-// number of rays through a voxel, its slot is written once, by the one thread
-// that owns its word, after every ray has been cast.
+// The marks deduplicate the removal set: whatever the number of rays through a
+// voxel, its slot is written once, by the one thread that owns its word, after
+// every ray has been cast.
 //
 // What bounds the cast: VALU work per step (some 30 instructions) and the
 // 16-cycle address rate of a gather.  A wave per line spent its time on the

@@ -98,10 +98,10 @@ struct SegBuffers {
     uint32_t* occ_key;     // [cap] occupied keys, ascending
     uint32_t* parent;      // [cap] union-find parent (rank indices)
     uint32_t* csize;       // [cap] component size at its root
-    uint32_t* scan_a;      // [cap] scan scratch
+    uint32_t* scan_a;      // [cap] cluster id at roots (a scroll stages voxels here and in the next five)
     uint32_t* scan_b;      // [cap]
-    uint32_t* sort_k[2];   // [cap] radix keys (cluster id), ping-pong
-    uint32_t* sort_v[2];   // [cap] radix values (voxel key), ping-pong
+    uint32_t* sort_k[2];   // [cap] cluster ids, between passes of the sort
+    uint32_t* sort_v[2];   // [cap] voxel keys; [1] first holds the propagated labels
     uint32_t* cl_off;      // [cap+1]
     uint32_t* cl_tag;      // [cap]
     uint32_t* cl_key;      // [cap]
@@ -109,8 +109,8 @@ struct SegBuffers {
     float* cl_y;
     float* cl_z;
     uint32_t* wrank;       // [nwords+1] exclusive popcount prefix of the occupancy words
-    uint32_t* blk;         // block partials for scans (sized generously)
-    uint32_t* hist;        // radix histograms
+    uint32_t* blk;         // tile totals of the fused scans, in whole 16-byte reads
+    uint32_t* hist;        // the sort's digits per tile and digit totals
 };
 
 

@@ -335,11 +335,11 @@ __device__ __forceinline__ void swap3(double* U, double* V, uint32_t* I, uint32_
 
 // One thread's chain over the points idx[0..m) (indices into U, V) in that
 // order: a point pops the stack top while it does not turn left of the top
-// two (collinear and repeated points too); the kept indices go to out[0..h) and h is returned.  out may be
-// idx itself (a store lands at or below the read position).  The two top
-// entries' coordinates stay in registers, the next point's coordinates and
-// the index after it are loaded a step ahead, so a step waits for one LDS
-// load at most when it does not pop.
+// two (collinear and repeated points too); the kept indices go to out[0..h)
+// and h is returned.  out may be idx itself (a store lands at or below the
+// read position).  The two top entries' coordinates stay in registers, the
+// next point's coordinates and the index after it are loaded a step ahead, so
+// a step waits for one LDS load at most when it does not pop.
 template <typename S>
 __device__ __forceinline__ uint32_t chain_run(const double* U, const double* V, const S* idx, uint32_t m, S* out)
 {

@@ -144,7 +144,8 @@ __global__ void __launch_bounds__(kOneBlockThreads) k_hull_prepare(
 // a lane has four directions (q, q + 16 and their opposites) for a quarter of
 // its wave's points: a point per lane and direction took 64 LDS reads per
 // wave and 5 instructions each and was bound by both (526 us for the 34M
-// inliers of 2000 clusters, 257 us so; the bytes take about 130).  A tile's 64
+// inliers of 2000 clusters, 249 us so, 220 with the projection in fp32; the
+// bytes take about 130).  A tile's 64
 // extremes (value, position in the inlier list) go to ext_v / ext_i.
 __device__ __forceinline__ float key_of(float v, uint32_t pos, uint32_t mask)
 {
@@ -402,8 +403,9 @@ __device__ __forceinline__ bool inside_polygon(const F2* P, int np, F mg, F u, F
 // A point is first tested in fp32, by a margin above the rounding there; the
 // few near the border or outside are collected and tested in fp64 by margin[k],
 // so that one wave does for a tile what else nearly every wave would run for a
-// lane or two (34M inliers in no order: 277 us with fp64 alone, 355 us with
-// both in place, 312 us so).  The fp32 coordinates are the fp64 ones relative
+// lane or two (34M inliers in no order, 2048 workgroups: 277 us with fp64 alone,
+// 355 with both in place, 312 so; with 16384 workgroups and the points projected
+// once 227).  The fp32 coordinates are the fp64 ones relative
 // to corner 0, rounded: each errs by 2^-24 of itself and none exceeds the
 // extent E of the inliers in the plane, wherever they lie along the normal.
 // Differences then err by 3 * 2^-24 E, a product of two of them by 7 * 2^-24
@@ -863,8 +865,8 @@ vm_status hulls(const vm_clusters& cl, const vm_planes& planes, const vm_hulls_o
     }
     // the tile kernels stride over the device-side counts; many more workgroups
     // than fit at once even out what they find (34k tiles of 2000 clusters:
-    // extremes 259 us and filter 316 with 2048, of which 1792 fit, 226 and 228
-    // with 16384; a frame's few hundred tiles: 17 us either way)
+    // extremes 259 us and filter 316 with 2048, of which 1792 fit, 249 and 227
+    // with 16384; a frame's few hundred tiles: 19 us either way)
     const int tgrid = grid_for(hull_tiles_bound(kc, cl.n_cap), 1, kTileGrid);
     // the tiles' extremes lie where the survivors go afterwards: a filtered
     // cluster of m > 64 inliers has at most m / 1024 + 1 tiles of 256 bytes in

@@ -157,9 +157,10 @@ constexpr uint32_t kBucketAvg = 512;      // target points per bucket
 constexpr uint32_t kBucketMaxLog2 = 12;   // at most 4096 buckets (LDS counters)
 constexpr uint32_t kBucketChunk = 1024;   // points aggregated per LDS table fill
 constexpr uint32_t kBucketTableLog2 = 10;
-constexpr uint32_t kBucketTable = 1u << kBucketTableLog2;   // LDS table slots: 20 KB, so eight workgroups
-                                                             // fit on a CU; a bucket averages kBucketAvg
-                                                             // points, so the table is about half full
+constexpr uint32_t kBucketTable = 1u << kBucketTableLog2;   // LDS table slots: 20 KB (eight workgroups' on
+                                                             // a CU, where registers let five); a bucket
+                                                             // averages kBucketAvg points, so the table is
+                                                             // about half full
 static_assert(kBucketTable >= kBucketChunk, "a chunk's distinct keys always fit: every probe ends");
 constexpr uint32_t kRecPerThread = kBucketChunk / kBlock;   // records per thread per fill
 constexpr uint32_t kSlotPerThread = kBucketTable / kBlock;  // table entries per thread
