@@ -435,14 +435,14 @@ __device__ __forceinline__ Segment segment_at(const uint32_t* __restrict__ bits,
 // kernel cost a launch and the list's way through memory: boundary and pairs
 // took 28 + 12 us for 916k voxels, 18 + 9 for 29k (a tile per compute unit);
 // now 28 and 14.
-// kSkip: every pair has a cell of the tile, so an empty tile ends with the two
-// words of its own rows, read before all else.  That pays where most tiles are
-// empty (2000x2000x500 cells with 2000 points: 1059 us without, 387 so; with the
-// empty tile left after a row's four reads 777) and is one more wait elsewhere
-// (916k voxels in 400x400x200 cells 28 -> 32 us, 7.9M in 800x800x400 174 -> 198).
-// A map whose table has room for fewer than 256 voxels a tile, so that at half
-// load a quarter of the tiles at most can hold a surface's 512, takes it.
-constexpr uint64_t kSkipVoxels = 256;
+// Every pair has a cell of the tile, so an empty tile can end with the two words
+// of its own rows, read before all else.  That pays where most tiles are empty
+// (2000x2000x500 cells with 2000 points: 1059 us without, 387 so; with the empty
+// tile left after a row's four reads 777) and is one more wait elsewhere (916k
+// voxels in 400x400x200 cells, 217 a tile, 28 -> 32 us, 7.9M in 800x800x400, 254 a
+// tile, 174 -> 198).  A tile that holds a surface has some 512 voxels, so with
+// fewer than 64 a tile most are empty.
+constexpr uint64_t kSkipVoxels = 64;
 
 constexpr uint32_t kPairHash = 1024;   // LDS hash set of root pairs per tile
 constexpr uint32_t kTilePairs = 256;   // distinct pairs listed per tile
@@ -469,8 +469,8 @@ __device__ __forceinline__ FacePair face_pair(uint32_t t)
     return i < kTZ - 1 ? FacePair{0, 1 + i, -1, -1} : FacePair{kTY - 1, i - (kTZ - 2), 1, -1};
 }
 
-template <bool kSkip>
-__global__ void __launch_bounds__(kBlock) k_ccl_boundary(const uint32_t* __restrict__ bits, uint32_t nwords,
+__global__ void __launch_bounds__(kBlock) k_ccl_boundary(const DevCounters* __restrict__ ctr,
+                                                         const uint32_t* __restrict__ bits, uint32_t nwords,
                                                          const uint32_t* __restrict__ wrank, Dims d, TileGrid tg,
                                                          uint32_t* parent)
 {
@@ -497,13 +497,14 @@ __global__ void __launch_bounds__(kBlock) k_ccl_boundary(const uint32_t* __restr
     __shared__ uint32_t wtot[kBlock / kWave];
     const int lane = (int)(j & (kWave - 1)), wave = (int)(j / kWave);
     const uint32_t nv = xcd_virtual_tiles(tg);
+    const bool skip = ctr->n_occ < kSkipVoxels * nv;
     for (uint32_t v0 = blockIdx.x; v0 < nv; v0 += gridDim.x) {
         uint32_t t;
         if (!xcd_tile(v0, tg, &t)) continue;   // uniform over the workgroup
         const uint32_t tx = t % tg.ntx, ty = (t / tg.ntx) % tg.nty, tz = t / (tg.ntx * tg.nty);
         const uint32_t x0 = tx * kTX;
         const int y = (int)(ty * kTY) + yl, z = (int)(tz * kTZ) + zl;
-        if (kSkip) {
+        if (skip) {
             uint32_t key0;
             if (!__syncthreads_or(row_bits(bits, nwords, d, x0, (uint32_t)y, (uint32_t)z, &key0) != 0u)) continue;
         }
@@ -991,9 +992,7 @@ hipError_t launch_ccl(const Geom& g, const uint32_t* bits, SegBuffers& b, uint32
     }
     {
         StageScope t(VM_STAGE_CCL_LINK, s);
-        const bool skip = cap < kSkipVoxels * nv;
-        if (skip) k_ccl_boundary<true><<<vgrid, kBlock, 0, s>>>(bits, g.nwords, b.wrank, d, tg, b.parent);
-        else k_ccl_boundary<false><<<vgrid, kBlock, 0, s>>>(bits, g.nwords, b.wrank, d, tg, b.parent);
+        k_ccl_boundary<<<vgrid, kBlock, 0, s>>>(ctr, bits, g.nwords, b.wrank, d, tg, b.parent);
         k_ccl_flatten<<<grid_for(cap, kFlatBlock, 1024), kFlatBlock, 0, s>>>(ctr, b.parent, b.csize);
     }
     return hipGetLastError();

@@ -1,8 +1,8 @@
-"""Labelling of grids whose table has room for few voxels a tile, where the face
-kernel leaves empty tiles at once: clouds of a few voxels, blobs across faces,
+"""Labelling of grids with few voxels a tile, where the face kernel leaves empty
+tiles at once, and of one on each side of the line: clouds of a few voxels, blobs across faces,
 edges and corners of tiles, a diagonal through every tile corner, lines along
 each axis, and tiles with one voxel beside empty ones -- labels and clusters
-exact against the oracle, and the same from a map with a large table."""
+exact against the oracle."""
 import numpy as np
 import pytest
 
@@ -24,6 +24,12 @@ def _fills(dims, rng):
     yield "diagonal", np.c_[t, t, t]
     yield "lines", np.concatenate([np.c_[t, 0 * t + 15, 0 * t + 16], np.c_[0 * t + 31, t, 0 * t + 3], np.c_[0 * t + 64, 0 * t + 1, t]])
     yield "one voxel", d[None] - 1
+    # 64 voxels a tile, counting the tile rows of all eight dies: one less, and as many
+    tiles = 8 * -(-dims[0] // 32) * -(-(-(-dims[1] // 16) * -(-dims[2] // 16)) // 8)
+    cells = rng.choice(int(np.prod(d)), min(64 * tiles, int(np.prod(d))), replace=False)
+    cells = np.c_[cells % dims[0], cells // dims[0] % dims[1], cells // (dims[0] * dims[1])]
+    yield "below the line", cells[:-1]
+    yield "at the line", cells
 
 
 @pytest.mark.parametrize("dims", [(97, 66, 65), (129, 40, 100), (33, 200, 48), (64, 16, 700)])
@@ -39,15 +45,14 @@ def test_sparse_labels_equal_the_oracle(dims):
         om.insert(pts)
         ref = oracle.ccl26(om.key, om.dims)[0]
         c = oracle.group(om.key, ref, om.means(), 2)
-        for log2 in (13, 18):
-            m = vm.Map((0.0, 0.0, 0.0), s, dims, log2)
-            m.insert(torch.from_numpy(pts).cuda())
-            lab = torch.zeros(len(om.key), dtype=torch.int32, device="cuda")
-            note(f"ccl sparse {dims} {name} table 2^{log2}")
-            cl = m.ccl(2, labels=lab)
-            torch.cuda.synchronize()
-            assert np.array_equal(lab.cpu().numpy().view(np.uint32), ref), name
-            got = vm.read_clusters(cl)
-            assert np.array_equal(got["off"], c.off) and np.array_equal(got["tag"], c.tag), name
-            assert np.array_equal(got["key"], c.key), name
-            m.close()
+        m = vm.Map((0.0, 0.0, 0.0), s, dims, 18)
+        m.insert(torch.from_numpy(pts).cuda())
+        lab = torch.zeros(len(om.key), dtype=torch.int32, device="cuda")
+        note(f"ccl sparse {dims} {name}")
+        cl = m.ccl(2, labels=lab)
+        torch.cuda.synchronize()
+        assert np.array_equal(lab.cpu().numpy().view(np.uint32), ref), name
+        got = vm.read_clusters(cl)
+        assert np.array_equal(got["off"], c.off) and np.array_equal(got["tag"], c.tag), name
+        assert np.array_equal(got["key"], c.key), name
+        m.close()
